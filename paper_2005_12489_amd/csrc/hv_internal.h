@@ -116,6 +116,8 @@ struct BatchHeader {
     int32_t counter;    // tiles appended to the compacted list (0 when staged)
     int32_t ecounter;   // tiles with no data within r, listed for zero-filling (0 when staged)
     uint64_t t_start;   // wall clock when the batch started on the device
+    int32_t leaf_tiles; // tiles for the object kernel: frontier at the leaves (0 when staged)
+    int32_t node_tiles; // and one level above (0 when staged)
 };
 
 // Device addresses of one batch's workspace (a kernel argument).
@@ -126,8 +128,8 @@ struct DevBatch {
     const uint32_t *order;  // the requests by zoom, lowest first: the tile-frontier kernel's order
     uint32_t *frontier;  // per request: up to 256 frontier nodes
     int32_t *fmeta;      // per request: frontier size, frontier level, 64 bits of regions it reaches
-    uint32_t *list;      // compacted list of requests with data nearby
-    uint32_t *elist;     // requests whose tile has no data within r
+    uint32_t *list;      // from the front: requests for the region kernel; from the back: leaf_tiles
+    uint32_t *elist;     // from the front: requests whose tile has no data within r; from the back: node_tiles
     uint32_t *done;      // per request: parts finished
     uint64_t *ts;        // per request: wall clock at completion
 };
@@ -159,6 +161,15 @@ DevBatch device_batch(const Workspace &w, unsigned char *dws);
 hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, const LaunchShape &s,
                         hipStream_t stream, hipEvent_t *marks = nullptr);
 
+
+// The object kernel (hv_objects.h): tiles whose frontier lies at the leaves or
+// one level above, in strips of whole pixel rows, a workgroup to a strip.  More
+// strips spread a tile's objects over more workgroups, and each reads the
+// frontier anew.
+constexpr int kLeafStrips = 4;         // up to 4,096 objects in reach
+constexpr int kNodeStrips = 16;        // up to 65,536
+constexpr int kStripRows = 64;         // most rows of a strip
+constexpr int64_t kObjectsGrid = 4096;
 
 // Workgroups that fill the current device for a shape (occupancy x CUs).
 int persistent_grid(const LaunchShape &s, int max_levels);

@@ -49,6 +49,17 @@ __device__ inline uint32_t lanes_below(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// Reserves popcount(hm) consecutive slots of *counter for the wave's set lanes.
+__device__ inline int wave_alloc(int *counter, uint64_t hm, int lane) {
+    int base = 0;
+    if (hm) {
+        const int first = __ffsll((unsigned long long)hm) - 1;
+        if (lane == first) base = atomicAdd(counter, __popcll(hm));
+        base = __shfl(base, first, 64);
+    }
+    return base + (int)lanes_below(hm);
+}
+
 // The frontier level holds at most kFrontier entries, every level below it at
 // most 64 (a level is pushed only when none of its entries remain).
 __host__ __device__ constexpr int stack_words(int levels) { return 64 * (levels > 0 ? levels : 1) + kFrontier; }
@@ -100,13 +111,24 @@ __device__ inline uint64_t wave_or64(uint64_t v) {
 // while that level holds at most cull nodes meeting the tile.
 // grow (px) widens the tile's box beyond r on every side: 1/4 for
 // anti-aliased output, whose sub-samples lie 1/4 px from the pixel centres.
-__global__ __launch_bounds__(256) void k_tile_frontier(DevBatch B, int rs, int cull, double grow) {
-    __shared__ uint32_t buf[4][2][kFrontier];
+// objects: tiles whose frontier lies at level 0 or 1 go to the object kernel's
+// lists, not to the region kernel's.
+// WPT wavefronts per request: one in large batches, which fill the GPU anyway;
+// in small ones the walk's time is its chain of loads, up to 4,096 children of
+// a level's 256 nodes, and more wavefronts shorten it.
+template <int WPT>
+__global__ __launch_bounds__(WPT > 4 ? 64 * WPT : 256) void k_tile_frontier(DevBatch B, int rs, int cull, double grow, int objects) {
+    constexpr int kTiles = WPT > 4 ? 1 : 4 / WPT;  // requests of a workgroup
+    __shared__ uint32_t buf[kTiles][2][kFrontier];
+    __shared__ int count[kTiles];
+    __shared__ unsigned long long regions[kTiles];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: keeps per-tile values scalar
+    const int slot = wv / WPT, tid = (int)threadIdx.x - slot * 64 * WPT;
     if (blockIdx.x == 0 && threadIdx.x == 0) B.hdr->t_start = wall_clock64();
-    const int64_t i = (int64_t)blockIdx.x * 4 + wv;
-    if (i >= B.hdr->n_req) return;
+    const int64_t i = (int64_t)blockIdx.x * kTiles + slot;
+    const int64_t n_req = B.hdr->n_req;
+    if (i >= n_req) return;  // with several wavefronts to a request, a whole workgroup's
     const int64_t t = B.order[i];  // requests by zoom, lowest first: the list follows this order
     const DevReq rq = B.reqs[t];
     const DevIndex ix = B.ixs[rq.index];
@@ -115,25 +137,72 @@ __global__ __launch_bounds__(256) void k_tile_frontier(DevBatch B, int rs, int c
     const double m = rq.r + grow + kCullPad;
     const double qx0 = (ox + (0.5 - m)) * iS, qx1 = (ox + (255.5 + m)) * iS;
     const double qy0 = (oy + (0.5 - m)) * iS, qy1 = (oy + (255.5 + m)) * iS;
-    uint32_t *cur = buf[wv][0], *nxt = buf[wv][1];
+    uint32_t *cur = buf[slot][0], *nxt = buf[slot][1];
     int ncur = 0, lvl = ix.levels - 1;
     uint64_t cbits = ~0ull;  // regions the current frontier level can reach
-    if (ix.levels > 0) {
-        const double4 root = ix.nodes[ix.meta[ix.levels - 1]];
-        if (meets(root, qx0, qx1, qy0, qy1)) {
-            if (lane == 0) cur[0] = 0;
-            ncur = 1;
-            if (rs) cbits = region_bits(root, S, ox, oy, m, rs);
+    auto sync = [&]() {
+        if (WPT > 1) __syncthreads();
+        else __builtin_amdgcn_wave_barrier();
+    };
+    auto begin_level = [&]() {
+        if (WPT > 1) {
+            if (tid == 0) {
+                count[slot] = 0;
+                regions[slot] = 0;
+            }
+            __syncthreads();
         }
+    };
+    // appends the lanes' hits to a level's list of `n` nodes; its new length
+    auto take = [&](bool hit, uint32_t node, uint32_t *to, int n) -> int {
+        const uint64_t hm = __ballot(hit);
+        const int pos = WPT > 1 ? wave_alloc(&count[slot], hm, lane) : n + (int)lanes_below(hm);
+        if (hit && pos < cull) to[pos] = node;
+        if (WPT == 1) return n + __popcll(hm);
+        __syncthreads();
+        n = count[slot];
+        __syncthreads();
+        return n;
+    };
+    auto end_level = [&](uint64_t bits) {
+        if (!rs) return;
+        cbits = wave_or64(bits);
+        if (WPT > 1) {
+            if (lane == 0) atomicOr(&regions[slot], (unsigned long long)cbits);
+            __syncthreads();
+            cbits = regions[slot];
+            __syncthreads();
+        }
+    };
+    // The walk starts at the first level, from the top, whose next level has
+    // more nodes than a frontier may hold, all of that level's nodes tested at
+    // once: each level above it would cost a memory latency or two.
+    if (lvl >= 0) {
+        while (lvl > 0 && ix.meta[kMaxLevels + lvl - 1] <= cull) --lvl;
+        const int64_t cnt = ix.meta[kMaxLevels + lvl], off = ix.meta[lvl];
+        uint64_t nbits = 0;
+        begin_level();
+        for (int base = 0; base < (int)cnt; base += 64 * WPT) {
+            const int k = base + tid;
+            bool hit = false;
+            if (k < (int)cnt) {
+                const double4 nb = ix.nodes[off + k];
+                hit = meets(nb, qx0, qx1, qy0, qy1);
+                if (hit && rs) nbits |= region_bits(nb, S, ox, oy, m, rs);
+            }
+            ncur = take(hit, (uint32_t)k, cur, ncur);
+        }
+        sync();
+        end_level(nbits);
     }
-    __builtin_amdgcn_wave_barrier();
     while (lvl > 0 && ncur > 0) {
         const int cl = lvl - 1;
         const int64_t cnt = ix.meta[kMaxLevels + cl], off = ix.meta[cl];
         int nn = 0;
         uint64_t nbits = 0;
-        for (int base = 0; base < ncur * kFan; base += 64) {
-            const int k = base + lane;
+        begin_level();
+        for (int base = 0; base < ncur * kFan; base += 64 * WPT) {
+            const int k = base + tid;
             bool hit = false;
             int64_t child = 0;
             if (k < ncur * kFan) {
@@ -144,32 +213,31 @@ __global__ __launch_bounds__(256) void k_tile_frontier(DevBatch B, int rs, int c
                     if (hit && rs) nbits |= region_bits(nb, S, ox, oy, m, rs);
                 }
             }
-            const uint64_t hm = __ballot(hit);
-            const int pos = nn + (int)lanes_below(hm);
-            if (hit && pos < cull) nxt[pos] = (uint32_t)child;
-            nn += __popcll(hm);
+            nn = take(hit, (uint32_t)child, nxt, nn);
             if (nn > cull) break;
         }
-        __builtin_amdgcn_wave_barrier();
+        sync();
         if (nn > cull) break;
         uint32_t *tmp = cur;
         cur = nxt;
         nxt = tmp;
         ncur = nn;
-        if (rs) cbits = wave_or64(nbits);
+        end_level(nbits);
         --lvl;
     }
     if (ncur == 0) {
         // no data within r of the tile: its mask is all zero, written by the
         // query kernel
-        if (lane == 0) B.elist[atomicAdd(&B.hdr->ecounter, 1)] = (uint32_t)t;
+        if (tid == 0) B.elist[atomicAdd(&B.hdr->ecounter, 1)] = (uint32_t)t;
         return;
     }
-    for (int k = lane; k < ncur; k += 64) B.frontier[t * kFrontier + k] = cur[k];
-    if (lane == 0) {
+    for (int k = tid; k < ncur; k += 64 * WPT) B.frontier[t * kFrontier + k] = cur[k];
+    if (tid == 0) {
         reinterpret_cast<int4 *>(B.fmeta)[t] = make_int4(ncur, lvl, (int)(uint32_t)cbits, (int)(uint32_t)(cbits >> 32));
         B.done[t] = 0;
-        B.list[atomicAdd(&B.hdr->counter, 1)] = (uint32_t)t;
+        if (objects && lvl == 0) B.list[n_req - 1 - atomicAdd(&B.hdr->leaf_tiles, 1)] = (uint32_t)t;
+        else if (objects && lvl == 1) B.elist[n_req - 1 - atomicAdd(&B.hdr->node_tiles, 1)] = (uint32_t)t;
+        else B.list[atomicAdd(&B.hdr->counter, 1)] = (uint32_t)t;
     }
 }
 
@@ -492,6 +560,14 @@ __global__ __launch_bounds__(256) void k_query(DevBatch B, int cap, int max_leve
     }
 }
 
+}  // namespace
+}  // namespace hv
+
+#include "hv_objects.h"
+
+namespace hv {
+namespace {
+
 // ------------------------------------------------------------ region mode
 // One workgroup per RS x RS region of a tile.  It walks the tree once with
 // the region's box grown by r, all lanes testing children together, and
@@ -538,17 +614,6 @@ struct RegionLds {
     int *ctl;        // [0] stack size, [1] queued objects
     uint32_t *scan;  // 16 words
 };
-
-// Reserves popcount(hm) consecutive slots of *counter for the wave's set lanes.
-__device__ inline int wave_alloc(int *counter, uint64_t hm, int lane) {
-    int base = 0;
-    if (hm) {
-        const int first = __ffsll((unsigned long long)hm) - 1;
-        if (lane == first) base = atomicAdd(counter, __popcll(hm));
-        base = __shfl(base, first, 64);
-    }
-    return base + (int)lanes_below(hm);
-}
 
 // Exclusive scan over the workgroup (blockDim a multiple of 64, at most
 // 1024); `scan` holds 16 words of LDS.  Every thread must call it.
@@ -1124,10 +1189,7 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
 }
 
 template <int RS, int OPL, int AA>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_query_region(DevBatch B, int cap, int max_levels) {
-    extern __shared__ double4 smem[];
-    constexpr int RPT = (256 / RS) * (256 / RS);
-    unsigned char *base = reinterpret_cast<unsigned char *>(smem);
+__device__ inline RegionLds region_lds(unsigned char *base, int cap, int max_levels) {
     RegionLds L;
     L.stk = reinterpret_cast<uint32_t *>(base);
     unsigned char *cb = base + align16((size_t)query_stack_words(max_levels, blockDim.x, OPL) * 4);
@@ -1139,18 +1201,66 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     L.mask = reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(L.cpre) + align16((size_t)(cap + 1) * 4));
     L.ctl = reinterpret_cast<int *>(L.mask + RS * (RS / 32) * (AA ? 4 : 1));
     L.scan = reinterpret_cast<uint32_t *>(L.ctl + 4);
+    return L;
+}
+
+// Region `reg` of the k-th listed tile.
+template <int RS, int OPL, int AA>
+__device__ __forceinline__ void region_item(const DevBatch &B, int64_t k, int reg, uint8_t *out, int cap,
+                                            const RegionLds &L) {
+    const int64_t t = B.list[k];
+    const DevReq rq = B.reqs[t];
+    const DevIndex ix = B.ixs[rq.index];
+    if (ix.seg) region_query<RS, 1, OPL, AA>(ix, rq, t, reg, B.frontier, B.fmeta, out, cap, L);
+    else region_query<RS, 0, OPL, AA>(ix, rq, t, reg, B.frontier, B.fmeta, out, cap, L);
+    if (threadIdx.x == 0) part_done(B, t, (256 / RS) * (256 / RS));
+}
+
+template <int RS, int OPL, int AA>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_query_region(DevBatch B, int cap, int max_levels) {
+    extern __shared__ double4 smem[];
+    constexpr int RPT = (256 / RS) * (256 / RS);
+    const RegionLds L = region_lds<RS, OPL, AA>(reinterpret_cast<unsigned char *>(smem), cap, max_levels);
     uint8_t *const out = B.hdr->out;
     zero_empty_tiles(B, out, AA ? HV_AA_BYTES : HV_MASK_BYTES);
     const ItemMap im(B.hdr->counter, RPT);
-    for (int64_t u = im.first; u < im.n; u += im.step) {
-        const int64_t t = B.list[im.pos(u, RPT)];
-        const int reg = (int)(u % RPT);
-        const DevReq rq = B.reqs[t];
-        const DevIndex ix = B.ixs[rq.index];
-        if (ix.seg) region_query<RS, 1, OPL, AA>(ix, rq, t, reg, B.frontier, B.fmeta, out, cap, L);
-        else region_query<RS, 0, OPL, AA>(ix, rq, t, reg, B.frontier, B.fmeta, out, cap, L);
-        if (threadIdx.x == 0) part_done(B, t, RPT);
+    for (int64_t u = im.first; u < im.n; u += im.step)
+        region_item<RS, OPL, AA>(B, im.pos(u, RPT), (int)(u % RPT), out, cap, L);
+}
+
+// The object kernel alone, and, for batches small enough that each kernel's
+// last workgroups leave the GPU idle (the default's four-wave shape), both
+// kinds of work in one launch, regions first.
+template <int AA>
+__global__ __launch_bounds__(kStripThreads) __attribute__((amdgpu_waves_per_eu(AA ? 4 : 5))) void k_query_objects(DevBatch B) {
+    __shared__ __align__(16) StripLds<AA> L;
+    const int64_t items = object_items(B, kLeafStrips, kNodeStrips);
+    for (int64_t u = blockIdx.x; u < items; u += gridDim.x) object_item<AA>(B, u, kLeafStrips, kNodeStrips, B.hdr->out, L);
+}
+
+// Up to this many requests leave workgroups to spare: tiles are cut into twice
+// the strips (a screen of 21 tiles 47 -> 32 us; 256 sparse tiles 20 -> 25).
+constexpr int kFewRequests = 64;
+constexpr int kBothWaves = kStripThreads / 64, kBothRegion = 32, kBothOpl = 2;
+
+template <int AA>
+__global__ __launch_bounds__(kStripThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_query_both(DevBatch B, int cap, int max_levels) {
+    const bool few = B.hdr->n_req <= kFewRequests;
+    const int sl = few ? 2 * kLeafStrips : kLeafStrips, sn = few ? 2 * kNodeStrips : kNodeStrips;
+    extern __shared__ double4 smem[];
+    constexpr int RPT = (256 / kBothRegion) * (256 / kBothRegion);
+    const RegionLds L = region_lds<kBothRegion, kBothOpl, AA>(reinterpret_cast<unsigned char *>(smem), cap, max_levels);
+    uint8_t *const out = B.hdr->out;
+    zero_empty_tiles(B, out, AA ? HV_AA_BYTES : HV_MASK_BYTES);
+    const int64_t regions = (int64_t)B.hdr->counter * RPT, items = regions + object_items(B, sl, sn);
+    for (int64_t u = blockIdx.x; u < items; u += gridDim.x) {
+        if (u < regions) region_item<kBothRegion, kBothOpl, AA>(B, u / RPT, (int)(u % RPT), out, cap, L);
+        else object_item<AA>(B, u - regions, sl, sn, out, *reinterpret_cast<StripLds<AA> *>(smem));
     }
+}
+
+bool in_one_launch(const LaunchShape &s) {
+    return !s.fill && s.region == kBothRegion && s.waves == kBothWaves && s.opl == kBothOpl;
 }
 
 // ------------------------------------------------------------ polygon filling
@@ -1576,6 +1686,9 @@ __global__ __launch_bounds__(256) void k_fill_region(DevBatch B, int cap, int ma
     }
 }
 
+// Batches of up to this many requests take four wavefronts to a request's frontier.
+constexpr int64_t kWideFrontier = 512;
+
 using RegionKernel = void (*)(DevBatch, int, int);
 
 template <int AA>
@@ -1585,7 +1698,10 @@ RegionKernel region_kernel_aa(const LaunchShape &s) {
     return s.opl == 4 ? k_query_region<64, 4, AA> : s.opl == 2 ? k_query_region<64, 2, AA> : k_query_region<64, 1, AA>;
 }
 
-RegionKernel region_kernel(const LaunchShape &s) { return s.aa ? region_kernel_aa<1>(s) : region_kernel_aa<0>(s); }
+RegionKernel region_kernel(const LaunchShape &s) {
+    if (in_one_launch(s)) return s.aa ? k_query_both<1> : k_query_both<0>;
+    return s.aa ? region_kernel_aa<1>(s) : region_kernel_aa<0>(s);
+}
 
 struct GridKey {
     int device, block, waves, region, opl, fill, aa;
@@ -1597,7 +1713,10 @@ struct GridKey {
 
 size_t query_lds_bytes(const LaunchShape &s, int max_levels) {
     if (s.fill) return fill_lds_bytes(s.cand_cap, max_levels, 64 * s.waves, s.region);
-    if (s.region) return region_lds_bytes(s.cand_cap, max_levels, 64 * s.waves, s.region, s.opl, s.aa);
+    if (s.region) {
+        const size_t b = region_lds_bytes(s.cand_cap, max_levels, 64 * s.waves, s.region, s.opl, s.aa);
+        return in_one_launch(s) ? std::max(b, s.aa ? sizeof(StripLds<1>) : sizeof(StripLds<0>)) : b;
+    }
     return (size_t)s.waves * wave_lds_bytes(s.cand_cap, max_levels, s.block);
 }
 
@@ -1693,9 +1812,20 @@ hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, 
     const DevBatch B = device_batch(w, dws);
     hipError_t e;
     if (marks && (e = hipEventRecord(marks[0], st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_tile_frontier, dim3((uint32_t)((n_req + 3) / 4)), dim3(256), 0, st, B, s.region, s.cull,
-                       s.aa ? 0.25 : 0.0);
+    const double grow = s.aa ? 0.25 : 0.0;
+    const int objects = s.region && !s.fill;
+    if (n_req <= kWideFrontier)
+        hipLaunchKernelGGL(k_tile_frontier<4>, dim3((uint32_t)n_req), dim3(256), 0, st, B, s.region, s.cull, grow, objects);
+    else
+        hipLaunchKernelGGL(k_tile_frontier<1>, dim3((uint32_t)((n_req + 3) / 4)), dim3(256), 0, st, B, s.region, s.cull,
+                           grow, objects);
     if (marks && (e = hipEventRecord(marks[1], st)) != hipSuccess) return e;
+    if (s.region && !s.fill && !in_one_launch(s)) {
+        const int64_t items = n_req * kNodeStrips;
+        const dim3 go((uint32_t)(items < kObjectsGrid ? items : kObjectsGrid));
+        if (s.aa) hipLaunchKernelGGL(k_query_objects<1>, go, dim3(kStripThreads), 0, st, B);
+        else hipLaunchKernelGGL(k_query_objects<0>, go, dim3(kStripThreads), 0, st, B);
+    }
     const size_t lds = query_lds_bytes(s, max_levels);
     // never more workgroups than there are blocks (or regions) to render
     const int64_t per_tile = s.region ? (256 / s.region) * (256 / s.region)
