@@ -51,12 +51,13 @@ hv::DevIndex dev_view(const hv_index *ix) {
     d.n = ix->a.n;
     d.levels = ix->a.levels;
     d.seg = ix->a.seg;
-    d.order = ix->a.order;
+    d.cells = ix->a.cells;
+    d.cell_top = ix->a.cell_top;
+    d.cell_gaps = ix->a.cell_gaps;
     d.pedges = ix->p.edges;
     d.pfirst = ix->p.first;
     d.pchunk = ix->p.chunks;
     d.psuper = ix->p.supers;
-    d.npoly = ix->p.npoly;
     return d;
 }
 
@@ -348,7 +349,7 @@ hv_index *hv_index_build(const double *objects, int kind, int64_t n) {
         delete ix;
         return nullptr;
     }
-    const hv::BuildResult br = hv::build_index(objects, kind, n, t_stream, &ix->a);
+    const hv::BuildResult br = hv::build_index(objects, kind, n, t_stream, &ix->a, true);
     if (br.status != HV_OK) {
         fail(br.status, std::string("hv_index_build: ") + br.msg);
         hv::free_index_arrays(&ix->a);

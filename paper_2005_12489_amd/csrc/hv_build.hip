@@ -494,7 +494,7 @@ BuildResult build_polygons(const double *edges, int64_t n, const int64_t *first,
         free_poly_arrays(poly);
         return {HV_EINVAL, "edges hold a non-finite coordinate, |lon| > 180 or |lat| > 90"};
     }
-    const BuildResult r = build_index(diag, HV_SEGMENTS | HV_INPUT_MERC01, npoly, st, tree);
+    const BuildResult r = build_index(diag, HV_SEGMENTS | HV_INPUT_MERC01, npoly, st, tree, false);
     if (r.status != HV_OK) {
         release();
         free_poly_arrays(poly);
@@ -545,6 +545,9 @@ void free_index_arrays(IndexArrays *a) {
     if (a->rep) (void)hipFree(a->rep);
     if (a->order) (void)hipFree(a->order);
     if (a->meta) (void)hipFree(a->meta);
+    if (a->cells) (void)hipFree(a->cells);
+    a->cells = nullptr;
+    a->cell_top = -1;
     a->obj = nullptr;
     a->nodes = nullptr;
     a->rep = nullptr;
@@ -561,7 +564,8 @@ void free_index_arrays(IndexArrays *a) {
         }                                     \
     } while (0)
 
-BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStream_t st, IndexArrays *out) {
+BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStream_t st, IndexArrays *out,
+                        bool with_cells) {
     const int kind = kind_flags & 0xff;
     const int merc = (kind_flags & HV_INPUT_MERC01) != 0;
     const int seg = kind != HV_POINTS;
@@ -602,14 +606,14 @@ BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStr
     double *proj;
     uint64_t *k0, *k1;
     uint32_t *v0, *v1, *counts, *part;
-    int *err;
+    CellFlags *flags;
     HV_TRY(s.alloc(&proj, sizeof(double) * W * n));
     HV_TRY(s.alloc(&k0, sizeof(uint64_t) * n));
     HV_TRY(s.alloc(&k1, sizeof(uint64_t) * n));
     HV_TRY(s.alloc(&v1, sizeof(uint32_t) * n));
     HV_TRY(s.alloc(&counts, sizeof(uint32_t) * ncount));
     HV_TRY(s.alloc(&part, sizeof(uint32_t) * npart));
-    HV_TRY(s.alloc(&err, sizeof(int)));
+    HV_TRY(s.alloc(&flags, sizeof(CellFlags)));
     HV_TRY(hipMalloc((void **)&out->obj, sizeof(double) * W * n));
     HV_TRY(hipMalloc((void **)&out->order, sizeof(uint32_t) * n));
     HV_TRY(hipMalloc((void **)&out->nodes, sizeof(double4) * total));
@@ -617,6 +621,21 @@ BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStr
     v0 = out->order;  // the sort's value buffer doubles as the stored order
     out->device_bytes = (int64_t)(sizeof(double) * W * n + sizeof(uint32_t) * n +
                                   (sizeof(double4) + sizeof(double2)) * total);
+    // the cells are an aid only: without memory for them the index does
+    // without
+    uint32_t *longs = nullptr;
+    if (with_cells && cell_top(n) >= 0) {
+        const int top = cell_top(n);
+        const size_t bytes = sizeof(uint32_t) * (size_t)cell_level_words(top + 1);
+        if ((!seg || s.alloc(&longs, cell_long_bytes()) == hipSuccess) &&
+            hipMalloc((void **)&out->cells, bytes) == hipSuccess) {
+            out->cell_top = top;
+            out->device_bytes += (int64_t)bytes;
+        } else {
+            (void)hipGetLastError();
+            out->cells = nullptr;
+        }
+    }
 
     {
         int64_t meta[2 * kMaxLevels] = {};
@@ -626,12 +645,12 @@ BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStr
         }
         HV_TRY(hipMemcpy(out->meta, meta, sizeof(meta), hipMemcpyHostToDevice));
     }
-    HV_TRY(hipMemsetAsync(err, 0, sizeof(int), st));
+    HV_TRY(hipMemsetAsync(flags, 0, sizeof(CellFlags), st));
     const int64_t g = cdiv(n, 256);
     if (seg)
-        hipLaunchKernelGGL(k_project_key<4>, dim3((uint32_t)g), dim3(256), 0, st, objects, n, merc, proj, k0, v0, bits, err);
+        hipLaunchKernelGGL(k_project_key<4>, dim3((uint32_t)g), dim3(256), 0, st, objects, n, merc, proj, k0, v0, bits, &flags->bad);
     else
-        hipLaunchKernelGGL(k_project_key<2>, dim3((uint32_t)g), dim3(256), 0, st, objects, n, merc, proj, k0, v0, bits, err);
+        hipLaunchKernelGGL(k_project_key<2>, dim3((uint32_t)g), dim3(256), 0, st, objects, n, merc, proj, k0, v0, bits, &flags->bad);
     HV_TRY(hipGetLastError());
 
     uint64_t *kin = k0, *kout = k1;
@@ -675,10 +694,13 @@ BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStr
                                out->rep + out->level_off[l], np);
     }
     HV_TRY(hipGetLastError());
-    int herr = 0;
-    HV_TRY(hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, st));
+    if (out->cells) HV_TRY(build_cells(out->obj, n, seg, out->cell_top, out->cells, flags, longs, st));
+    CellFlags found;
+    HV_TRY(hipMemcpyAsync(&found, flags, sizeof found, hipMemcpyDeviceToHost, st));
     HV_TRY(hipStreamSynchronize(st));
-    if (herr) {
+    out->cell_gaps = found.gaps;
+    if (found.outside) out->cell_top = -1;
+    if (found.bad) {
         free_index_arrays(out);
         return {HV_EINVAL, "objects hold a non-finite coordinate, |lon| > 180 or |lat| > 90"};
     }

@@ -28,15 +28,53 @@ struct DevIndex {
     int64_t n;
     int32_t levels;
     int32_t seg;                 // 0 points, 1 segments / edges
+    const uint32_t *cells;       // occupancy cells, levels 0 .. cell_top (cell_top < 0: none)
+    int32_t cell_top;
+    int32_t cell_gaps;           // 1: a cell without a bit may still hold an object
     // polygon indexes only (filling): the tree above holds the polygons'
     // bounding boxes as diagonals, in sorted order
-    const uint32_t *order;       // sorted position -> polygon
     const double *pedges;        // edges, 4 doubles each, polygon after polygon in sorted order
     const int64_t *pfirst;       // the polygon at sorted position k owns edges [pfirst[k], pfirst[k + 1])
     const float4 *pchunk;        // chunk c: a box holding edges [kEdgeChunk c, kEdgeChunk (c + 1))
     const float4 *psuper;        // super-chunk s: a box holding chunks [kChunkSuper s, kChunkSuper (s + 1))
-    int64_t npoly;
 };
+
+// Occupancy cells (hv_cells.hip).  Level l is a grid of 2^(8 + l) x 2^(8 + l)
+// cells over the world, stored by word columns: bit b of word (xw, y) is cell
+// (32 xw + b, y), and a column's rows lie next to each other, so that a run of
+// rows is one wide load.  kCellPad rows above and below and one column on
+// either side are always zero, so that a look over the world's edge needs no
+// test.
+constexpr int kCellPad = 64;
+constexpr int kCellTopMax = 9;             // 2^34 cells, 2 GiB
+constexpr double kCellBitsPerObject = 32;  // the finest level has at most this many cells per object
+
+__host__ __device__ constexpr int64_t cell_stride(int level) { return (int64_t(256) << level) + 2 * kCellPad; }
+// Words of the levels below `level`: the offset of its first word.
+__host__ __device__ constexpr int64_t cell_level_words(int level) {
+    // a level has (8 * 2^l + 2) (256 * 2^l + 2 kCellPad) words
+    return 2048 * (((int64_t(1) << (2 * level)) - 1) / 3) + (512 + 16 * kCellPad) * ((int64_t(1) << level) - 1) +
+           4 * kCellPad * level;
+}
+// Word (0, 0) of a level, from the level's first word.
+__host__ __device__ constexpr int64_t cell_origin(int level) { return cell_stride(level) + kCellPad; }
+
+// What marking the cells found, in device memory.
+struct CellFlags {
+    int32_t bad;                    // a coordinate is not finite or out of range
+    int32_t outside;                // an object lies outside [0, 1]^2: the cells are not used
+    int32_t gaps;                   // long segments were left out
+    int32_t pad;
+    unsigned long long n_long, long_cells;
+};
+
+// The finest level for n objects, or -1 if they are too few.
+int cell_top(int64_t n);
+size_t cell_long_bytes();
+// Marks the cells of n sorted objects and fills all levels.  flags starts at
+// zero; longs: scratch of cell_long_bytes() (segments only).
+hipError_t build_cells(const double *obj, int64_t n, int seg, int top, uint32_t *cells, CellFlags *flags,
+                       uint32_t *longs, hipStream_t st);
 
 // A request as the kernels see it: one tile of one index with its own
 // radius / half-width.  `index` selects an entry of the batch's index table.
@@ -57,6 +95,9 @@ struct IndexArrays {
     double2 *rep = nullptr;      // per node: the first vertex of its first object
     uint32_t *order = nullptr;
     int64_t *meta = nullptr;     // device copy of level_off / level_cnt
+    uint32_t *cells = nullptr;   // occupancy cells, or NULL
+    int32_t cell_top = -1;
+    int32_t cell_gaps = 0;
     int64_t n = 0;
     int32_t seg = 0;
     int32_t levels = 0;
@@ -88,9 +129,10 @@ BuildResult build_polygons(const double *edges, int64_t n, const int64_t *first,
 void free_poly_arrays(PolyArrays *p);
 
 // Builds the index on `stream` and synchronises.  `objects` is a device
-// pointer; validation of coordinates happens on the device.
+// pointer; validation of coordinates happens on the device.  with_cells:
+// mark the occupancy cells too (for distance masks).
 BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStream_t stream,
-                        IndexArrays *out);
+                        IndexArrays *out, bool with_cells);
 void free_index_arrays(IndexArrays *a);
 
 struct LaunchShape {

@@ -611,7 +611,7 @@ struct RegionLds {
     uint32_t *crng;  // ilo | ihi << 6 | jlo << 12 | jhi << 18 (region pixels)
     uint32_t *cpre;  // exclusive prefix sums of work cells per queued object
     uint32_t *mask;  // RS rows x RS/32 words (x4 for anti-aliased output: sub-sample m at m * RS * RS/32)
-    int *ctl;        // [0] stack size, [1] queued objects
+    int *ctl;        // [0] stack size, [1] queued objects, [2] settled from cells
     uint32_t *scan;  // 16 words
 };
 
@@ -674,6 +674,94 @@ __device__ inline int region_cells(uint32_t rg) {
     return (jhi - jlo + 1) * ((ihi >> 3) - (ilo >> 3) + 1);
 }
 
+// A radius is looked at in the finest cells that give it at most kCellRho
+// cells and that the index has; below kCellMin they decide too little.
+constexpr double kCellRho = 15.0;
+constexpr double kCellMin = 1.5;
+constexpr float kCellMargin = 1e-3f;  // cells: far above the cells' own 1e-6 and FP32 rounding here
+
+// The level whose occupancy cells settle pixels of zoom z at radius r, as a
+// shift k >= 0 from z (cells are 2^-k px), or -1.
+__device__ inline int cell_shift(const DevIndex &ix, int z, double r) {
+    if (ix.cell_top < z) return -1;
+    const int k = min(ix.cell_top - z, ilogb(kCellRho / r));
+    return k >= 0 && ldexp(r, k) >= kCellMin ? k : -1;
+}
+
+// Settles the pixels of a region from the occupancy cells 2^-k px wide: lit
+// where an occupied cell lies wholly within r of the centre, unlit where no
+// occupied cell comes within r.  The window of cells around a pixel -- at most
+// 32 columns by 33 rows -- is the same for all pixels up to its place, so lane
+// t of each wave holds the columns of row t that count, and a pixel ANDs them
+// with its window: two 16-byte loads per four rows, neighbouring pixels
+// reading the same lines.  `mask` gets the settled pixels; the unlit ones of
+// its row j go to the words at rows + 32 j.
+template <int RS>
+__device__ __forceinline__ void settle_from_cells(const DevIndex &ix, const DevReq &rq, int k, int i0, int j0,
+                                                  uint32_t *mask, uint8_t *rows) {
+    constexpr int W = RS / 32;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int level = rq.z + k;
+    const float rho = (float)ldexp(rq.r, k);
+    const float f = k ? 0.0f : 0.5f;  // a centre lies on a cell corner, or in a cell's middle
+    const int R = (int)ceilf(rho + kCellMargin);
+    const int groups = (2 * R + (k ? 0 : 1) + 3) >> 2;
+    // columns of window row `lane`, relative to the centre: bit b is the cell
+    // from b - 16 - f to b - 15 - f
+    uint32_t inner = 0, outer = 0;
+    {
+        const float y0 = (float)(lane - R) - f, y1 = y0 + 1.0f;
+        const float dn = fmaxf(fmaxf(y0, -y1), 0.0f), df = fmaxf(fabsf(y0), fabsf(y1));
+        const float ro = rho + kCellMargin, ri = rho - kCellMargin;
+        auto bits = [](int a, int b) -> uint32_t {
+            a = max(a, 0);
+            b = min(b, 31);
+            return a > b ? 0u : (0xffffffffu >> (31 - b)) & (0xffffffffu << a);
+        };
+        if (dn <= ro) {
+            const float w = sqrtf(ro * ro - dn * dn);
+            outer = bits((int)ceilf(15.0f + f - w), (int)floorf(16.0f + f + w));
+        }
+        if (df <= ri) {
+            const float w = sqrtf(ri * ri - df * df);
+            inner = bits((int)ceilf(16.0f + f - w), (int)floorf(15.0f + f + w));
+        }
+        if (ix.cell_gaps) outer = 0xffffffffu;
+    }
+    const int64_t stride = cell_stride(level);
+    const uint32_t *cells = ix.cells + cell_level_words(level) + cell_origin(level);
+    const int cx0 = (rq.x << (8 + k)) - 16, cy0 = (rq.y << (8 + k)) - R;
+    const int half = (1 << k) >> 1;
+    const int col = i0 + lane % RS;
+    const int xb = cx0 + (col << k) + half;
+    const uint32_t sh = (uint32_t)xb & 31u;
+    const uint32_t *at = cells + (int64_t)(xb >> 5) * stride + cy0 + half;
+    for (int row = wv * (64 / RS) + lane / RS; row < RS; row += nw * (64 / RS)) {
+        const uint32_t *p = at + ((j0 + row) << k);
+        uint32_t in = 0, near = 0;
+        for (int g = 0; g < groups; ++g) {
+            const u32x4 a = *reinterpret_cast<const u32x4 *>(p + 4 * g);
+            const u32x4 b = *reinterpret_cast<const u32x4 *>(p + 4 * g + stride);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t w = __builtin_amdgcn_alignbit(b[q], a[q], sh);
+                in |= w & (uint32_t)__builtin_amdgcn_readlane((int)inner, 4 * g + q);
+                near |= w & (uint32_t)__builtin_amdgcn_readlane((int)outer, 4 * g + q);
+            }
+        }
+        if (ix.cell_gaps) near = 1;
+        const uint64_t lit = __ballot(in != 0), unlit = __ballot(near == 0);
+        // the wave's 64 pixels are 64 / RS rows of W words
+        if (lane < 2) {
+            const int r2 = W == 1 ? row + lane : row, wd = W == 1 ? 0 : lane;
+            const uint32_t l = (uint32_t)(lit >> (32 * lane)), d = (uint32_t)(unlit >> (32 * lane));
+            mask[r2 * W + wd] = l | d;
+            *reinterpret_cast<uint32_t *>(rows + r2 * 32 + 4 * wd) = d;
+        }
+    }
+}
+
 // AA = 0: one bit per pixel, [D(centre) <= r].  AA = 1: Algorithm 1's value
 // 0-4, the number of the pixel's four sub-samples (centre +- 1/4 px in x and
 // y) within r, each against its own nearest object; the region keeps one
@@ -728,7 +816,27 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
         return;
     }
 
-    for (int k = tid; k < NM * MW; k += nthr) mask[k] = 0;
+    // ctl[2]: whether the output rows hold the pixels known to be unlit, until
+    // the mask is written over them
+    bool settled = false;
+    if (const int cell_k = AA ? -1 : cell_shift(ix, rq.z, r); cell_k >= 0) {
+        uint8_t *const rows = tm + ry * RS * 32 + rx * (RS / 8);
+        settled = true;
+        settle_from_cells<RS>(ix, rq, cell_k, (int)i0, (int)j0, mask, rows);
+        __syncthreads();
+        bool full = true;
+        for (int k = tid; k < MW; k += nthr) full &= mask[k] == 0xffffffffu;
+        if (__syncthreads_and(full)) {
+            for (int k = tid; k < MW; k += nthr) {
+                uint32_t *const o = reinterpret_cast<uint32_t *>(rows + (k / W) * 32 + 4 * (k % W));
+                *o = ~*o;
+            }
+            __syncthreads();
+            return;
+        }
+    } else {
+        for (int k = tid; k < NM * MW; k += nthr) mask[k] = 0;
+    }
     // a range is done once every pixel in it is set in every mask
     auto range_done = [&](int ilo, int ihi, int jlo, int jhi) -> bool {
         bool d = range_lit<W>(mask, ilo, ihi, jlo, jhi);
@@ -739,6 +847,7 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
     if (tid == 0) {
         ctl[0] = 0;
         ctl[1] = 0;
+        ctl[2] = settled;
     }
     __syncthreads();
     // accepts keep a margin so that they never claim a sample whose distance
@@ -880,7 +989,7 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
     // that the second, full walk finds most ranges lit and reads few objects.
     // A frontier made of leaves, or of nodes whose leaves cannot be small,
     // takes the full walk only.
-    bool accept_pass = racc > 0.0 && flevel > 0 && promising;
+    bool accept_pass = racc > 0.0 && flevel > 0 && promising && !settled;
     bool done = false;
     for (;;) {
         const int sp = ctl[0];
@@ -1180,9 +1289,10 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
             *reinterpret_cast<uint32_t *>(tm + (ry * RS + row) * 256 + rx * RS + col) = v;
         }
     } else {
+        const bool cut = ctl[2];
         for (int k = tid; k < RS * W; k += nthr) {
-            const int row = k / W, wd = k % W;
-            *reinterpret_cast<uint32_t *>(tm + (ry * RS + row) * 32 + rx * (RS / 8) + 4 * wd) = mask[k];
+            uint32_t *const o = reinterpret_cast<uint32_t *>(tm + (ry * RS + k / W) * 32 + rx * (RS / 8) + 4 * (k % W));
+            *o = cut ? mask[k] & ~*o : mask[k];
         }
     }
     __syncthreads();

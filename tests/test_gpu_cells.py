@@ -1,0 +1,71 @@
+"""Pixels settled from the occupancy cells, against the oracle: every distance
+of cell size and radius at which they are used, the world's edges, segments
+over many cells, and the sets for which they are not used."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_common import build, log, render
+from helpers import parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available(), "needs a GPU"
+    return t
+
+
+@pytest.fixture(scope="module")
+def hv():
+    from paper_2005_12489_amd import hv as m
+    return m
+
+
+N = 131_072  # cells down to zoom 3
+
+
+def dataset(name):
+    """(objects in normalised coordinates, kind)."""
+    rng = np.random.default_rng(len(name))
+    p = np.concatenate([rng.uniform(0, 1, (N // 4, 2)), 0.3 + 0.02 * rng.normal(size=(N - N // 4, 2))])
+    p = np.clip(p, 0.0, 1.0)
+    if name == "points":
+        return p, 0
+    if name == "edges of the world":
+        p[::3, 0] = rng.choice([0.0, 1.0], len(p[::3]))
+        p[1::3, 1] = rng.choice([0.0, 1.0], len(p[1::3]))
+        return p, 0
+    if name == "outside":  # one object beyond the world: the cells are not used
+        p[7] = (1.002, 0.5)
+        return p, 0
+    ang = rng.uniform(0, 2 * np.pi, N)
+    size = 10.0 ** rng.uniform(-5, -2.5, N)
+    if name == "long segments":
+        size[:40] = 0.7
+    if name == "too many long segments":  # the cells then settle no pixel as unlit
+        size[: N // 8] = 0.2
+    q = np.clip(p + size[:, None] * np.stack([np.cos(ang), np.sin(ang)], 1), 0.0, 1.0)
+    return np.concatenate([p, q], 1), 1
+
+
+@pytest.mark.parametrize("name", ["points", "edges of the world", "outside", "segments", "long segments",
+                                  "too many long segments"])
+def test_settled(hv, torch, name):
+    obj, kind = dataset(name)
+    ref = oracle.OracleIndex(obj, kind, merc01=True)
+    log(f"cells {name}")
+    h = build(hv, torch, obj, kind | hv.HV_INPUT_MERC01)
+    # a shallow frontier keeps the tiles in region mode, whatever they hold
+    shapes = [dict(region=rs, waves_per_wg=w, objs_per_lane=2, cand_cap=128 * w, cull_nodes=1)
+              for rs, w in ((32, 1), (32, 4), (64, 2))]
+    tiles = np.array([[0, 0, 0], [1, 0, 0], [1, 1, 1], [2, 1, 1], [2, 3, 0], [3, 2, 2], [3, 7, 7], [4, 4, 4]])
+    for r in (0.1, 0.19, 0.5, 0.75, 1.5, 2.0, 7.5, 14.9, 15.0, 15.1):
+        tri = ref.render(tiles, r)["tri"]
+        for L in [None] + shapes:
+            log(f"  r={r} launch={L}")
+            mism, amb, lit = parity(render(hv, torch, h, tiles, r, L), tri)
+            assert mism == 0, f"r={r} {L}: {mism} mismatches of {lit} lit"
+    hv.hv_free(h)
