@@ -21,15 +21,21 @@
 namespace hv {
 namespace {
 
-constexpr int kRT = 256;            // radix-sort threads per block
-constexpr int kRIPT = 16;           // keys per thread
-constexpr int kRTile = kRT * kRIPT; // keys per block
+constexpr int kST = 512;            // radix-sort threads per block
+constexpr int kSKeys = 16;          // keys per thread
+constexpr int kSTile = kST * kSKeys;
+constexpr int kRT = 256;            // scan threads per block
+constexpr int kRIPT = 16;           // counts per thread
+constexpr int kRTile = kRT * kRIPT;
 constexpr double kMaxLat = 85.0511287798066;
 constexpr double kPi = 3.14159265358979323846;
 
 // ------------------------------------------------------------ projection
 // lon/lat (deg) -> normalised Web-Mercator X (east), Y (south, 0 = north).
+// Contraction is off so that every kernel that projects an object gets the same
+// bits: the sort key and the stored coordinates are computed apart.
 __device__ inline void mercator(double lon, double lat, double &X, double &Y) {
+#pragma clang fp contract(off)
     lat = fmin(fmax(lat, -kMaxLat), kMaxLat);
     const double phi = lat * (kPi / 180.0);
     X = (lon + 180.0) / 360.0;
@@ -59,76 +65,94 @@ __device__ inline uint32_t quantise(double c, int bits) {
     return (uint32_t)q;
 }
 
+// An object's projected coordinates.
 template <int W>
-__global__ __launch_bounds__(256) void k_project_key(const double *__restrict__ in, int64_t n, int merc,
-                                                     double *__restrict__ proj, uint64_t *__restrict__ keys,
-                                                     uint32_t *__restrict__ ids, int bits, int *err) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+__device__ inline void project(const double *__restrict__ in, int64_t i, int merc, double *p) {
     double v[W];
-#pragma unroll
-    for (int c = 0; c < W; ++c) v[c] = in[i * W + c];
-    bool bad = false;
-#pragma unroll
-    for (int c = 0; c < W; ++c) bad |= !isfinite(v[c]);
-    if (!merc) {
-#pragma unroll
-        for (int c = 0; c < W; c += 2) bad |= fabs(v[c]) > 180.0 || fabs(v[c + 1]) > 90.0;
+    if constexpr (W == 2) {
+        const double2 g = reinterpret_cast<const double2 *>(in)[i];
+        v[0] = g.x, v[1] = g.y;
+    } else {
+        const double4 g = reinterpret_cast<const double4 *>(in)[i];
+        v[0] = g.x, v[1] = g.y, v[2] = g.z, v[3] = g.w;
     }
-    if (bad) atomicOr(err, 1);
-    double p[W];
 #pragma unroll
     for (int c = 0; c < W; c += 2) {
         if (merc) { p[c] = v[c]; p[c + 1] = v[c + 1]; }
         else mercator(v[c], v[c + 1], p[c], p[c + 1]);
     }
+}
+
+// The Hilbert key of every object's box centre: its low 8 bits (the first digit
+// sorted by) and the rest, at most 32 bits.
+template <int W>
+__global__ __launch_bounds__(256) void k_project_key(const double *__restrict__ in, int64_t n, int merc,
+                                                     uint8_t *__restrict__ low, uint32_t *__restrict__ high, int bits,
+                                                     int *err) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    bool bad = false;
 #pragma unroll
-    for (int c = 0; c < W; ++c) proj[i * W + c] = p[c];
+    for (int c = 0; c < W; c += 2) {
+        const double x = in[i * W + c], y = in[i * W + c + 1];
+        bad |= !isfinite(x) || !isfinite(y) || (!merc && (fabs(x) > 180.0 || fabs(y) > 90.0));
+    }
+    if (bad) atomicOr(err, 1);
+    double p[W];
+    project<W>(in, i, merc, p);
     double cx = p[0], cy = p[1];
     if constexpr (W == 4) {
         cx = 0.5 * (fmin(p[0], p[2]) + fmax(p[0], p[2]));
         cy = 0.5 * (fmin(p[1], p[3]) + fmax(p[1], p[3]));
     }
-    keys[i] = hilbert_d(quantise(cx, bits), quantise(cy, bits), bits);
-    ids[i] = (uint32_t)i;
+    const uint64_t key = hilbert_d(quantise(cx, bits), quantise(cy, bits), bits);
+    low[i] = (uint8_t)key;
+    high[i] = (uint32_t)(key >> 8);
 }
 
-// Projects polygon edges (4 doubles each) in their given order; flags
-// coordinates that are not finite or outside [-180, 180] x [-90, 90].
-__global__ __launch_bounds__(256) void k_project_edges(const double *__restrict__ in, int64_t n, int merc,
-                                                       double *__restrict__ out, int *err) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    double v[4];
+// Least and greatest of 16 neighbouring lanes' boxes, in every lane.
+__device__ inline double4 box16(double4 b) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) v[c] = in[i * 4 + c];
-    bool bad = false;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) bad |= !isfinite(v[c]);
-    if (!merc) bad |= fabs(v[0]) > 180.0 || fabs(v[1]) > 90.0 || fabs(v[2]) > 180.0 || fabs(v[3]) > 90.0;
-    if (bad) atomicOr(err, 1);
-    double p[4] = {v[0], v[1], v[2], v[3]};
-    if (!merc) {
-        mercator(v[0], v[1], p[0], p[1]);
-        mercator(v[2], v[3], p[2], p[3]);
+    for (int o = 1; o < 16; o <<= 1) {
+        b.x = fmin(b.x, __shfl_xor(b.x, o, 64));
+        b.y = fmin(b.y, __shfl_xor(b.y, o, 64));
+        b.z = fmax(b.z, __shfl_xor(b.z, o, 64));
+        b.w = fmax(b.w, __shfl_xor(b.w, o, 64));
     }
-    reinterpret_cast<double4 *>(out)[i] = make_double4(p[0], p[1], p[2], p[3]);
+    return b;
 }
 
-// Bounding box of each polygon's edges, written as the diagonal segment
-// (min X, min Y) - (max X, max Y), whose own box is the polygon's box.
+__device__ inline double4 edge_box(const double *p) {
+    return make_double4(fmin(p[0], p[2]), fmin(p[1], p[3]), fmax(p[0], p[2]), fmax(p[1], p[3]));
+}
+
+__device__ inline double4 box_union(const double4 &a, const double4 &b) {
+    return make_double4(fmin(a.x, b.x), fmin(a.y, b.y), fmax(a.z, b.z), fmax(a.w, b.w));
+}
+
+// Bounding box of each polygon's projected edges, written as the diagonal
+// segment (min X, min Y) - (max X, max Y), whose own box is the polygon's box;
+// 16 lanes to a polygon.  Flags coordinates that are not finite or outside
+// [-180, 180] x [-90, 90].
 __global__ __launch_bounds__(256) void k_polygon_boxes(const double *__restrict__ edges,
-                                                       const int64_t *__restrict__ first, int64_t npoly,
-                                                       double *__restrict__ diag) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= npoly) return;
-    double x0 = INFINITY, y0 = INFINITY, x1 = -INFINITY, y1 = -INFINITY;
-    for (int64_t e = first[p]; e < first[p + 1]; ++e) {
-        const double4 g = reinterpret_cast<const double4 *>(edges)[e];
-        x0 = fmin(x0, fmin(g.x, g.z)); x1 = fmax(x1, fmax(g.x, g.z));
-        y0 = fmin(y0, fmin(g.y, g.w)); y1 = fmax(y1, fmax(g.y, g.w));
-    }
-    reinterpret_cast<double4 *>(diag)[p] = make_double4(x0, y0, x1, y1);
+                                                       const int64_t *__restrict__ first, int64_t npoly, int merc,
+                                                       double *__restrict__ diag, int *err) {
+    const int64_t p = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
+    const int c = threadIdx.x & 15;
+    double4 box = make_double4(INFINITY, INFINITY, -INFINITY, -INFINITY);
+    bool bad = false;
+    if (p < npoly)
+        for (int64_t e = first[p] + c; e < first[p + 1]; e += 16) {
+            const double4 v = reinterpret_cast<const double4 *>(edges)[e];
+            bad |= !isfinite(v.x) || !isfinite(v.y) || !isfinite(v.z) || !isfinite(v.w);
+            if (!merc) bad |= fabs(v.x) > 180.0 || fabs(v.y) > 90.0 || fabs(v.z) > 180.0 || fabs(v.w) > 90.0;
+            double q[4];
+            project<4>(edges, e, merc, q);
+            box = box_union(box, edge_box(q));
+        }
+    if (bad) atomicOr(err, 1);
+    box = box16(box);
+    if (p < npoly && c == 0) reinterpret_cast<double4 *>(diag)[p] = box;
 }
 
 // Conservative float box of each run of kEdgeChunk consecutive edges of the
@@ -145,18 +169,25 @@ __device__ inline float float_up(double d) {
     return f;
 }
 
+// Eight lanes to a run.
 __global__ __launch_bounds__(256) void k_edge_chunks(const double *__restrict__ edges, int64_t n,
                                                      float4 *__restrict__ chunks) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= (n + kEdgeChunk - 1) / kEdgeChunk) return;
-    double x0 = INFINITY, y0 = INFINITY, x1 = -INFINITY, y1 = -INFINITY;
-    const int64_t e1 = min(n, (c + 1) * kEdgeChunk);
-    for (int64_t e = c * kEdgeChunk; e < e1; ++e) {
+    static_assert(kEdgeChunk == 8, "a chunk is 8 neighbouring lanes");
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    double4 b = make_double4(INFINITY, INFINITY, -INFINITY, -INFINITY);
+    if (e < n) {
         const double4 g = reinterpret_cast<const double4 *>(edges)[e];
-        x0 = fmin(x0, fmin(g.x, g.z)); x1 = fmax(x1, fmax(g.x, g.z));
-        y0 = fmin(y0, fmin(g.y, g.w)); y1 = fmax(y1, fmax(g.y, g.w));
+        b = make_double4(fmin(g.x, g.z), fmin(g.y, g.w), fmax(g.x, g.z), fmax(g.y, g.w));
     }
-    chunks[c] = make_float4(float_down(x0), float_down(y0), float_up(x1), float_up(y1));
+#pragma unroll
+    for (int o = 1; o < 8; o <<= 1) {
+        b.x = fmin(b.x, __shfl_xor(b.x, o, 64));
+        b.y = fmin(b.y, __shfl_xor(b.y, o, 64));
+        b.z = fmax(b.z, __shfl_xor(b.z, o, 64));
+        b.w = fmax(b.w, __shfl_xor(b.w, o, 64));
+    }
+    if (e < n && e % kEdgeChunk == 0)
+        chunks[e / kEdgeChunk] = make_float4(float_down(b.x), float_down(b.y), float_up(b.z), float_up(b.w));
 }
 
 // Union of each run of kChunkSuper chunk boxes (already outward-rounded):
@@ -174,20 +205,24 @@ __global__ __launch_bounds__(256) void k_super_chunks(const float4 *__restrict__
     supers[s] = b;
 }
 
-// Copies each polygon's edges from input order to the tree's order: wave w
+// Projects each polygon's edges from input order into the tree's order: wave w
 // of the grid moves sorted polygon w, whose edges start at src_first[order[w]]
 // in `src` and at dst_first[w] in `dst`.
 __global__ __launch_bounds__(256) void k_permute_polygons(const double4 *__restrict__ src,
                                                           const int64_t *__restrict__ src_first,
                                                           const uint32_t *__restrict__ order,
-                                                          const int64_t *__restrict__ dst_first, int64_t npoly,
+                                                          const int64_t *__restrict__ dst_first, int64_t npoly, int merc,
                                                           double4 *__restrict__ dst) {
     const int64_t k = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int lane = threadIdx.x & 63;
     if (k >= npoly) return;
     const int64_t p = order[k];
     const int64_t s0 = src_first[p], cnt = src_first[p + 1] - s0, d0 = dst_first[k];
-    for (int64_t e = lane; e < cnt; e += 64) dst[d0 + e] = src[s0 + e];
+    for (int64_t e = lane; e < cnt; e += 64) {
+        double q[4];
+        project<4>(reinterpret_cast<const double *>(src), s0 + e, merc, q);
+        dst[d0 + e] = make_double4(q[0], q[1], q[2], q[3]);
+    }
 }
 
 // ------------------------------------------------------------ scans
@@ -273,45 +308,62 @@ __global__ __launch_bounds__(256) void k_scan_down(uint32_t *__restrict__ a, int
 
 // ------------------------------------------------------------ radix sort
 // Digit histogram of one block's tile; counts are digit-major so that one
-// exclusive scan gives every (digit, block) its output offset.
-__global__ __launch_bounds__(256) void k_radix_hist(const uint64_t *__restrict__ keys, int64_t n, int shift,
-                                                    uint32_t *__restrict__ counts, int64_t nb) {
+// exclusive scan gives every (digit, block) its output offset.  FIRST: the
+// digit is the key's low byte, kept apart.
+template <bool FIRST>
+__global__ __launch_bounds__(kST) void k_radix_hist(const uint8_t *__restrict__ low, const uint32_t *__restrict__ keys,
+                                                    int64_t n, int shift, uint32_t *__restrict__ counts, int64_t nb) {
     __shared__ uint32_t h[256];
-    h[threadIdx.x] = 0;
+    if (threadIdx.x < 256) h[threadIdx.x] = 0;
     __syncthreads();
-    const int64_t t0 = (int64_t)blockIdx.x * kRTile;
+    const int64_t t0 = (int64_t)blockIdx.x * kSTile;
 #pragma unroll
-    for (int k = 0; k < kRIPT; ++k) {
-        const int64_t idx = t0 + k * kRT + threadIdx.x;
-        if (idx < n) atomicAdd(&h[(uint32_t)(keys[idx] >> shift) & 255u], 1u);
+    for (int k = 0; k < kSKeys; ++k) {
+        const int64_t idx = t0 + k * kST + threadIdx.x;
+        if (idx < n) atomicAdd(&h[FIRST ? low[idx] : (keys[idx] >> shift) & 255u], 1u);
     }
     __syncthreads();
-    counts[(int64_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
+    if (threadIdx.x < 256) counts[(int64_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
 }
 
-// Stable scatter.  Keys of a tile are visited in input order (k, wave,
-// lane); within a wave, lanes holding the same digit find each other with
-// eight ballots, and per-digit running bases carry the order across waves
-// and across k.
-__global__ __launch_bounds__(256) void k_radix_scatter(const uint64_t *__restrict__ kin,
-                                                       const uint32_t *__restrict__ vin,
-                                                       uint64_t *__restrict__ kout, uint32_t *__restrict__ vout,
-                                                       int64_t n, int shift, const uint32_t *__restrict__ offs,
-                                                       int64_t nb) {
-    __shared__ uint32_t base[256];
-    __shared__ uint32_t wc[4][256];
-    const int tid = threadIdx.x, w = tid >> 6;
-    base[tid] = offs[(int64_t)tid * nb + blockIdx.x];
-    const int64_t t0 = (int64_t)blockIdx.x * kRTile;
-    for (int k = 0; k < kRIPT; ++k) {
+// Stable scatter of (key, object) pairs.  A wave ranks kSKeys * 64 consecutive
+// keys in input order: lanes holding the same digit find each other with eight
+// ballots, and per-digit counts carry the order from one 64 to the next.  The
+// tile is then brought into digit order in LDS, so that a digit's keys -- 32
+// on average -- go out as one run of whole lines.  (Written lane by lane, each
+// to its own line, a pass over 1e9 pairs took 26 ms.)  FIRST: the digit is the
+// key's low byte and the objects are in input order.
+template <bool FIRST>
+__global__ __launch_bounds__(kST) void k_radix_scatter(const uint8_t *__restrict__ low, const uint32_t *__restrict__ kin,
+                                                       const uint32_t *__restrict__ vin, uint32_t *__restrict__ kout,
+                                                       uint32_t *__restrict__ vout, int64_t n, int shift,
+                                                       const uint32_t *__restrict__ offs, int64_t nb) {
+    constexpr int kWaves = kST / 64;
+    __shared__ uint32_t sorted[kSTile];
+    __shared__ uint8_t digit_of[kSTile];
+    __shared__ uint16_t wc[kWaves][256];  // keys of a digit seen by a wave; then where its first goes in the tile
+    __shared__ uint32_t goff[256];        // where the tile's first key of a digit goes, less its place in the tile
+    __shared__ uint32_t ws[16];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    for (int k = tid; k < kWaves * 256; k += kST) wc[0][k] = 0;
+    __syncthreads();
+    const int64_t w0 = (int64_t)blockIdx.x * kSTile + (int64_t)w * (64 * kSKeys);
+    const int count = (int)min((int64_t)kSTile, n - (int64_t)blockIdx.x * kSTile);
+    uint32_t key[kSKeys], val[kSKeys];
+    uint16_t rank[kSKeys];
+    uint8_t dig[kSKeys];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) wc[q][tid] = 0;
-        __syncthreads();
-        const int64_t idx = t0 + k * kRT + tid;
+    for (int k = 0; k < kSKeys; ++k) {
+        const int64_t idx = w0 + k * 64 + lane;
         const bool valid = idx < n;
-        const uint64_t key = valid ? kin[idx] : 0ull;
-        const uint32_t val = valid ? vin[idx] : 0u;
-        const uint32_t d = (uint32_t)(key >> shift) & 255u;
+        key[k] = valid ? kin[idx] : 0u;
+        val[k] = FIRST ? (uint32_t)idx : valid ? vin[idx] : 0u;
+        dig[k] = FIRST ? (valid ? low[idx] : 0) : (uint8_t)(key[k] >> shift);
+    }
+#pragma unroll
+    for (int k = 0; k < kSKeys; ++k) {
+        const bool valid = w0 + k * 64 + lane < n;
+        const uint32_t d = dig[k];
         uint64_t m = __ballot(valid);
 #pragma unroll
         for (int b = 0; b < 8; ++b) {
@@ -319,82 +371,96 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const uint64_t *__restric
             const uint64_t bb = __ballot(bit);
             m &= bit ? bb : ~bb;
         }
-        const uint32_t rank = lanes_below(m);
-        if (valid && rank == 0) wc[w][d] = (uint32_t)__popcll(m);
-        __syncthreads();
-        {
-            uint32_t run = base[tid];
+        const uint32_t below = lanes_below(m), seen = wc[w][d];
+        rank[k] = (uint16_t)(seen + below);
+        __builtin_amdgcn_wave_barrier();
+        if (valid && below == 0) wc[w][d] = (uint16_t)(seen + (uint32_t)__popcll(m));
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    {
+        uint32_t total = 0, sum = 0;
+        if (tid < 256)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < kWaves; ++q) total += wc[q][tid];
+        uint32_t all;
+        sum = block_excl_scan(tid < 256 ? total : 0u, &all, ws);
+        if (tid < 256) {
+            goff[tid] = offs[(int64_t)tid * nb + blockIdx.x] - sum;
+#pragma unroll
+            for (int q = 0; q < kWaves; ++q) {
                 const uint32_t c = wc[q][tid];
-                wc[q][tid] = run;
-                run += c;
+                wc[q][tid] = (uint16_t)sum;
+                sum += c;
             }
-            base[tid] = run;
         }
-        __syncthreads();
-        if (valid) {
-            const uint32_t pos = wc[w][d] + rank;
-            kout[pos] = key;
-            vout[pos] = val;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSKeys; ++k)
+        if (w0 + k * 64 + lane < n) {
+            const uint32_t at = wc[w][dig[k]] + rank[k];
+            rank[k] = (uint16_t)at;
+            sorted[at] = key[k];
+            digit_of[at] = dig[k];
         }
-        __syncthreads();
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSKeys; ++k) {
+        const int i = k * kST + tid;
+        if (i < count) kout[goff[digit_of[i]] + i] = sorted[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSKeys; ++k)
+        if (w0 + k * 64 + lane < n) sorted[rank[k]] = val[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSKeys; ++k) {
+        const int i = k * kST + tid;
+        if (i < count) vout[goff[digit_of[i]] + i] = sorted[i];
     }
 }
 
 // ------------------------------------------------------------ gather + pack
+// Projects the objects once more, now in sorted order, and packs the leaves:
+// each leaf's box and representative, the first vertex of its first object.
 template <int W>
-__global__ __launch_bounds__(256) void k_gather(const double *__restrict__ proj, const uint32_t *__restrict__ order,
-                                                int64_t n, double *__restrict__ out) {
+__global__ __launch_bounds__(256) void k_gather_leaves(const double *__restrict__ in, const uint32_t *__restrict__ order,
+                                                       int64_t n, int merc, double *__restrict__ obj,
+                                                       double4 *__restrict__ leaf, double2 *__restrict__ rep) {
+    static_assert(kLeaf == 16, "a leaf is 16 neighbouring lanes");
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int64_t s = order[i];
-#pragma unroll
-    for (int c = 0; c < W; ++c) out[i * W + c] = proj[s * W + c];
-}
-
-template <int W>
-__global__ __launch_bounds__(256) void k_leaf_boxes(const double *__restrict__ obj, int64_t n,
-                                                    double4 *__restrict__ leaf, int64_t nleaf) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nleaf) return;
-    const int64_t lo = i * kLeaf, hi = min<int64_t>(lo + kLeaf, n);
-    double x0 = INFINITY, y0 = INFINITY, x1 = -INFINITY, y1 = -INFINITY;
-    for (int64_t k = lo; k < hi; ++k) {
-#pragma unroll
-        for (int c = 0; c < W; c += 2) {
-            const double x = obj[k * W + c], y = obj[k * W + c + 1];
-            x0 = fmin(x0, x); x1 = fmax(x1, x);
-            y0 = fmin(y0, y); y1 = fmax(y1, y);
+    double4 b = make_double4(INFINITY, INFINITY, -INFINITY, -INFINITY);
+    if (i < n) {
+        double p[W];
+        project<W>(in, order[i], merc, p);
+        if constexpr (W == 2) {
+            reinterpret_cast<double2 *>(obj)[i] = make_double2(p[0], p[1]);
+            b = make_double4(p[0], p[1], p[0], p[1]);
+        } else {
+            reinterpret_cast<double4 *>(obj)[i] = make_double4(p[0], p[1], p[2], p[3]);
+            b = make_double4(fmin(p[0], p[2]), fmin(p[1], p[3]), fmax(p[0], p[2]), fmax(p[1], p[3]));
         }
+        if (i % kLeaf == 0) rep[i / kLeaf] = make_double2(p[0], p[1]);
     }
-    leaf[i] = make_double4(x0, y0, x1, y1);
+    b = box16(b);
+    if (i < n && i % kLeaf == 0) leaf[i / kLeaf] = b;
 }
 
-__global__ __launch_bounds__(256) void k_level_boxes(const double4 *__restrict__ child, int64_t nchild,
-                                                     double4 *__restrict__ parent, int64_t nparent) {
+// A level's boxes and representatives from its children's.  Node i of level l
+// owns the sorted objects [i * 16^(l + 1), (i + 1) * 16^(l + 1)), so its
+// representative is its first child's.
+__global__ __launch_bounds__(256) void k_level(const double4 *__restrict__ child, const double2 *__restrict__ child_rep,
+                                               int64_t nchild, double4 *__restrict__ parent,
+                                               double2 *__restrict__ parent_rep) {
+    static_assert(kFan == 16, "a node is 16 neighbouring lanes");
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nparent) return;
-    const int64_t lo = i * kFan, hi = min<int64_t>(lo + kFan, nchild);
-    double x0 = INFINITY, y0 = INFINITY, x1 = -INFINITY, y1 = -INFINITY;
-    for (int64_t k = lo; k < hi; ++k) {
-        const double4 b = child[k];
-        x0 = fmin(x0, b.x); y0 = fmin(y0, b.y);
-        x1 = fmax(x1, b.z); y1 = fmax(y1, b.w);
+    const double4 b = box16(i < nchild ? child[i] : make_double4(INFINITY, INFINITY, -INFINITY, -INFINITY));
+    if (i < nchild && i % kFan == 0) {
+        parent[i / kFan] = b;
+        parent_rep[i / kFan] = child_rep[i];
     }
-    parent[i] = make_double4(x0, y0, x1, y1);
-}
-
-// Node i of level l owns the sorted objects [i * 16^(l + 1), (i + 1) *
-// 16^(l + 1)); its representative is the first vertex of the first of them,
-// a point of an object inside the node's box.
-template <int W>
-__global__ __launch_bounds__(256) void k_node_reps(const double *__restrict__ obj, int shift,
-                                                   double2 *__restrict__ rep, int64_t count) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    const int64_t o = i << shift;
-    rep[i] = make_double2(obj[o * W], obj[o * W + 1]);
 }
 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -409,18 +475,25 @@ int key_bits_for(int64_t n) {
     return std::min(32, std::max(8, kb));
 }
 
-struct Scratch {
-    void *p[8] = {};
-    int k = 0;
-    ~Scratch() {
-        for (int i = 0; i < k; ++i)
-            if (p[i]) (void)hipFree(p[i]);
+// Offsets of the arrays of one block.
+struct Carve {
+    size_t bytes = 0;
+    size_t take(size_t b) {
+        const size_t at = bytes;
+        bytes += (b + 255) & ~size_t(255);
+        return at;
     }
-    template <class T>
-    hipError_t alloc(T **out, size_t bytes) {
-        hipError_t e = hipMalloc((void **)out, bytes ? bytes : 1);
-        if (e == hipSuccess) p[k++] = *out;
-        return e;
+};
+
+struct Scratch {
+    unsigned char *p = nullptr;
+    size_t bytes = 0;
+    ~Scratch() {
+        if (p) device_release(p, bytes);
+    }
+    hipError_t alloc(size_t want) {
+        if (want == 0) return hipSuccess;
+        return device_acquire(reinterpret_cast<void **>(&p), want, &bytes);
     }
 };
 
@@ -433,70 +506,57 @@ BuildResult hip_fail(hipError_t e) {
 }  // namespace
 
 void free_poly_arrays(PolyArrays *p) {
-    if (p->edges) (void)hipFree(p->edges);
-    if (p->first) (void)hipFree(p->first);
-    if (p->chunks) (void)hipFree(p->chunks);
-    if (p->supers) (void)hipFree(p->supers);
-    p->supers = nullptr;
-    p->edges = nullptr;
-    p->first = nullptr;
-    p->chunks = nullptr;
+    if (p->block) device_release(p->block, p->block_bytes);
+    *p = PolyArrays{};
 }
 
 BuildResult build_polygons(const double *edges, int64_t n, const int64_t *first, int64_t npoly, int flags,
                            hipStream_t st, IndexArrays *tree, PolyArrays *poly) {
     const int merc = (flags & HV_INPUT_MERC01) != 0;
+    *tree = IndexArrays{};
+    *poly = PolyArrays{};
     poly->npoly = npoly;
     poly->n_edges = n;
-    tree->n = 0;
     tree->seg = 1;
-    tree->levels = 0;
     if (npoly == 0) return {HV_OK, ""};
-    // projected edges and offsets in input order first; once the tree has
-    // sorted the polygons, both are rewritten in the tree's order so that the
-    // polygons of one region lie close together in memory
-    double *proj = nullptr, *diag = nullptr;
-    int64_t *in_first = nullptr;
-    int *err = nullptr;
-    auto release = [&]() {
-        if (proj) (void)hipFree(proj);
-        if (in_first) (void)hipFree(in_first);
-        if (diag) (void)hipFree(diag);
-        if (err) (void)hipFree(err);
-        proj = diag = nullptr;
-        in_first = nullptr;
-        err = nullptr;
-    };
     auto bail = [&](hipError_t e) {
-        release();
         free_poly_arrays(poly);
         free_index_arrays(tree);
         return hip_fail(e);
     };
+    // The polygons' boxes, from the edges as they are; once the tree has sorted
+    // the polygons, the edges are projected into the tree's order, so that the
+    // polygons of one region lie close together in memory.
+    const int64_t nchunk = cdiv(n, kEdgeChunk), nsuper = cdiv(nchunk, kChunkSuper);
+    Carve index, work;
+    const size_t o_edges = index.take(sizeof(double) * 4 * (size_t)n);
+    const size_t o_first = index.take(sizeof(int64_t) * (size_t)(npoly + 1));
+    const size_t o_chunks = index.take(sizeof(float4) * (size_t)nchunk);
+    const size_t o_supers = index.take(sizeof(float4) * (size_t)nsuper);
+    const size_t o_in = work.take(sizeof(int64_t) * (size_t)(npoly + 1));
+    const size_t o_diag = work.take(sizeof(double) * 4 * (size_t)npoly), o_err = work.take(sizeof(int));
+    Scratch scratch;
     hipError_t e;
-    if ((e = hipMalloc((void **)&proj, sizeof(double) * 4 * (size_t)n)) != hipSuccess) return bail(e);
-    if ((e = hipMalloc((void **)&in_first, sizeof(int64_t) * (size_t)(npoly + 1))) != hipSuccess) return bail(e);
-    if ((e = hipMalloc((void **)&diag, sizeof(double) * 4 * (size_t)npoly)) != hipSuccess) return bail(e);
-    if ((e = hipMalloc((void **)&err, sizeof(int))) != hipSuccess) return bail(e);
+    if ((e = scratch.alloc(work.bytes)) != hipSuccess) return bail(e);
+    int64_t *const in_first = reinterpret_cast<int64_t *>(scratch.p + o_in);
+    double *const diag = reinterpret_cast<double *>(scratch.p + o_diag);
+    int *const err = reinterpret_cast<int *>(scratch.p + o_err);
     if ((e = hipMemcpyAsync(in_first, first, sizeof(int64_t) * (size_t)(npoly + 1), hipMemcpyHostToDevice, st)) !=
         hipSuccess)
         return bail(e);
     if ((e = hipMemsetAsync(err, 0, sizeof(int), st)) != hipSuccess) return bail(e);
-    hipLaunchKernelGGL(k_project_edges, dim3((uint32_t)cdiv(n, 256)), dim3(256), 0, st, edges, n, merc, proj, err);
-    hipLaunchKernelGGL(k_polygon_boxes, dim3((uint32_t)cdiv(npoly, 256)), dim3(256), 0, st, proj, in_first, npoly,
-                       diag);
+    hipLaunchKernelGGL(k_polygon_boxes, dim3((uint32_t)cdiv(npoly, 16)), dim3(256), 0, st, edges, in_first, npoly, merc,
+                       diag, err);
     if ((e = hipGetLastError()) != hipSuccess) return bail(e);
     int herr = 0;
     if ((e = hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess) return bail(e);
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return bail(e);
     if (herr) {
-        release();
         free_poly_arrays(poly);
         return {HV_EINVAL, "edges hold a non-finite coordinate, |lon| > 180 or |lat| > 90"};
     }
     const BuildResult r = build_index(diag, HV_SEGMENTS | HV_INPUT_MERC01, npoly, st, tree, false);
     if (r.status != HV_OK) {
-        release();
         free_poly_arrays(poly);
         return r;
     }
@@ -511,48 +571,34 @@ BuildResult build_polygons(const double *edges, int64_t n, const int64_t *first,
         const uint32_t p = order[(size_t)k];
         sorted_first[(size_t)k + 1] = sorted_first[(size_t)k] + (first[p + 1] - first[p]);
     }
-    const int64_t nchunk = cdiv(n, kEdgeChunk);
-    if ((e = hipMalloc((void **)&poly->edges, sizeof(double) * 4 * (size_t)n)) != hipSuccess) return bail(e);
-    if ((e = hipMalloc((void **)&poly->first, sizeof(int64_t) * (size_t)(npoly + 1))) != hipSuccess) return bail(e);
-    const int64_t nsuper = cdiv(nchunk, kChunkSuper);
-    if (nchunk > 0 && (e = hipMalloc((void **)&poly->chunks, sizeof(float4) * (size_t)nchunk)) != hipSuccess)
-        return bail(e);
-    if (nsuper > 0 && (e = hipMalloc((void **)&poly->supers, sizeof(float4) * (size_t)nsuper)) != hipSuccess)
-        return bail(e);
+    if ((e = device_acquire(&poly->block, index.bytes, &poly->block_bytes)) != hipSuccess) return bail(e);
+    unsigned char *const block = static_cast<unsigned char *>(poly->block);
+    poly->edges = reinterpret_cast<double *>(block + o_edges);
+    poly->first = reinterpret_cast<int64_t *>(block + o_first);
+    poly->chunks = reinterpret_cast<float4 *>(block + o_chunks);
+    poly->supers = reinterpret_cast<float4 *>(block + o_supers);
     if ((e = hipMemcpyAsync(poly->first, sorted_first.data(), sizeof(int64_t) * (size_t)(npoly + 1),
                             hipMemcpyHostToDevice, st)) != hipSuccess)
         return bail(e);
     hipLaunchKernelGGL(k_permute_polygons, dim3((uint32_t)cdiv(npoly, 4)), dim3(256), 0, st,
-                       reinterpret_cast<const double4 *>(proj), in_first, tree->order, poly->first, npoly,
+                       reinterpret_cast<const double4 *>(edges), in_first, tree->order, poly->first, npoly, merc,
                        reinterpret_cast<double4 *>(poly->edges));
     if (nchunk > 0) {
-        hipLaunchKernelGGL(k_edge_chunks, dim3((uint32_t)cdiv(nchunk, 256)), dim3(256), 0, st, poly->edges, n,
-                           poly->chunks);
+        hipLaunchKernelGGL(k_edge_chunks, dim3((uint32_t)cdiv(nchunk * kEdgeChunk, 256)), dim3(256), 0, st, poly->edges,
+                           n, poly->chunks);
         hipLaunchKernelGGL(k_super_chunks, dim3((uint32_t)cdiv(nsuper, 256)), dim3(256), 0, st, poly->chunks,
                            nchunk, poly->supers);
     }
     if ((e = hipGetLastError()) != hipSuccess) return bail(e);
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return bail(e);
-    release();
     tree->device_bytes += (int64_t)(sizeof(double) * 4 * (size_t)n + sizeof(int64_t) * (size_t)(npoly + 1) +
                                     sizeof(float4) * (size_t)(nchunk + nsuper));
     return r;
 }
 
 void free_index_arrays(IndexArrays *a) {
-    if (a->obj) (void)hipFree(a->obj);
-    if (a->nodes) (void)hipFree(a->nodes);
-    if (a->rep) (void)hipFree(a->rep);
-    if (a->order) (void)hipFree(a->order);
-    if (a->meta) (void)hipFree(a->meta);
-    if (a->cells) (void)hipFree(a->cells);
-    a->cells = nullptr;
-    a->cell_top = -1;
-    a->obj = nullptr;
-    a->nodes = nullptr;
-    a->rep = nullptr;
-    a->order = nullptr;
-    a->meta = nullptr;
+    if (a->block) device_release(a->block, a->block_bytes);
+    *a = IndexArrays{};
 }
 
 #define HV_TRY(expr)                          \
@@ -570,16 +616,10 @@ BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStr
     const int merc = (kind_flags & HV_INPUT_MERC01) != 0;
     const int seg = kind != HV_POINTS;
     const int W = seg ? 4 : 2;
+    *out = IndexArrays{};
     out->n = n;
     out->seg = seg;
-    out->levels = 0;
-    out->nodes_total = 0;
-    out->device_bytes = 0;
     if (n == 0) return {HV_OK, ""};  // empty index: no device memory at all
-    {
-        hipError_t e = hipMalloc((void **)&out->meta, sizeof(int64_t) * 2 * kMaxLevels);
-        if (e != hipSuccess) return hip_fail(e);
-    }
 
     // node-level sizes
     int levels = 0;
@@ -598,43 +638,56 @@ BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStr
     const int bits = key_bits_for(n);
     out->key_bits = bits;
     const int passes = (2 * bits + 7) / 8;
-    const int64_t nb = cdiv(n, kRTile);
+    const int64_t nb = cdiv(n, kSTile);
     const int64_t ncount = 256 * nb;
     const int64_t npart = cdiv(ncount, kRTile);
 
-    Scratch s;
-    double *proj;
-    uint64_t *k0, *k1;
-    uint32_t *v0, *v1, *counts, *part;
-    CellFlags *flags;
-    HV_TRY(s.alloc(&proj, sizeof(double) * W * n));
-    HV_TRY(s.alloc(&k0, sizeof(uint64_t) * n));
-    HV_TRY(s.alloc(&k1, sizeof(uint64_t) * n));
-    HV_TRY(s.alloc(&v1, sizeof(uint32_t) * n));
-    HV_TRY(s.alloc(&counts, sizeof(uint32_t) * ncount));
-    HV_TRY(s.alloc(&part, sizeof(uint32_t) * npart));
-    HV_TRY(s.alloc(&flags, sizeof(CellFlags)));
-    HV_TRY(hipMalloc((void **)&out->obj, sizeof(double) * W * n));
-    HV_TRY(hipMalloc((void **)&out->order, sizeof(uint32_t) * n));
-    HV_TRY(hipMalloc((void **)&out->nodes, sizeof(double4) * total));
-    HV_TRY(hipMalloc((void **)&out->rep, sizeof(double2) * total));
-    v0 = out->order;  // the sort's value buffer doubles as the stored order
-    out->device_bytes = (int64_t)(sizeof(double) * W * n + sizeof(uint32_t) * n +
-                                  (sizeof(double4) + sizeof(double2)) * total);
-    // the cells are an aid only: without memory for them the index does
-    // without
-    uint32_t *longs = nullptr;
-    if (with_cells && cell_top(n) >= 0) {
-        const int top = cell_top(n);
-        const size_t bytes = sizeof(uint32_t) * (size_t)cell_level_words(top + 1);
-        if ((!seg || s.alloc(&longs, cell_long_bytes()) == hipSuccess) &&
-            hipMalloc((void **)&out->cells, bytes) == hipSuccess) {
-            out->cell_top = top;
-            out->device_bytes += (int64_t)bytes;
-        } else {
-            (void)hipGetLastError();
-            out->cells = nullptr;
-        }
+    // All arrays of the index in one block (a free costs 29 ms per GB here,
+    // whatever the number of blocks); the cells are an aid only, and an index
+    // without memory for them does without.
+    const size_t obj_bytes = sizeof(double) * W * (size_t)n, order_bytes = sizeof(uint32_t) * (size_t)n;
+    const size_t node_bytes = sizeof(double4) * (size_t)total, rep_bytes = sizeof(double2) * (size_t)total;
+    const size_t meta_bytes = sizeof(int64_t) * 2 * kMaxLevels;
+    const int top = with_cells ? cell_top(n) : -1;
+    const size_t cell_bytes = sizeof(uint32_t) * (size_t)cell_level_words(top + 1);
+    const size_t long_bytes = top >= 0 && seg ? cell_long_bytes(n) : 0;
+    Carve index;
+    const size_t o_obj = index.take(obj_bytes), o_order = index.take(order_bytes), o_nodes = index.take(node_bytes);
+    const size_t o_rep = index.take(rep_bytes), o_meta = index.take(meta_bytes);
+    const size_t o_flags = index.take(sizeof(CellFlags)), bare = index.bytes;
+    const size_t o_cells = index.take(cell_bytes);
+    // The sort works in the objects' own array, which is only written after
+    // it; sets too small for that (the arrays are aligned) get scratch of their own,
+    // as does the list of segments over many cells.
+    Carve sort;
+    const size_t o_low = sort.take((size_t)n), o_k0 = sort.take(order_bytes), o_k1 = sort.take(order_bytes);
+    const size_t o_v1 = sort.take(order_bytes), o_counts = sort.take(sizeof(uint32_t) * (size_t)ncount);
+    const size_t o_part = sort.take(sizeof(uint32_t) * (size_t)npart);
+    Scratch scratch;
+    if (top >= 0 && (scratch.alloc(long_bytes) != hipSuccess ||
+                     device_acquire(&out->block, index.bytes, &out->block_bytes) != hipSuccess)) {
+        (void)hipGetLastError();
+        out->block = nullptr;
+    }
+    const bool cells = top >= 0 && out->block;
+    if (!out->block) HV_TRY(device_acquire(&out->block, bare, &out->block_bytes));
+    unsigned char *const block = static_cast<unsigned char *>(out->block);
+    out->obj = reinterpret_cast<double *>(block + o_obj);
+    out->order = reinterpret_cast<uint32_t *>(block + o_order);
+    out->nodes = reinterpret_cast<double4 *>(block + o_nodes);
+    out->rep = reinterpret_cast<double2 *>(block + o_rep);
+    out->meta = reinterpret_cast<int64_t *>(block + o_meta);
+    CellFlags *const flags = reinterpret_cast<CellFlags *>(block + o_flags);
+    if (cells) {
+        out->cells = reinterpret_cast<uint32_t *>(block + o_cells);
+        out->cell_top = top;
+    }
+    out->device_bytes = (int64_t)(obj_bytes + order_bytes + node_bytes + rep_bytes + (cells ? cell_bytes : 0));
+    Scratch small;
+    unsigned char *work = reinterpret_cast<unsigned char *>(out->obj);
+    if (sort.bytes > obj_bytes) {
+        HV_TRY(small.alloc(sort.bytes));
+        work = small.p;
     }
 
     {
@@ -643,58 +696,51 @@ BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStr
             meta[l] = out->level_off[l];
             meta[kMaxLevels + l] = out->level_cnt[l];
         }
-        HV_TRY(hipMemcpy(out->meta, meta, sizeof(meta), hipMemcpyHostToDevice));
+        HV_TRY(hipMemcpyAsync(out->meta, meta, sizeof(meta), hipMemcpyHostToDevice, st));
+        HV_TRY(hipStreamSynchronize(st));
     }
     HV_TRY(hipMemsetAsync(flags, 0, sizeof(CellFlags), st));
-    const int64_t g = cdiv(n, 256);
-    if (seg)
-        hipLaunchKernelGGL(k_project_key<4>, dim3((uint32_t)g), dim3(256), 0, st, objects, n, merc, proj, k0, v0, bits, &flags->bad);
-    else
-        hipLaunchKernelGGL(k_project_key<2>, dim3((uint32_t)g), dim3(256), 0, st, objects, n, merc, proj, k0, v0, bits, &flags->bad);
+    const dim3 g((uint32_t)cdiv(n, 256)), t(256);
+    uint8_t *const low = work + o_low;
+    uint32_t *kin = reinterpret_cast<uint32_t *>(work + o_k0), *kout = reinterpret_cast<uint32_t *>(work + o_k1);
+    uint32_t *const v1 = reinterpret_cast<uint32_t *>(work + o_v1);
+    uint32_t *const counts = reinterpret_cast<uint32_t *>(work + o_counts);
+    uint32_t *const part = reinterpret_cast<uint32_t *>(work + o_part);
+    if (seg) hipLaunchKernelGGL(k_project_key<4>, g, t, 0, st, objects, n, merc, low, kin, bits, &flags->bad);
+    else hipLaunchKernelGGL(k_project_key<2>, g, t, 0, st, objects, n, merc, low, kin, bits, &flags->bad);
     HV_TRY(hipGetLastError());
 
-    uint64_t *kin = k0, *kout = k1;
-    uint32_t *vin = v0, *vout = v1;
+    // the last pass writes the stored order
+    uint32_t *vin = nullptr, *vout = passes % 2 ? out->order : v1;
     for (int p = 0; p < passes; ++p) {
-        const int shift = 8 * p;
-        hipLaunchKernelGGL(k_radix_hist, dim3((uint32_t)nb), dim3(kRT), 0, st, kin, n, shift, counts, nb);
+        const int shift = 8 * (p - 1);
+        const dim3 gs((uint32_t)nb), ts(kST);
+        if (p == 0) hipLaunchKernelGGL(k_radix_hist<true>, gs, ts, 0, st, low, kin, n, 0, counts, nb);
+        else hipLaunchKernelGGL(k_radix_hist<false>, gs, ts, 0, st, low, kin, n, shift, counts, nb);
         hipLaunchKernelGGL(k_scan_reduce, dim3((uint32_t)npart), dim3(kRT), 0, st, counts, ncount, part);
         hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, st, part, npart);
         hipLaunchKernelGGL(k_scan_down, dim3((uint32_t)npart), dim3(kRT), 0, st, counts, ncount, part);
-        hipLaunchKernelGGL(k_radix_scatter, dim3((uint32_t)nb), dim3(kRT), 0, st, kin, vin, kout, vout, n, shift,
-                           counts, nb);
+        if (p == 0)
+            hipLaunchKernelGGL(k_radix_scatter<true>, gs, ts, 0, st, low, kin, vin, kout, vout, n, 0, counts, nb);
+        else hipLaunchKernelGGL(k_radix_scatter<false>, gs, ts, 0, st, low, kin, vin, kout, vout, n, shift, counts, nb);
         HV_TRY(hipGetLastError());
         std::swap(kin, kout);
-        std::swap(vin, vout);
+        vin = vout;
+        vout = vin == v1 ? out->order : v1;
     }
-    if (vin != out->order)
-        HV_TRY(hipMemcpyAsync(out->order, vin, sizeof(uint32_t) * n, hipMemcpyDeviceToDevice, st));
 
     if (seg)
-        hipLaunchKernelGGL(k_gather<4>, dim3((uint32_t)g), dim3(256), 0, st, proj, out->order, n, out->obj);
+        hipLaunchKernelGGL(k_gather_leaves<4>, g, t, 0, st, objects, out->order, n, merc, out->obj, out->nodes, out->rep);
     else
-        hipLaunchKernelGGL(k_gather<2>, dim3((uint32_t)g), dim3(256), 0, st, proj, out->order, n, out->obj);
-    const int64_t nl = out->level_cnt[0];
-    if (seg)
-        hipLaunchKernelGGL(k_leaf_boxes<4>, dim3((uint32_t)cdiv(nl, 256)), dim3(256), 0, st, out->obj, n, out->nodes, nl);
-    else
-        hipLaunchKernelGGL(k_leaf_boxes<2>, dim3((uint32_t)cdiv(nl, 256)), dim3(256), 0, st, out->obj, n, out->nodes, nl);
+        hipLaunchKernelGGL(k_gather_leaves<2>, g, t, 0, st, objects, out->order, n, merc, out->obj, out->nodes, out->rep);
     for (int l = 1; l < levels; ++l) {
-        const int64_t np = out->level_cnt[l];
-        hipLaunchKernelGGL(k_level_boxes, dim3((uint32_t)cdiv(np, 256)), dim3(256), 0, st,
-                           out->nodes + out->level_off[l - 1], out->level_cnt[l - 1], out->nodes + out->level_off[l], np);
-    }
-    for (int l = 0; l < levels; ++l) {
-        const int64_t np = out->level_cnt[l];
-        if (seg)
-            hipLaunchKernelGGL(k_node_reps<4>, dim3((uint32_t)cdiv(np, 256)), dim3(256), 0, st, out->obj, 4 * (l + 1),
-                               out->rep + out->level_off[l], np);
-        else
-            hipLaunchKernelGGL(k_node_reps<2>, dim3((uint32_t)cdiv(np, 256)), dim3(256), 0, st, out->obj, 4 * (l + 1),
-                               out->rep + out->level_off[l], np);
+        const int64_t c = out->level_off[l - 1], nc = out->level_cnt[l - 1], at = out->level_off[l];
+        hipLaunchKernelGGL(k_level, dim3((uint32_t)cdiv(nc, 256)), t, 0, st, out->nodes + c, out->rep + c, nc,
+                           out->nodes + at, out->rep + at);
     }
     HV_TRY(hipGetLastError());
-    if (out->cells) HV_TRY(build_cells(out->obj, n, seg, out->cell_top, out->cells, flags, longs, st));
+    if (cells)
+        HV_TRY(build_cells(out->obj, n, seg, top, out->cells, flags, reinterpret_cast<uint32_t *>(scratch.p), st));
     CellFlags found;
     HV_TRY(hipMemcpyAsync(&found, flags, sizeof found, hipMemcpyDeviceToHost, st));
     HV_TRY(hipStreamSynchronize(st));

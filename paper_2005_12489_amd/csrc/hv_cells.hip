@@ -18,7 +18,7 @@ namespace hv {
 namespace {
 
 constexpr int kLongCells = 56;          // segments over more cells go to the long list
-constexpr int64_t kLongCap = 1 << 20;   // its length
+constexpr int64_t kLongCap = 1 << 20;   // its most entries
 constexpr int kBlock = 128;             // a workgroup marks blocks of kBlock x kBlock cells in LDS
 constexpr int kHalo = 40;               // rows around a block (and one word on either side) that its segments reach
 constexpr int kMarkChunk = 4096;        // objects of a workgroup
@@ -218,7 +218,7 @@ int cell_top(int64_t n) {
     return top;
 }
 
-size_t cell_long_bytes() { return sizeof(uint32_t) * (size_t)kLongCap; }
+size_t cell_long_bytes(int64_t n) { return sizeof(uint32_t) * (size_t)std::min(n, kLongCap); }
 
 hipError_t build_cells(const double *obj, int64_t n, int seg, int top, uint32_t *cells, CellFlags *flags,
                        uint32_t *longs, hipStream_t st) {

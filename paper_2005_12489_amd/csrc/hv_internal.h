@@ -70,9 +70,9 @@ struct CellFlags {
 
 // The finest level for n objects, or -1 if they are too few.
 int cell_top(int64_t n);
-size_t cell_long_bytes();
+size_t cell_long_bytes(int64_t n);
 // Marks the cells of n sorted objects and fills all levels.  flags starts at
-// zero; longs: scratch of cell_long_bytes() (segments only).
+// zero; longs: scratch of cell_long_bytes(n) (segments only).
 hipError_t build_cells(const double *obj, int64_t n, int seg, int top, uint32_t *cells, CellFlags *flags,
                        uint32_t *longs, hipStream_t st);
 
@@ -88,8 +88,19 @@ struct BuildResult {
     const char *msg;
 };
 
+// Device memory for indexes and their builds.  hipFree takes about 29 ms per
+// GB on MI355X, so blocks given back are kept, up to kPoolBytes in all, for
+// the next request that they fit; beyond that the oldest are freed, and all of
+// them before an allocation fails.  device_release waits for the device, as
+// hipFree does.  Safe from several threads; a block stays on its device.
+constexpr size_t kPoolBytes = size_t(1) << 30;
+hipError_t device_acquire(void **p, size_t bytes, size_t *held);
+void device_release(void *p, size_t held);
+
 // Device arrays owned by one index (freed by free_index_arrays).
 struct IndexArrays {
+    void *block = nullptr;       // holds them all
+    size_t block_bytes = 0;
     double *obj = nullptr;
     double4 *nodes = nullptr;
     double2 *rep = nullptr;      // per node: the first vertex of its first object
@@ -111,6 +122,8 @@ struct IndexArrays {
 // Device arrays of a polygon index beyond its box tree (freed by
 // free_poly_arrays).
 struct PolyArrays {
+    void *block = nullptr;       // holds them all
+    size_t block_bytes = 0;
     double *edges = nullptr;     // projected, polygon after polygon in the tree's sorted order
     int64_t *first = nullptr;    // npoly + 1 offsets into edges, by sorted position
     float4 *chunks = nullptr;    // ceil(n_edges / kEdgeChunk) conservative float boxes
