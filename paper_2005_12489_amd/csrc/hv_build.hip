@@ -534,22 +534,22 @@ BuildResult build_polygons(const double *edges, int64_t n, const int64_t *first,
     const size_t o_chunks = index.take(sizeof(float4) * (size_t)nchunk);
     const size_t o_supers = index.take(sizeof(float4) * (size_t)nsuper);
     const size_t o_in = work.take(sizeof(int64_t) * (size_t)(npoly + 1));
-    const size_t o_diag = work.take(sizeof(double) * 4 * (size_t)npoly), o_err = work.take(sizeof(int));
+    const size_t o_diag = work.take(sizeof(double) * 4 * (size_t)npoly), o_flags = work.take(sizeof(CellFlags));
     Scratch scratch;
     hipError_t e;
     if ((e = scratch.alloc(work.bytes)) != hipSuccess) return bail(e);
     int64_t *const in_first = reinterpret_cast<int64_t *>(scratch.p + o_in);
     double *const diag = reinterpret_cast<double *>(scratch.p + o_diag);
-    int *const err = reinterpret_cast<int *>(scratch.p + o_err);
+    CellFlags *const flg = reinterpret_cast<CellFlags *>(scratch.p + o_flags);
     if ((e = hipMemcpyAsync(in_first, first, sizeof(int64_t) * (size_t)(npoly + 1), hipMemcpyHostToDevice, st)) !=
         hipSuccess)
         return bail(e);
-    if ((e = hipMemsetAsync(err, 0, sizeof(int), st)) != hipSuccess) return bail(e);
+    if ((e = hipMemsetAsync(flg, 0, sizeof(CellFlags), st)) != hipSuccess) return bail(e);
     hipLaunchKernelGGL(k_polygon_boxes, dim3((uint32_t)cdiv(npoly, 16)), dim3(256), 0, st, edges, in_first, npoly, merc,
-                       diag, err);
+                       diag, &flg->bad);
     if ((e = hipGetLastError()) != hipSuccess) return bail(e);
     int herr = 0;
-    if ((e = hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess) return bail(e);
+    if ((e = hipMemcpyAsync(&herr, &flg->bad, sizeof(int), hipMemcpyDeviceToHost, st)) != hipSuccess) return bail(e);
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return bail(e);
     if (herr) {
         free_poly_arrays(poly);
@@ -571,7 +571,16 @@ BuildResult build_polygons(const double *edges, int64_t n, const int64_t *first,
         const uint32_t p = order[(size_t)k];
         sorted_first[(size_t)k + 1] = sorted_first[(size_t)k] + (first[p + 1] - first[p]);
     }
-    if ((e = device_acquire(&poly->block, index.bytes, &poly->block_bytes)) != hipSuccess) return bail(e);
+    // (the cells are an aid only: without memory for them, none)
+    const int top = cell_top(n);
+    const size_t bare = index.bytes, cell_bytes = 2 * sizeof(uint32_t) * (size_t)cell_level_words(top + 1);
+    const size_t o_cells = index.take(cell_bytes);
+    bool cells = top >= 0;
+    if (cells && device_acquire(&poly->block, index.bytes, &poly->block_bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        cells = false;
+    }
+    if (!cells && (e = device_acquire(&poly->block, bare, &poly->block_bytes)) != hipSuccess) return bail(e);
     unsigned char *const block = static_cast<unsigned char *>(poly->block);
     poly->edges = reinterpret_cast<double *>(block + o_edges);
     poly->first = reinterpret_cast<int64_t *>(block + o_first);
@@ -590,7 +599,19 @@ BuildResult build_polygons(const double *edges, int64_t n, const int64_t *first,
                            nchunk, poly->supers);
     }
     if ((e = hipGetLastError()) != hipSuccess) return bail(e);
+    CellFlags found = {};
+    if (cells) {
+        tree->cells = reinterpret_cast<uint32_t *>(block + o_cells);
+        if ((e = build_poly_cells(poly->edges, poly->first, tree->obj, npoly, top, tree->cells, flg, st)) != hipSuccess)
+            return bail(e);
+        if ((e = hipMemcpyAsync(&found, flg, sizeof found, hipMemcpyDeviceToHost, st)) != hipSuccess) return bail(e);
+    }
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return bail(e);
+    if (cells) {
+        tree->cell_top = found.outside ? -1 : top;
+        tree->cell_gaps = found.gaps;
+        tree->device_bytes += (int64_t)cell_bytes;
+    }
     tree->device_bytes += (int64_t)(sizeof(double) * 4 * (size_t)n + sizeof(int64_t) * (size_t)(npoly + 1) +
                                     sizeof(float4) * (size_t)(nchunk + nsuper));
     return r;

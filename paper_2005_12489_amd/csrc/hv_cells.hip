@@ -24,7 +24,7 @@ constexpr int kHalo = 40;               // rows around a block (and one word on 
 constexpr int kMarkChunk = 4096;        // objects of a workgroup
 
 struct Line {  // a segment in cells, the upper end first
-    double x0, y0, x1, y1;
+    double x0, y0, x1, y1, slope;  // slope: dx / dy, used only where r0 < r1
     int r0, r1;
 };
 
@@ -49,6 +49,7 @@ __device__ inline Line line_of(double4 s, double G, int g) {
     l.y1 = (down ? s.w : s.y) * G;
     l.r0 = cell_of(l.y0, g);
     l.r1 = cell_of(l.y1, g);
+    l.slope = (l.x1 - l.x0) / (l.y1 - l.y0);
     return l;
 }
 
@@ -59,9 +60,8 @@ __device__ inline void mark(uint32_t *w, uint32_t m) {
 
 // The cells of row r that the line touches; word (xw, y) is base[xw * stride + y].
 __device__ inline void mark_row(const Line &l, int r, int g, int64_t stride, uint32_t *base) {
-    const double slope = (l.x1 - l.x0) / (l.y1 - l.y0);  // used only where r0 < r1
-    double a = r == l.r0 ? l.x0 : l.x0 + ((double)r - l.y0) * slope;
-    double b = r == l.r1 ? l.x1 : l.x0 + ((double)(r + 1) - l.y0) * slope;
+    double a = r == l.r0 ? l.x0 : l.x0 + ((double)r - l.y0) * l.slope;
+    double b = r == l.r1 ? l.x1 : l.x0 + ((double)(r + 1) - l.y0) * l.slope;
     const double lo = fmin(l.x0, l.x1), hi = fmax(l.x0, l.x1);
     a = fmin(fmax(a, lo), hi);
     b = fmin(fmax(b, lo), hi);
@@ -210,6 +210,143 @@ __global__ __launch_bounds__(256) void k_cells_up(uint32_t *cells, int level) {
         even_bits(lo) | (even_bits(hi) << 16);
 }
 
+// ------------------------------------------------------------ polygons
+// Two bits per cell: `in`, the closed cell lies inside some polygon, and `near`,
+// the cell may hold a point of one.  A polygon is drawn at the finest level at
+// which its box spans at most kPolyCells cells, by one wavefront in LDS: the
+// cells its edges come within kPolyEps of, and each row's parity of crossings
+// left of the cells' centres.  A cell that no edge comes near has its centre's
+// parity throughout.
+constexpr double kPolyCells = 61.0;
+constexpr double kPolyEps = 1e-6;  // cells
+
+__device__ inline uint64_t columns64(int c0, int c1) { return (~0ull >> (63 - (c1 - c0))) << c0; }
+
+__device__ inline void or64(uint32_t *w, uint64_t m) {
+    if ((uint32_t)m) atomicOr(&w[0], (uint32_t)m);
+    if ((uint32_t)(m >> 32)) atomicOr(&w[1], (uint32_t)(m >> 32));
+}
+
+__global__ __launch_bounds__(256) void k_poly_cells(const double4 *__restrict__ edges, const int64_t *__restrict__ first,
+                                                    const double4 *__restrict__ boxes, int64_t npoly, int top,
+                                                    uint32_t *in, uint32_t *near, CellFlags *flags) {
+    __shared__ uint32_t lds[4][2][128];  // touched cells, parity: 64 rows of 64 cells
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t k = (int64_t)blockIdx.x * 4 + wv;
+    if (k >= npoly) return;
+    uint32_t *const touched = lds[wv][0], *const odd = lds[wv][1];
+    double4 b = boxes[k];
+    if (!((int)in_world(b.x) & (int)in_world(b.y) & (int)in_world(b.z) & (int)in_world(b.w))) {
+        if (lane == 0) flags->outside = 1;
+        return;
+    }
+    const double ext = fmax(b.z - b.x, b.w - b.y);
+    int level = top;
+    while (level > 0 && ldexp(ext, 8 + level) > kPolyCells) --level;
+    const int g = 256 << level;
+    const double G = (double)g;
+    if (ext * G > kPolyCells) {
+        if (lane == 0) flags->gaps = 1;
+        return;
+    }
+    const int bx = cell_of(b.x * G, g) - 1, by = cell_of(b.y * G, g) - 1;
+    for (int q = lane; q < 128; q += 64) touched[q] = odd[q] = 0;
+    __builtin_amdgcn_wave_barrier();
+    for (int64_t e = first[k] + lane; e < first[k + 1]; e += 64) {
+        const double4 s = edges[e];
+        const double x0 = s.x * G - bx, y0 = s.y * G - by, x1 = s.z * G - bx, y1 = s.w * G - by;
+        const double ylo = fmin(y0, y1), yhi = fmax(y0, y1), xlo = fmin(x0, x1), xhi = fmax(x0, x1);
+        const int r0 = max((int)floor(ylo - kPolyEps), 0), r1 = min((int)floor(yhi + kPolyEps), 63);
+        const double slope = (x1 - x0) / (y1 - y0);  // not used where the ends share a row
+        for (int r = r0; r <= r1; ++r) {
+            double a = x0, c = x1;
+            if (r0 != r1) {
+                // x where the edge enters and leaves the row, within the edge
+                a = x0 + (fmin(fmax((double)r - kPolyEps, ylo), yhi) - y0) * slope;
+                c = x0 + (fmin(fmax((double)r + 1.0 + kPolyEps, ylo), yhi) - y0) * slope;
+                if (!(yhi > ylo)) a = x0, c = x1;
+                a = fmin(fmax(a, xlo), xhi);
+                c = fmin(fmax(c, xlo), xhi);
+            }
+            const int c0 = max((int)floor(fmin(a, c) - kPolyEps), 0), c1 = min((int)floor(fmax(a, c) + kPolyEps), 63);
+            if (c0 <= c1) or64(&touched[2 * r], columns64(c0, c1));
+            const double yc = (double)r + 0.5;
+            if ((y0 > yc) != (y1 > yc)) {
+                const int from = (int)fmin(fmax(floor(x0 + (yc - y0) * slope - 0.5) + 1.0, 0.0), 64.0);
+                if (from < 64) {
+                    const uint64_t m = ~0ull << from;
+                    if ((uint32_t)m) atomicXor(&odd[2 * r], (uint32_t)m);
+                    atomicXor(&odd[2 * r + 1], (uint32_t)(m >> 32));
+                }
+            }
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    // lane r writes row r; cells beyond the world's edge stay unmarked
+    const int y = by + lane;
+    if (y < 0 || y >= g) return;
+    uint64_t world = bx < 0 ? ~1ull : ~0ull;
+    if (g - bx < 64) world &= ~0ull >> (64 - (g - bx));
+    const uint64_t t = ((uint64_t)touched[2 * lane + 1] << 32 | touched[2 * lane]) & world;
+    const uint64_t i = ((uint64_t)odd[2 * lane + 1] << 32 | odd[2 * lane]) & world & ~t;
+    const int64_t stride = cell_stride(level);
+    const int xw = bx >> 5, sh = bx & 31;
+    const int64_t at = cell_level_words(level) + cell_origin(level) + xw * stride + y;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        auto part = [&](uint64_t v) -> uint32_t {
+            return q == 0 ? (uint32_t)(v << sh) : q == 1 ? (uint32_t)(v >> (32 - sh)) : sh ? (uint32_t)(v >> (64 - sh)) : 0u;
+        };
+        const uint32_t mi = part(i), mn = part(t | i);
+        if (mn) mark(near + at + q * stride, mn);
+        if (mi) mark(in + at + q * stride, mi);
+    }
+}
+
+// Bit b of the low half of v doubled into bits 2b and 2b + 1.
+__device__ inline uint32_t twice_bits(uint32_t v) {
+    v &= 0xffffu;
+    v = (v | (v << 8)) & 0x00ff00ffu;
+    v = (v | (v << 4)) & 0x0f0f0f0fu;
+    v = (v | (v << 2)) & 0x33333333u;
+    v = (v | (v << 1)) & 0x55555555u;
+    return v | (v << 1);
+}
+
+// What polygons drawn at coarser levels cover of level `level` (>= 1).
+__global__ __launch_bounds__(256) void k_poly_down(uint32_t *in, uint32_t *near, int level) {
+    const int g = 256 << level;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= (int64_t)(g >> 5) * g) return;
+    const int xw = (int)(i >> (8 + level)), y = (int)(i & (g - 1));
+    const int64_t from = cell_level_words(level - 1) + cell_origin(level - 1) + (xw >> 1) * cell_stride(level - 1) + (y >> 1);
+    const int64_t to = cell_level_words(level) + cell_origin(level) + xw * cell_stride(level) + y;
+    const int half = 16 * (xw & 1);
+    const uint32_t a = twice_bits(in[from] >> half), b = twice_bits(near[from] >> half);
+    if (a) in[to] |= a;
+    if (b) near[to] |= b;
+}
+
+// Level `level` from the one below it: inside where all four cells are, near
+// where one is.
+__global__ __launch_bounds__(256) void k_poly_up(uint32_t *in, uint32_t *near, int level) {
+    const int g = 256 << level;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= (int64_t)(g >> 5) * g) return;
+    const int xw = (int)(i >> (8 + level)), y = (int)(i & (g - 1));
+    const int64_t stride = cell_stride(level + 1);
+    const int64_t from = cell_level_words(level + 1) + cell_origin(level + 1) + 2 * xw * stride + 2 * y;
+    const int64_t to = cell_level_words(level) + cell_origin(level) + xw * cell_stride(level) + y;
+    uint2 a = *reinterpret_cast<const uint2 *>(in + from), b = *reinterpret_cast<const uint2 *>(in + from + stride);
+    const uint32_t al = a.x & a.y, bl = b.x & b.y;
+    const uint32_t inside = even_bits(al & (al >> 1)) | even_bits(bl & (bl >> 1)) << 16;
+    a = *reinterpret_cast<const uint2 *>(near + from), b = *reinterpret_cast<const uint2 *>(near + from + stride);
+    const uint32_t an = a.x | a.y, bn = b.x | b.y;
+    const uint32_t close = even_bits(an | (an >> 1)) | even_bits(bn | (bn >> 1)) << 16;
+    if (inside) in[to] |= inside;
+    if (close) near[to] |= close;
+}
+
 }  // namespace
 
 int cell_top(int64_t n) {
@@ -219,6 +356,22 @@ int cell_top(int64_t n) {
 }
 
 size_t cell_long_bytes(int64_t n) { return sizeof(uint32_t) * (size_t)std::min(n, kLongCap); }
+
+hipError_t build_poly_cells(const double *edges, const int64_t *first, const double *boxes, int64_t npoly, int top,
+                            uint32_t *cells, CellFlags *flags, hipStream_t st) {
+    const int64_t words = cell_level_words(top + 1);
+    uint32_t *const in = cells, *const near = cells + words;
+    hipError_t e = hipMemsetAsync(cells, 0, 2 * sizeof(uint32_t) * (size_t)words, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_poly_cells, dim3((uint32_t)((npoly + 3) / 4)), dim3(256), 0, st,
+                       reinterpret_cast<const double4 *>(edges), first, reinterpret_cast<const double4 *>(boxes), npoly,
+                       top, in, near, flags);
+    for (int l = 1; l <= top; ++l)
+        hipLaunchKernelGGL(k_poly_down, dim3((uint32_t)(256ll << (2 * l)) / 32), dim3(256), 0, st, in, near, l);
+    for (int l = top - 1; l >= 0; --l)
+        hipLaunchKernelGGL(k_poly_up, dim3((uint32_t)(256ll << (2 * l)) / 32), dim3(256), 0, st, in, near, l);
+    return hipGetLastError();
+}
 
 hipError_t build_cells(const double *obj, int64_t n, int seg, int top, uint32_t *cells, CellFlags *flags,
                        uint32_t *longs, hipStream_t st) {

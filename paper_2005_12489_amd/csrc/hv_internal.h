@@ -75,6 +75,11 @@ size_t cell_long_bytes(int64_t n);
 // zero; longs: scratch of cell_long_bytes(n) (segments only).
 hipError_t build_cells(const double *obj, int64_t n, int seg, int top, uint32_t *cells, CellFlags *flags,
                        uint32_t *longs, hipStream_t st);
+// The same for npoly polygons (edges and boxes in sorted order): cells inside
+// some polygon, then, cell_level_words(top + 1) words on, cells that may hold a
+// point of one.
+hipError_t build_poly_cells(const double *edges, const int64_t *first, const double *boxes, int64_t npoly, int top,
+                            uint32_t *cells, CellFlags *flags, hipStream_t st);
 
 // A request as the kernels see it: one tile of one index with its own
 // radius / half-width.  `index` selects an entry of the batch's index table.

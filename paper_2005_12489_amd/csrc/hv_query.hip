@@ -1426,6 +1426,55 @@ __host__ __device__ inline size_t fill_lds_bytes(int cap, int levels, int thread
            align16((kFillGroup + 1) * 8) + align16((size_t)threads * 8) + align16((size_t)threads) + 32;
 }
 
+// Settles the pixels of a fill region from the polygons' cells: inside where a
+// cell at the centre lies inside a polygon, outside where one can hold no point
+// of any.  In cells of 2^-k px, k up to kFillShift, a centre is the corner of
+// four cells and any of them decides; at zoom `top` and beyond it lies within
+// one.  `mask` gets the settled pixels, the words at rows + 32 j those of its
+// row j that are outside.
+constexpr int kFillShift = 4;
+
+template <int RS>
+__device__ __forceinline__ void settle_fill(const DevIndex &ix, const DevReq &rq, int i0, int j0, uint32_t *mask,
+                                            uint8_t *rows) {
+    constexpr int W = RS / 32;
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2), aligned(4)));
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int k = min(ix.cell_top - rq.z, kFillShift), level = rq.z + k;
+    const int64_t stride = cell_stride(level);
+    const uint32_t *in = ix.cells + cell_level_words(level) + cell_origin(level);
+    const uint32_t *near = in + cell_level_words(ix.cell_top + 1);
+    const int gx = (rq.x << 8) + i0 + lane % RS;  // pixel, world
+    for (int row = wv * (64 / RS) + lane / RS; row < RS; row += nw * (64 / RS)) {
+        const int gy = (rq.y << 8) + j0 + row;
+        bool inside, outside;
+        if (k > 0) {
+            const int cx = (gx << k) + (1 << k >> 1) - 1, cy = (gy << k) + (1 << k >> 1) - 1;  // the upper left cell
+            const int64_t at = (cx >> 5) * stride + cy;
+            const int64_t next = ((cx + 1) >> 5) * stride + cy;
+            const uint32_t s0 = (uint32_t)cx & 31u, s1 = (uint32_t)(cx + 1) & 31u;
+            const u32x2 a = *reinterpret_cast<const u32x2 *>(in + at), b = *reinterpret_cast<const u32x2 *>(in + next);
+            const u32x2 c = *reinterpret_cast<const u32x2 *>(near + at), d = *reinterpret_cast<const u32x2 *>(near + next);
+            inside = (((a.x | a.y) >> s0) | ((b.x | b.y) >> s1)) & 1u;
+            outside = !(((c.x & c.y) >> s0) & ((d.x & d.y) >> s1) & 1u);
+        } else {
+            const int cx = gx >> -k, cy = gy >> -k;
+            const int64_t at = (cx >> 5) * stride + cy;
+            inside = (in[at] >> (cx & 31)) & 1u;
+            outside = !((near[at] >> (cx & 31)) & 1u);
+        }
+        if (ix.cell_gaps) outside = false;
+        const uint64_t lit = __ballot(inside), unlit = __ballot(outside);
+        // the wave's 64 pixels are 64 / RS rows of W words
+        if (lane < 2) {
+            const int r2 = W == 1 ? row + lane : row, wd = W == 1 ? 0 : lane;
+            const uint32_t l = (uint32_t)(lit >> (32 * lane)), d = (uint32_t)(unlit >> (32 * lane));
+            mask[r2 * W + wd] = l | d;
+            *reinterpret_cast<uint32_t *>(rows + r2 * 32 + 4 * wd) = d;
+        }
+    }
+}
+
 template <int RS>
 __device__ __forceinline__ void fill_query(const DevIndex &ix, const DevReq &rq, int64_t t, int reg,
                                            const uint32_t *__restrict__ frontier, const int32_t *__restrict__ fmeta,
@@ -1452,7 +1501,24 @@ __device__ __forceinline__ void fill_query(const DevIndex &ix, const DevReq &rq,
             *reinterpret_cast<uint32_t *>(tm + (ry * RS + k / W) * 32 + rx * (RS / 8) + 4 * (k % W)) = 0u;
         return;
     }
-    for (int k = tid; k < RS * W; k += nthr) mask[k] = 0;
+    const bool settled = ix.cell_top >= 0;
+    uint8_t *const out_rows = tm + ry * RS * 32 + rx * (RS / 8);
+    if (settled) {
+        settle_fill<RS>(ix, rq, (int)i0, (int)j0, mask, out_rows);
+        __syncthreads();
+        bool full = true;
+        for (int k = tid; k < RS * W; k += nthr) full &= mask[k] == 0xffffffffu;
+        if (__syncthreads_and(full)) {
+            for (int k = tid; k < RS * W; k += nthr) {
+                uint32_t *const o = reinterpret_cast<uint32_t *>(out_rows + (k / W) * 32 + 4 * (k % W));
+                *o = ~*o;
+            }
+            __syncthreads();
+            return;
+        }
+    } else {
+        for (int k = tid; k < RS * W; k += nthr) mask[k] = 0;
+    }
     if (tid == 0) {
         ctl[0] = 0;
         ctl[1] = 0;
@@ -1751,8 +1817,8 @@ __device__ __forceinline__ void fill_query(const DevIndex &ix, const DevReq &rq,
     if (!done && ctl[1] > 0) test();
     __syncthreads();
     for (int k = tid; k < RS * W; k += nthr) {
-        const int row = k / W, wd = k % W;
-        *reinterpret_cast<uint32_t *>(tm + (ry * RS + row) * 32 + rx * (RS / 8) + 4 * wd) = mask[k];
+        uint32_t *const o = reinterpret_cast<uint32_t *>(out_rows + (k / W) * 32 + 4 * (k % W));
+        *o = settled ? mask[k] & ~*o : mask[k];
     }
     __syncthreads();
 }
