@@ -165,10 +165,21 @@ thread_local HostStage t_stage;
 thread_local HostStage t_stage_b, t_stage_map;
 
 // Copies the staged workspace to a fresh stream-ordered device allocation
-// and launches the query; the allocation is released in stream order.
+// and launches the query; the allocation is released in stream order.  A batch
+// of few requests needs no copy.
 int run_batch(const hv::DevIndex *ixs, int n_ix, int max_levels, const hv::DevReq *reqs, int64_t n_req,
               uint8_t *out, const hv::LaunchShape &shape, const char *who, hipEvent_t *marks = nullptr,
               HostStage &st = t_stage) {
+    if (hv::few_requests(shape, n_req, n_ix)) {
+        unsigned char *dws = nullptr;
+        hipError_t e = hipMallocAsync((void **)&dws, hv::few_bytes(n_req), t_stream);
+        if (e != hipSuccess) return hip_status(e, who);
+        e = hv::launch_few(ixs, n_ix, reqs, n_req, out, dws, max_levels, shape, t_stream, marks);
+        const hipError_t ef = hipFreeAsync(dws, t_stream);
+        if (e != hipSuccess) return hip_status(e, who);
+        if (ef != hipSuccess) return hip_status(ef, who);
+        return HV_OK;
+    }
     const hv::Workspace w = hv::workspace_layout(n_req, n_ix);
     hipError_t e = st.acquire(w.staged_bytes());
     if (e != hipSuccess) return hip_status(e, who);

@@ -222,6 +222,16 @@ hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, 
                         hipStream_t stream, hipEvent_t *marks = nullptr);
 
 
+// Batches that travel in the kernels' arguments: this many requests over this
+// many indexes, in the default shape or filling.
+constexpr int kFewRequests = 64, kFewIndexes = 4;
+bool few_requests(const LaunchShape &s, int64_t n_req, int n_ix);
+// Device bytes that launch_few needs at dws, and the launch itself (marks as for
+// launch_query).
+size_t few_bytes(int64_t n_req);
+hipError_t launch_few(const DevIndex *ixs, int n_ix, const DevReq *reqs, int64_t n_req, uint8_t *out, unsigned char *dws,
+                      int max_levels, const LaunchShape &s, hipStream_t st, hipEvent_t *marks);
+
 // The object kernel (hv_objects.h): tiles whose frontier lies at the leaves or
 // one level above, in strips of whole pixel rows, a workgroup to a strip.  More
 // strips spread a tile's objects over more workgroups, and each reads the

@@ -105,39 +105,40 @@ __device__ inline uint64_t wave_or64(uint64_t v) {
     return v;
 }
 
+// A tile's frontier: its nodes (in LDS), their number and level, and the regions
+// they can reach.
+struct Frontier {
+    const uint32_t *nodes;
+    int n, level;
+    uint64_t regions;
+};
+
+// LDS of one request's walk.
+struct FrontierLds {
+    uint32_t buf[2][kFrontier];
+    int count;
+    unsigned long long regions;
+};
+
 // rs: region side of the query kernel that follows (32 or 64), for which the
 // frontier records the regions its nodes can reach; 0 marks every part.
 // cull (1..kFrontier): the cull depth -- the walk goes one level deeper only
 // while that level holds at most cull nodes meeting the tile.
 // grow (px) widens the tile's box beyond r on every side: 1/4 for
 // anti-aliased output, whose sub-samples lie 1/4 px from the pixel centres.
-// objects: tiles whose frontier lies at level 0 or 1 go to the object kernel's
-// lists, not to the region kernel's.
-// WPT wavefronts per request: one in large batches, which fill the GPU anyway;
-// in small ones the walk's time is its chain of loads, up to 4,096 children of
-// a level's 256 nodes, and more wavefronts shorten it.
+// WPT wavefronts per request, tid their lanes: one in large batches, which fill
+// the GPU anyway; in small ones the walk's time is its chain of loads, up to
+// 4,096 children of a level's 256 nodes, and more wavefronts shorten it.
 template <int WPT>
-__global__ __launch_bounds__(WPT > 4 ? 64 * WPT : 256) void k_tile_frontier(DevBatch B, int rs, int cull, double grow, int objects) {
-    constexpr int kTiles = WPT > 4 ? 1 : 4 / WPT;  // requests of a workgroup
-    __shared__ uint32_t buf[kTiles][2][kFrontier];
-    __shared__ int count[kTiles];
-    __shared__ unsigned long long regions[kTiles];
-    const int lane = threadIdx.x & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: keeps per-tile values scalar
-    const int slot = wv / WPT, tid = (int)threadIdx.x - slot * 64 * WPT;
-    if (blockIdx.x == 0 && threadIdx.x == 0) B.hdr->t_start = wall_clock64();
-    const int64_t i = (int64_t)blockIdx.x * kTiles + slot;
-    const int64_t n_req = B.hdr->n_req;
-    if (i >= n_req) return;  // with several wavefronts to a request, a whole workgroup's
-    const int64_t t = B.order[i];  // requests by zoom, lowest first: the list follows this order
-    const DevReq rq = B.reqs[t];
-    const DevIndex ix = B.ixs[rq.index];
+__device__ __forceinline__ Frontier frontier_walk(const DevIndex &ix, const DevReq &rq, int rs, int cull, double grow,
+                                                  int tid, FrontierLds &lds) {
+    const int lane = tid & 63;
     const double iS = ldexp(1.0, -8 - rq.z), S = ldexp(256.0, rq.z);
     const double ox = 256.0 * (double)rq.x, oy = 256.0 * (double)rq.y;
     const double m = rq.r + grow + kCullPad;
     const double qx0 = (ox + (0.5 - m)) * iS, qx1 = (ox + (255.5 + m)) * iS;
     const double qy0 = (oy + (0.5 - m)) * iS, qy1 = (oy + (255.5 + m)) * iS;
-    uint32_t *cur = buf[slot][0], *nxt = buf[slot][1];
+    uint32_t *cur = lds.buf[0], *nxt = lds.buf[1];
     int ncur = 0, lvl = ix.levels - 1;
     uint64_t cbits = ~0ull;  // regions the current frontier level can reach
     auto sync = [&]() {
@@ -147,8 +148,8 @@ __global__ __launch_bounds__(WPT > 4 ? 64 * WPT : 256) void k_tile_frontier(DevB
     auto begin_level = [&]() {
         if (WPT > 1) {
             if (tid == 0) {
-                count[slot] = 0;
-                regions[slot] = 0;
+                lds.count = 0;
+                lds.regions = 0;
             }
             __syncthreads();
         }
@@ -156,11 +157,11 @@ __global__ __launch_bounds__(WPT > 4 ? 64 * WPT : 256) void k_tile_frontier(DevB
     // appends the lanes' hits to a level's list of `n` nodes; its new length
     auto take = [&](bool hit, uint32_t node, uint32_t *to, int n) -> int {
         const uint64_t hm = __ballot(hit);
-        const int pos = WPT > 1 ? wave_alloc(&count[slot], hm, lane) : n + (int)lanes_below(hm);
+        const int pos = WPT > 1 ? wave_alloc(&lds.count, hm, lane) : n + (int)lanes_below(hm);
         if (hit && pos < cull) to[pos] = node;
         if (WPT == 1) return n + __popcll(hm);
         __syncthreads();
-        n = count[slot];
+        n = lds.count;
         __syncthreads();
         return n;
     };
@@ -168,9 +169,9 @@ __global__ __launch_bounds__(WPT > 4 ? 64 * WPT : 256) void k_tile_frontier(DevB
         if (!rs) return;
         cbits = wave_or64(bits);
         if (WPT > 1) {
-            if (lane == 0) atomicOr(&regions[slot], (unsigned long long)cbits);
+            if (lane == 0) atomicOr(&lds.regions, (unsigned long long)cbits);
             __syncthreads();
-            cbits = regions[slot];
+            cbits = lds.regions;
             __syncthreads();
         }
     };
@@ -225,18 +226,37 @@ __global__ __launch_bounds__(WPT > 4 ? 64 * WPT : 256) void k_tile_frontier(DevB
         end_level(nbits);
         --lvl;
     }
-    if (ncur == 0) {
+    return Frontier{cur, ncur, lvl, cbits};
+}
+
+// objects: tiles whose frontier lies at level 0 or 1 go to the object kernel's
+// lists, not to the region kernel's.
+template <int WPT>
+__global__ __launch_bounds__(256) void k_tile_frontier(DevBatch B, int rs, int cull, double grow, int objects) {
+    static_assert(4 % WPT == 0, "a workgroup is four wavefronts");
+    __shared__ FrontierLds lds[4 / WPT];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: keeps per-tile values scalar
+    const int slot = wv / WPT, tid = (int)threadIdx.x - slot * 64 * WPT;
+    if (blockIdx.x == 0 && threadIdx.x == 0) B.hdr->t_start = wall_clock64();
+    const int64_t i = (int64_t)blockIdx.x * (4 / WPT) + slot;
+    const int64_t n_req = B.hdr->n_req;
+    if (i >= n_req) return;  // with four wavefronts to a request, the whole workgroup
+    const int64_t t = B.order[i];  // requests by zoom, lowest first: the list follows this order
+    const DevReq rq = B.reqs[t];
+    const DevIndex ix = B.ixs[rq.index];
+    const Frontier f = frontier_walk<WPT>(ix, rq, rs, cull, grow, tid, lds[slot]);
+    if (f.n == 0) {
         // no data within r of the tile: its mask is all zero, written by the
         // query kernel
         if (tid == 0) B.elist[atomicAdd(&B.hdr->ecounter, 1)] = (uint32_t)t;
         return;
     }
-    for (int k = tid; k < ncur; k += 64 * WPT) B.frontier[t * kFrontier + k] = cur[k];
+    for (int k = tid; k < f.n; k += 64 * WPT) B.frontier[t * kFrontier + k] = f.nodes[k];
     if (tid == 0) {
-        reinterpret_cast<int4 *>(B.fmeta)[t] = make_int4(ncur, lvl, (int)(uint32_t)cbits, (int)(uint32_t)(cbits >> 32));
+        reinterpret_cast<int4 *>(B.fmeta)[t] = make_int4(f.n, f.level, (int)(uint32_t)f.regions, (int)(uint32_t)(f.regions >> 32));
         B.done[t] = 0;
-        if (objects && lvl == 0) B.list[n_req - 1 - atomicAdd(&B.hdr->leaf_tiles, 1)] = (uint32_t)t;
-        else if (objects && lvl == 1) B.elist[n_req - 1 - atomicAdd(&B.hdr->node_tiles, 1)] = (uint32_t)t;
+        if (objects && f.level == 0) B.list[n_req - 1 - atomicAdd(&B.hdr->leaf_tiles, 1)] = (uint32_t)t;
+        else if (objects && f.level == 1) B.elist[n_req - 1 - atomicAdd(&B.hdr->node_tiles, 1)] = (uint32_t)t;
         else B.list[atomicAdd(&B.hdr->counter, 1)] = (uint32_t)t;
     }
 }
@@ -1348,9 +1368,8 @@ __global__ __launch_bounds__(kStripThreads) __attribute__((amdgpu_waves_per_eu(A
     for (int64_t u = blockIdx.x; u < items; u += gridDim.x) object_item<AA>(B, u, kLeafStrips, kNodeStrips, B.hdr->out, L);
 }
 
-// Up to this many requests leave workgroups to spare: tiles are cut into twice
-// the strips (a screen of 21 tiles 47 -> 32 us; 256 sparse tiles 20 -> 25).
-constexpr int kFewRequests = 64;
+// Up to kFewRequests requests leave workgroups to spare: tiles are cut into
+// twice the strips (a screen of 21 tiles 47 -> 32 us; 256 sparse tiles 20 -> 25).
 constexpr int kBothWaves = kStripThreads / 64, kBothRegion = 32, kBothOpl = 2;
 
 template <int AA>
@@ -1823,11 +1842,10 @@ __device__ __forceinline__ void fill_query(const DevIndex &ix, const DevReq &rq,
     __syncthreads();
 }
 
+// The workgroup's LDS; the group parity rows start at zero and every group
+// clears what it used.
 template <int RS>
-__global__ __launch_bounds__(256) void k_fill_region(DevBatch B, int cap, int max_levels) {
-    extern __shared__ double4 smem[];
-    constexpr int RPT = (256 / RS) * (256 / RS);
-    unsigned char *base = reinterpret_cast<unsigned char *>(smem);
+__device__ inline FillLds fill_lds(unsigned char *base, int cap, int max_levels) {
     FillLds L;
     L.stk = reinterpret_cast<uint32_t *>(base);
     unsigned char *cb = base + align16((size_t)region_stack_words(max_levels, blockDim.x) * 4);
@@ -1846,9 +1864,16 @@ __global__ __launch_bounds__(256) void k_fill_region(DevBatch B, int cap, int ma
     L.ls = L.spre + align16((kFillGroup + 1) * 8) / 8;
     L.lsq = reinterpret_cast<uint8_t *>(L.ls + blockDim.x);
     L.ctl = reinterpret_cast<int *>(L.lsq + align16(blockDim.x));
-    // the group parity rows start at zero and every group clears what it used
     for (int k = threadIdx.x; k < kFillGroup * RS * (RS / 32); k += blockDim.x) L.par[k] = 0;
     __syncthreads();
+    return L;
+}
+
+template <int RS>
+__global__ __launch_bounds__(256) void k_fill_region(DevBatch B, int cap, int max_levels) {
+    extern __shared__ double4 smem[];
+    constexpr int RPT = (256 / RS) * (256 / RS);
+    const FillLds L = fill_lds<RS>(reinterpret_cast<unsigned char *>(smem), cap, max_levels);
     uint8_t *const out = B.hdr->out;
     zero_empty_tiles(B, out);
     const ItemMap im(B.hdr->counter, RPT);
@@ -1860,6 +1885,93 @@ __global__ __launch_bounds__(256) void k_fill_region(DevBatch B, int cap, int ma
         fill_query<RS>(ix, rq, t, reg, B.frontier, B.fmeta, out, cap, L);
         if (threadIdx.x == 0) part_done(B, t, RPT);
     }
+}
+
+// ------------------------------------------------------------ small batches
+// A batch of at most kFewRequests requests travels in the kernels' arguments:
+// no staging copy, and no lists or counters to clear -- every request has as
+// many workgroups as the kind of tile with the most parts, and those without a
+// part end at once.  (One tile of 10k points: 5 us of copy before 17 us of
+// kernels, and a third of the call's host time.)
+struct FewBatch {
+    uint8_t *out;
+    uint32_t *frontier;  // per request: up to 256 frontier nodes
+    int32_t *fmeta;      // per request: frontier size (0: no data within r), level, 64 bits of regions
+    int32_t rs, cull;
+    double grow;
+    DevIndex ixs[kFewIndexes];
+    DevReq reqs[kFewRequests];
+};
+static_assert(sizeof(FewBatch) + 16 <= 4096, "kernel arguments");
+
+// The batch where the launch put it: indexing the parameter itself would copy
+// it to every thread's stack.
+__device__ inline const FewBatch &few_batch() {
+    return *reinterpret_cast<const FewBatch *>((const void *)__builtin_amdgcn_kernarg_segment_ptr());
+}
+
+__global__ __launch_bounds__(256) void k_few_frontier(FewBatch) {
+    __shared__ FrontierLds lds;
+    const FewBatch &A = few_batch();
+    const int t = blockIdx.x, tid = threadIdx.x;
+    const DevReq rq = A.reqs[t];
+    const DevIndex ix = A.ixs[rq.index];
+    const Frontier f = frontier_walk<4>(ix, rq, A.rs, A.cull, A.grow, tid, lds);
+    for (int k = tid; k < f.n; k += 256) A.frontier[t * kFrontier + k] = f.nodes[k];
+    if (tid == 0)
+        reinterpret_cast<int4 *>(A.fmeta)[t] = make_int4(f.n, f.level, (int)(uint32_t)f.regions, (int)(uint32_t)(f.regions >> 32));
+}
+
+// One of `parts` equal pieces of a tile's bytes.
+__device__ inline void zero_part(uint8_t *tile, int tile_bytes, int part, int parts) {
+    uint4 *m4 = reinterpret_cast<uint4 *>(tile);
+    const int n = tile_bytes / 16 / parts;
+    for (int k = threadIdx.x; k < n; k += blockDim.x) m4[part * n + k] = make_uint4(0, 0, 0, 0);
+}
+
+template <int AA>
+__global__ __launch_bounds__(kStripThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_few_query(FewBatch, int cap, int max_levels) {
+    extern __shared__ double4 smem[];
+    constexpr int RPT = (256 / kBothRegion) * (256 / kBothRegion);
+    const FewBatch &A = few_batch();
+    const int t = blockIdx.x / RPT, part = blockIdx.x % RPT;
+    const int4 fm = reinterpret_cast<const int4 *>(A.fmeta)[t];
+    const DevReq rq = A.reqs[t];
+    const DevIndex ix = A.ixs[rq.index];
+    if (fm.x == 0) {
+        constexpr int kBytes = AA ? HV_AA_BYTES : HV_MASK_BYTES;
+        if (part < 4) zero_part(A.out + (int64_t)t * kBytes, kBytes, part, 4);
+        return;
+    }
+    if (fm.y > 1) {
+        const RegionLds L = region_lds<kBothRegion, kBothOpl, AA>(reinterpret_cast<unsigned char *>(smem), cap, max_levels);
+        if (ix.seg) region_query<kBothRegion, 1, kBothOpl, AA>(ix, rq, t, part, A.frontier, A.fmeta, A.out, cap, L);
+        else region_query<kBothRegion, 0, kBothOpl, AA>(ix, rq, t, part, A.frontier, A.fmeta, A.out, cap, L);
+        return;
+    }
+    const int strips = 2 * (fm.y ? kNodeStrips : kLeafStrips);
+    if (part >= strips) return;
+    const int rows = 256 / strips, j0 = part * rows;
+    StripLds<AA> &L = *reinterpret_cast<StripLds<AA> *>(smem);
+    if (ix.seg) strip<1, AA>(ix, rq, t, fm.x, fm.y, j0, rows, A.frontier, A.out, L);
+    else strip<0, AA>(ix, rq, t, fm.x, fm.y, j0, rows, A.frontier, A.out, L);
+}
+
+template <int RS>
+__global__ __launch_bounds__(256) void k_few_fill(FewBatch, int cap, int max_levels) {
+    extern __shared__ double4 smem[];
+    constexpr int RPT = (256 / RS) * (256 / RS);
+    const FewBatch &A = few_batch();
+    const int t = blockIdx.x / RPT, part = blockIdx.x % RPT;
+    const int4 fm = reinterpret_cast<const int4 *>(A.fmeta)[t];
+    if (fm.x == 0) {
+        zero_part(A.out + (int64_t)t * HV_MASK_BYTES, HV_MASK_BYTES, part, RPT);
+        return;
+    }
+    const FillLds L = fill_lds<RS>(reinterpret_cast<unsigned char *>(smem), cap, max_levels);
+    const DevReq rq = A.reqs[t];
+    const DevIndex ix = A.ixs[rq.index];
+    fill_query<RS>(ix, rq, t, part, A.frontier, A.fmeta, A.out, cap, L);
 }
 
 // Batches of up to this many requests take four wavefronts to a request's frontier.
@@ -2021,6 +2133,38 @@ hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, 
     else if (s.block == 8) hipLaunchKernelGGL(k_query<8>, g, b, lds, st, B, s.cand_cap, max_levels);
     else if (s.block == 16) hipLaunchKernelGGL(k_query<16>, g, b, lds, st, B, s.cand_cap, max_levels);
     else hipLaunchKernelGGL(k_query<32>, g, b, lds, st, B, s.cand_cap, max_levels);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (marks && (e = hipEventRecord(marks[2], st)) != hipSuccess) return e;
+    return hipSuccess;
+}
+
+bool few_requests(const LaunchShape &s, int64_t n_req, int n_ix) {
+    return n_req <= kFewRequests && n_ix <= kFewIndexes && (s.fill || in_one_launch(s));
+}
+
+size_t few_bytes(int64_t n_req) { return (size_t)n_req * (sizeof(uint32_t) * kFrontier + sizeof(int32_t) * 4); }
+
+hipError_t launch_few(const DevIndex *ixs, int n_ix, const DevReq *reqs, int64_t n_req, uint8_t *out, unsigned char *dws,
+                      int max_levels, const LaunchShape &s, hipStream_t st, hipEvent_t *marks) {
+    FewBatch A;
+    A.out = out;
+    A.fmeta = reinterpret_cast<int32_t *>(dws);
+    A.frontier = reinterpret_cast<uint32_t *>(dws + sizeof(int32_t) * 4 * (size_t)n_req);
+    A.rs = s.region;
+    A.cull = s.cull;
+    A.grow = s.aa ? 0.25 : 0.0;
+    memcpy(A.ixs, ixs, sizeof(DevIndex) * (size_t)n_ix);
+    memcpy(A.reqs, reqs, sizeof(DevReq) * (size_t)n_req);
+    hipError_t e;
+    if (marks && (e = hipEventRecord(marks[0], st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_few_frontier, dim3((uint32_t)n_req), dim3(256), 0, st, A);
+    if (marks && (e = hipEventRecord(marks[1], st)) != hipSuccess) return e;
+    const size_t lds = query_lds_bytes(s, max_levels);
+    const dim3 g((uint32_t)(n_req * (256 / s.region) * (256 / s.region))), b((uint32_t)(64 * s.waves));
+    if (s.fill && s.region == 64) hipLaunchKernelGGL(k_few_fill<64>, g, b, lds, st, A, s.cand_cap, max_levels);
+    else if (s.fill) hipLaunchKernelGGL(k_few_fill<32>, g, b, lds, st, A, s.cand_cap, max_levels);
+    else if (s.aa) hipLaunchKernelGGL(k_few_query<1>, g, b, lds, st, A, s.cand_cap, max_levels);
+    else hipLaunchKernelGGL(k_few_query<0>, g, b, lds, st, A, s.cand_cap, max_levels);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (marks && (e = hipEventRecord(marks[2], st)) != hipSuccess) return e;
     return hipSuccess;
