@@ -121,8 +121,9 @@ int hv_set_stream(void *hip_stream);
  * the batch size n: region = 32, objs_per_lane 2, waves_per_wg 4 for
  * n < 1024, 2 for n < 4096 and 1 beyond (in a small batch the heaviest
  * regions set the time and more waves shorten them; a large one fills the
- * GPU with single-wave groups), cand_cap 128 * waves_per_wg and cull_nodes
- * 256.  Anti-aliased output takes the same default; filling has its own
+ * GPU with single-wave groups; n counts as smaller where few of the requests
+ * lie in dense data), cand_cap 128 * waves_per_wg (96 for one wave) and
+ * cull_nodes 256.  Anti-aliased output takes the same default; filling has its own
  * (hv_render_fill).  In a given shape, zero
  * fields take block 16, waves_per_wg 2 (1 in region mode), objs_per_lane
  * 1, cand_cap 64 * waves_per_wg * objs_per_lane in region mode (64
@@ -133,7 +134,8 @@ typedef struct {
     int32_t cand_cap;       /* LDS candidate capacity per wavefront, >= 64 */
     int32_t waves_per_wg;   /* wavefronts per workgroup: 1, 2 or 4 */
     int32_t grid_wgs;       /* workgroups of the persistent query kernel; 0 = ten times as many as fit on
-                               the GPU (filling: one per region, at most 262,144) */
+                               the GPU (filling, and masks with one wave per workgroup: one per
+                               region, at most 2^20) */
     int32_t region;         /* 0: one wavefront per pixel block; 32 or 64: one workgroup per region of
                                that side whose queued objects are dealt out over all lanes (block is
                                then unused and cand_cap sizes the queue) */

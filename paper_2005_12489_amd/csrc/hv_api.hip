@@ -81,19 +81,31 @@ int validate_style(const hv_style *style) {
     return HV_OK;
 }
 
-// Wavefronts per workgroup of the default shape for a batch of n requests:
-// in small batches the few heaviest regions set the time, and more waves on
-// each region shorten them; in large ones the GPU is full anyway and one wave
-// per region (occupancy bound by registers) does the least work per pixel.
-int default_waves(int64_t n) { return n < 1024 ? 4 : n < 4096 ? 2 : 1; }
+// Wavefronts per workgroup of the default shape for a batch of n requests, of
+// which `dense` hold enough objects for the region kernel: with few of those
+// the heaviest regions set the time, and more waves on each region shorten
+// them; with many the GPU is full anyway and one wave per region (occupancy
+// bound by registers) does the least work per pixel.  4,096 tiles of 10M
+// segments, none dense: 0.39 ms with four waves, 0.47 with one; 10,000
+// requests over 1e9 points, half of them dense: 7.2 ms and 4.6.
+int default_waves(int64_t n, int64_t dense) {
+    return n < 1024 || dense < 256 ? 4 : n < 4096 || dense < 1024 ? 2 : 1;
+}
 
-int resolve_shape(const hv_launch *l, int max_levels, hv::LaunchShape *s, int64_t n) {
-    // default: one workgroup per 32x32 region with default_waves(n) waves,
-    // two objects per lane at a leaf step and the smallest queue that allows
-    // (small LDS); hv_launch selects any other shape
+// A request of zoom z whose index would hold this many objects per tile if they
+// were spread evenly counts as dense: clusters then hold several times the
+// 65,536 up to which a tile goes to the object kernel.
+bool is_dense(int64_t n_objects, int32_t z) { return (double)n_objects >= std::ldexp(16384.0, 2 * z); }
+
+int resolve_shape(const hv_launch *l, int max_levels, hv::LaunchShape *s, int64_t n, int64_t dense) {
+    // default: one workgroup per 32x32 region with default_waves() waves and
+    // two objects per lane at a leaf step; hv_launch selects any other shape
     s->block = 16;
-    s->waves = default_waves(n);
-    s->cand_cap = 64 * s->waves * 2;
+    s->waves = default_waves(n, dense);
+    // (one wave: a queue of 96 takes a leaf step's 128 objects in two parts and
+    // leaves LDS for 16 workgroups a CU instead of 14: 10,000 requests over 1e9
+    // points 4.6 ms instead of 4.9)
+    s->cand_cap = s->waves == 1 ? 96 : 64 * s->waves * 2;
     s->grid = 0;
     s->region = 32;
     s->opl = 2;
@@ -227,6 +239,7 @@ struct BatchPlan {
     std::vector<const hv_index *> owners;
     std::vector<hv::DevReq> reqs;
     int max_levels = 0;
+    int64_t dense = 0, dense_kids = 0;  // dense requests, and those whose child tiles would be
 };
 
 int plan_batch(const hv_request *reqs, int64_t n, BatchPlan *p) {
@@ -264,6 +277,8 @@ int plan_batch(const hv_request *reqs, int64_t n, BatchPlan *p) {
             if (q.index->a.levels > p->max_levels) p->max_levels = q.index->a.levels;
         }
         p->reqs[(size_t)k] = hv::DevReq{q.z, q.x, q.y, slot, q.r_px};
+        p->dense += is_dense(q.index->a.n, q.z);
+        p->dense_kids += is_dense(q.index->a.n, q.z + 1);
     }
     return HV_OK;
 }
@@ -290,7 +305,7 @@ TuneKey batch_key_in(const hv_request *reqs, int64_t n, int *zs, double *rs) {
     std::nth_element(rs, rs + n / 2, rs + n);
     const double rm = rs[n / 2];
     return TuneKey{seg * 2 >= n ? 1 : 0, zs[n / 2] / 4, rm <= 1.0 ? 0 : rm <= 2.0 ? 1 : rm <= 4.0 ? 2 : 3,
-                   default_waves(n)};
+                   default_waves(n, n)};
 }
 
 TuneKey batch_key(const hv_request *reqs, int64_t n) {
@@ -478,7 +493,7 @@ int prepare_fill(const hv_index *index, const hv_tile *tiles, int64_t n_tiles, u
     if (n_tiles > 0 && (!tiles || !out_masks)) return fail(HV_EINVAL, "tiles or out_masks is NULL");
     int rc = validate_tiles(tiles, n_tiles);
     if (rc) return rc;
-    if ((rc = resolve_shape(launch, index->a.levels, shape, n_tiles))) return rc;
+    if ((rc = resolve_shape(launch, index->a.levels, shape, n_tiles, n_tiles))) return rc;
     if (!launch) {
         // filling's default at every batch size: two waves per 32 x 32 region
         shape->waves = 2;
@@ -574,7 +589,9 @@ int hv_render_tiles_ex(const hv_index *index, const hv_tile *tiles, int64_t n_ti
     if (n_tiles > 0 && (!tiles || !out_masks)) return fail(HV_EINVAL, "tiles or out_masks is NULL");
     if ((rc = validate_tiles(tiles, n_tiles))) return rc;
     hv::LaunchShape shape;
-    if ((rc = resolve_shape(launch, index->a.levels, &shape, n_tiles))) return rc;
+    int64_t dense = 0;
+    for (int64_t k = 0; k < n_tiles; ++k) dense += is_dense(index->a.n, tiles[k].z);
+    if ((rc = resolve_shape(launch, index->a.levels, &shape, n_tiles, dense))) return rc;
     if (n_tiles == 0) {
         t_err.clear();
         return HV_OK;
@@ -652,7 +669,7 @@ int hv_render_batch(const hv_request *reqs, int64_t n, uint8_t *out_masks, const
     hv_launch tuned;
     if (!launch && tuned_for(reqs, n, &tuned)) launch = &tuned;
     hv::LaunchShape shape;
-    if ((rc = resolve_shape(launch, p.max_levels, &shape, n))) return rc;
+    if ((rc = resolve_shape(launch, p.max_levels, &shape, n, p.dense))) return rc;
     if (n == 0) {
         t_err.clear();
         return HV_OK;
@@ -671,8 +688,8 @@ namespace {
 
 // The shape of an anti-aliased batch: one pass in region mode, four
 // sub-sample masks per region.
-int aa_shape(const hv_launch *launch, int max_levels, int64_t n, hv::LaunchShape *shape) {
-    int rc = resolve_shape(launch, max_levels, shape, n);
+int aa_shape(const hv_launch *launch, int max_levels, int64_t n, int64_t dense, hv::LaunchShape *shape) {
+    int rc = resolve_shape(launch, max_levels, shape, n, dense);
     if (rc) return rc;
     if (shape->region == 0) {
         shape->region = 32;
@@ -771,8 +788,8 @@ int hv_render_batch_aa(const hv_request *reqs, int64_t n, uint8_t *out_values, c
     int rc = plan_batch(reqs, n, &p);
     if (rc) return rc;
     hv::LaunchShape sa, sb;
-    if ((rc = aa_shape(launch, p.max_levels, n, &sa))) return rc;
-    if ((rc = resolve_shape(launch, p.max_levels, &sb, 4 * n))) return rc;
+    if ((rc = aa_shape(launch, p.max_levels, n, p.dense, &sa))) return rc;
+    if ((rc = resolve_shape(launch, p.max_levels, &sb, 4 * n, 4 * p.dense_kids))) return rc;
     if (n == 0) {
         t_err.clear();
         return HV_OK;
@@ -800,9 +817,10 @@ int time_batch(const hv_request *reqs, int64_t n, uint8_t *out_masks, const hv_l
     hv_launch tuned;
     if (!aa && !launch && tuned_for(reqs, n, &tuned)) launch = &tuned;
     hv::LaunchShape shape, sb;
-    if ((rc = aa ? aa_shape(launch, p.max_levels, n, &shape) : resolve_shape(launch, p.max_levels, &shape, n)))
+    if ((rc = aa ? aa_shape(launch, p.max_levels, n, p.dense, &shape)
+                 : resolve_shape(launch, p.max_levels, &shape, n, p.dense)))
         return rc;
-    if (aa && (rc = resolve_shape(launch, p.max_levels, &sb, 4 * n))) return rc;
+    if (aa && (rc = resolve_shape(launch, p.max_levels, &sb, 4 * n, 4 * p.dense_kids))) return rc;
     if ((rc = validate_out(out_masks))) return rc;
     // six marks: around the frontier and query kernels of the child tiles,
     // then of the one-pass requests (binary batches use the second three)
@@ -941,7 +959,7 @@ int hv_autotune(const hv_request *sample, int64_t n, uint8_t *scratch_masks, hv_
     int best_k = -1;
     for (int k = 0; k < (int)(sizeof(cands) / sizeof(cands[0])) && rc == HV_OK && e == hipSuccess; ++k) {
         hv::LaunchShape shape;
-        if (resolve_shape(&cands[k], p.max_levels, &shape, n)) continue;  // does not fit this batch
+        if (resolve_shape(&cands[k], p.max_levels, &shape, n, n)) continue;  // does not fit this batch
         for (int st = 0; st < kStages; ++st) {
             if (st < kStages - 1 && sizes[st] == sizes[st + 1]) continue;
             const BatchPlan &q = plans[st];
@@ -1057,7 +1075,7 @@ hv_batcher *hv_batcher_create(int64_t max_requests, int32_t max_indexes, int32_t
     int64_t limit[3] = {max_requests, max_requests, max_requests};
     int n_shapes = 0;
     if (launch) {
-        if (resolve_shape(launch, max_levels, &shape[0], max_requests)) return nullptr;
+        if (resolve_shape(launch, max_levels, &shape[0], max_requests, max_requests)) return nullptr;
         n_shapes = 1;
     } else {
         // the default's shape classes this batcher can meet: below 1024
@@ -1065,7 +1083,7 @@ hv_batcher *hv_batcher_create(int64_t max_requests, int32_t max_indexes, int32_t
         static const int64_t bounds[3] = {1023, 4095, int64_t(1) << 24};
         for (int k = 0; k < 3; ++k) {
             const int64_t hi = std::min(bounds[k], max_requests);
-            if (resolve_shape(nullptr, max_levels, &shape[n_shapes], hi)) return nullptr;
+            if (resolve_shape(nullptr, max_levels, &shape[n_shapes], hi, hi)) return nullptr;
             limit[n_shapes++] = hi;
             if (hi == max_requests) break;
         }
@@ -1139,6 +1157,7 @@ int hv_batcher_run(hv_batcher *b, const hv_request *reqs, int64_t n, uint8_t *ou
     hv::stage_host(b->w, p.table.data(), (int)p.table.size(), p.reqs.data(), n, out_masks, s.host);
     int k = 0;
     while (k + 1 < b->n_shapes && n > b->limit[k]) ++k;
+    while (k > 0 && b->shape[k].waves < default_waves(n, p.dense)) --k;  // (each graph runs any batch size)
     hipError_t e = hipGraphLaunch(s.exec[k], t_stream);
     if (e == hipSuccess) e = hipEventRecord(s.done, t_stream);
     if (e != hipSuccess) return hip_status(e, "hv_batcher_run");
@@ -1234,6 +1253,7 @@ int hv_render_batch_noalloc(const hv_request *reqs, int64_t n, uint8_t *out_mask
     hv::DevIndex table[HV_NOALLOC_MAX_INDEXES];
     const hv_index *owners[HV_NOALLOC_MAX_INDEXES];
     int n_ix = 0, max_levels = 0, dev = -1;
+    int64_t dense = 0;
     if (hipGetDevice(&dev) != hipSuccess) return hip_status(hipGetLastError(), "hipGetDevice");
     for (int64_t k = 0; k < n; ++k) {
         const hv_request &q = reqs[k];
@@ -1261,11 +1281,12 @@ int hv_render_batch_noalloc(const hv_request *reqs, int64_t n, uint8_t *out_mask
             if (q.index->a.levels > max_levels) max_levels = q.index->a.levels;
         }
         g_noalloc_reqs[k] = hv::DevReq{q.z, q.x, q.y, slot, q.r_px};
+        dense += is_dense(q.index->a.n, q.z);
     }
     hv_launch tuned;
     if (!launch && n > 0 && tuned_for_key(batch_key_in(reqs, n, g_noalloc_z, g_noalloc_r), &tuned)) launch = &tuned;
     hv::LaunchShape shape;
-    int rc = resolve_shape(launch, max_levels, &shape, n);
+    int rc = resolve_shape(launch, max_levels, &shape, n, dense);
     if (rc) return rc;
     if (n == 0) {
         t_err.clear();

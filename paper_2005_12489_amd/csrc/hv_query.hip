@@ -60,6 +60,17 @@ __device__ inline int wave_alloc(int *counter, uint64_t hm, int lane) {
     return base + (int)lanes_below(hm);
 }
 
+// threadIdx.x, opaque to the compiler: it otherwise computes everything that
+// depends on the lane alone before a kernel's loop over work items and keeps it
+// in registers (filling 99 VGPRs instead of 95, and 3.42 ms instead of 2.93 for
+// 4,096 requests over 2e8 edges; the region kernel 9 spilled registers instead
+// of 3).
+__device__ inline int own_thread() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
 // The frontier level holds at most kFrontier entries, every level below it at
 // most 64 (a level is pushed only when none of its entries remain).
 __host__ __device__ constexpr int stack_words(int levels) { return 64 * (levels > 0 ? levels : 1) + kFrontier; }
@@ -260,6 +271,9 @@ __global__ __launch_bounds__(256) void k_tile_frontier(DevBatch B, int rs, int c
         else B.list[atomicAdd(&B.hdr->counter, 1)] = (uint32_t)t;
     }
 }
+
+// Most workgroups of a launch with one for each region.
+constexpr int64_t kSpreadGrid = 1 << 20;
 
 // Writes the zero masks of the requests whose tile has no data within r
 // (listed by the tile-frontier kernel); workgroups take them in turn.
@@ -695,8 +709,11 @@ __device__ inline int region_cells(uint32_t rg) {
 }
 
 // A radius is looked at in the finest cells that give it at most kCellRho
-// cells and that the index has; below kCellMin they decide too little.
-constexpr double kCellRho = 15.0;
+// cells and that the index has; below kCellMin they decide too little.  (The
+// window holds up to 15.  Half of that settles nearly as many pixels with half
+// the rows to read: 10,000 requests over 1e9 points 5.5 ms, 5.8 at 10, 6.5 at 15;
+// the 2e8 edges 3.0 ms at each.)
+constexpr double kCellRho = 8.0;
 constexpr double kCellMin = 1.5;
 constexpr float kCellMargin = 1e-3f;  // cells: far above the cells' own 1e-6 and FP32 rounding here
 
@@ -757,27 +774,45 @@ __device__ __forceinline__ void settle_from_cells(const DevIndex &ix, const DevR
     const int xb = cx0 + (col << k) + half;
     const uint32_t sh = (uint32_t)xb & 31u;
     const uint32_t *at = cells + (int64_t)(xb >> 5) * stride + cy0 + half;
-    for (int row = wv * (64 / RS) + lane / RS; row < RS; row += nw * (64 / RS)) {
+    // four rows of pixels at a time share the window's masks and overlap their loads
+    constexpr int kRows = 4;
+    const int step = nw * (64 / RS);  // RS / step is 4, 8, 16, 32 or 64
+    for (int row = wv * (64 / RS) + lane / RS; row < RS; row += kRows * step) {
+        uint32_t in[kRows], near[kRows];
+#pragma unroll
+        for (int c = 0; c < kRows; ++c) in[c] = near[c] = 0;
         const uint32_t *p = at + ((j0 + row) << k);
-        uint32_t in = 0, near = 0;
-        for (int g = 0; g < groups; ++g) {
-            const u32x4 a = *reinterpret_cast<const u32x4 *>(p + 4 * g);
-            const u32x4 b = *reinterpret_cast<const u32x4 *>(p + 4 * g + stride);
+        const int64_t down = (int64_t)step << k;
+        for (int g = 0; g < groups; ++g, p += 4) {
+            u32x4 a[kRows], b[kRows];
+#pragma unroll
+            for (int c = 0; c < kRows; ++c) {
+                a[c] = *reinterpret_cast<const u32x4 *>(p + c * down);
+                b[c] = *reinterpret_cast<const u32x4 *>(p + c * down + stride);
+            }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const uint32_t w = __builtin_amdgcn_alignbit(b[q], a[q], sh);
-                in |= w & (uint32_t)__builtin_amdgcn_readlane((int)inner, 4 * g + q);
-                near |= w & (uint32_t)__builtin_amdgcn_readlane((int)outer, 4 * g + q);
+                const uint32_t mi = (uint32_t)__builtin_amdgcn_readlane((int)inner, 4 * g + q);
+                const uint32_t mo = (uint32_t)__builtin_amdgcn_readlane((int)outer, 4 * g + q);
+#pragma unroll
+                for (int c = 0; c < kRows; ++c) {
+                    const uint32_t w = __builtin_amdgcn_alignbit(b[c][q], a[c][q], sh);
+                    in[c] |= w & mi;
+                    near[c] |= w & mo;
+                }
             }
         }
-        if (ix.cell_gaps) near = 1;
-        const uint64_t lit = __ballot(in != 0), unlit = __ballot(near == 0);
-        // the wave's 64 pixels are 64 / RS rows of W words
-        if (lane < 2) {
-            const int r2 = W == 1 ? row + lane : row, wd = W == 1 ? 0 : lane;
-            const uint32_t l = (uint32_t)(lit >> (32 * lane)), d = (uint32_t)(unlit >> (32 * lane));
-            mask[r2 * W + wd] = l | d;
-            *reinterpret_cast<uint32_t *>(rows + r2 * 32 + 4 * wd) = d;
+#pragma unroll
+        for (int c = 0; c < kRows; ++c) {
+            if (ix.cell_gaps) near[c] = 1;
+            const uint64_t lit = __ballot(in[c] != 0), unlit = __ballot(near[c] == 0);
+            // the wave's 64 pixels are 64 / RS rows of W words
+            if (lane < 2) {
+                const int r2 = row + c * step + (W == 1 ? lane : 0), wd = W == 1 ? 0 : lane;
+                const uint32_t l = (uint32_t)(lit >> (32 * lane)), d = (uint32_t)(unlit >> (32 * lane));
+                mask[r2 * W + wd] = l | d;
+                *reinterpret_cast<uint32_t *>(rows + r2 * 32 + 4 * wd) = d;
+            }
         }
     }
 }
@@ -797,7 +832,7 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
     constexpr int W = RS / 32;   // mask words per region row
     constexpr int MW = RS * W;   // words of one mask
     constexpr int NM = AA ? 4 : 1;
-    const int tid = threadIdx.x, lane = tid & 63, nthr = blockDim.x;
+    const int tid = own_thread(), lane = tid & 63, nthr = blockDim.x;
     uint32_t *stk = L.stk;
     uint32_t *mask = L.mask;
     int *ctl = L.ctl;
@@ -1413,7 +1448,6 @@ bool in_one_launch(const LaunchShape &s) {
 // edges read.  A polygon (or a subtree) whose pixel centres in the region are
 // all filled already cannot change the OR and is skipped.
 constexpr int kFillGroup = 32;
-constexpr int64_t kFillGrid = 262144;  // default workgroups of a filling launch (at most one per region)
 
 struct FillLds {
     uint32_t *stk;
@@ -1500,7 +1534,7 @@ __device__ __forceinline__ void fill_query(const DevIndex &ix, const DevReq &rq,
                                            uint8_t *__restrict__ out, int cap, const FillLds &L) {
     constexpr int NR = 256 / RS;
     constexpr int W = RS / 32;
-    const int tid = threadIdx.x, lane = tid & 63, nthr = blockDim.x;
+    const int tid = own_thread(), lane = tid & 63, nthr = blockDim.x;
     uint32_t *stk = L.stk, *mask = L.mask, *par = L.par;
     int *ctl = L.ctl;
     const int rx = reg % NR, ry = reg / NR;
@@ -2120,11 +2154,14 @@ hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, 
                                       : ((256 / s.block) * (256 / s.block) + s.waves - 1) / s.waves;
     // (the item count per XCD is rounded up to whole tiles)
     const int64_t need = n_req * per_tile;
-    // filling's regions differ in cost by orders of magnitude (clusters of
-    // small polygons next to empty sea), so by default each gets its own
-    // workgroup and the dispatcher balances them; the distance kernels keep a
-    // persistent grid
-    int64_t grid = s.grid > 0 ? s.grid : s.fill ? kFillGrid : persistent_grid(s, max_levels);
+    // Filling's regions, and in large batches the distance kernel's, differ in
+    // cost by orders of magnitude (clusters next to empty sea, settled regions
+    // next to walked ones), so each gets its own workgroup and the dispatcher
+    // balances them: 10,000 requests over 1e9 points take 6.1 ms instead of 6.8
+    // with a persistent grid.  Smaller batches (more waves to a region) and
+    // anti-aliased ones keep that grid (10M segments 0.90 ms instead of 0.93).
+    const bool spread = s.fill || (s.region && !s.aa && s.waves == 1);
+    int64_t grid = s.grid > 0 ? s.grid : spread ? kSpreadGrid : persistent_grid(s, max_levels);
     if (grid > need) grid = need;
     const dim3 g((uint32_t)grid), b((uint32_t)(64 * s.waves));
     if (s.fill && s.region == 64) hipLaunchKernelGGL(k_fill_region<64>, g, b, lds, st, B, s.cand_cap, max_levels);
