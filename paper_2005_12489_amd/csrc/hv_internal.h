@@ -177,7 +177,7 @@ struct BatchHeader {
     int32_t ecounter;   // tiles with no data within r, listed for zero-filling (0 when staged)
     uint64_t t_start;   // wall clock when the batch started on the device
     int32_t leaf_tiles; // tiles for the object kernel: frontier at the leaves (0 when staged)
-    int32_t node_tiles; // and one level above (0 when staged)
+    int32_t node_tiles; // and above (0 when staged)
 };
 
 // Device addresses of one batch's workspace (a kernel argument).
@@ -232,12 +232,13 @@ size_t few_bytes(int64_t n_req);
 hipError_t launch_few(const DevIndex *ixs, int n_ix, const DevReq *reqs, int64_t n_req, uint8_t *out, unsigned char *dws,
                       int max_levels, const LaunchShape &s, hipStream_t st, hipEvent_t *marks);
 
-// The object kernel (hv_objects.h): tiles whose frontier lies at the leaves or
-// one level above, in strips of whole pixel rows, a workgroup to a strip.  More
+// The object kernel (hv_objects.h): tiles with few objects in reach, in strips
+// of whole pixel rows, a workgroup to a strip.  More
 // strips spread a tile's objects over more workgroups, and each reads the
 // frontier anew.
 constexpr int kLeafStrips = 4;         // up to 4,096 objects in reach
-constexpr int kNodeStrips = 16;        // up to 65,536
+constexpr int kNodeStrips = 16;        // up to 65,536, or 262,144
+constexpr int kObjectUpper = 64;       // most level-2 nodes of a tile taken object by object
 constexpr int kStripRows = 64;         // most rows of a strip
 constexpr int64_t kObjectsGrid = 4096;
 

@@ -1,7 +1,8 @@
 // Tiles with few objects in reach, object by object.
 //
-// Where a tile's frontier (k_tile_frontier) lies at the leaves or one level
-// above them, at most 65,536 objects can reach the tile, and walking the tree
+// Where a tile's frontier (k_tile_frontier) lies at the leaves, one level above
+// them or, without cells to settle it, two levels above with few nodes
+// (by_objects), at most 262,144 objects can reach the tile, and walking the tree
 // for each of its regions would test the same nodes and read the same leaves
 // over and over, a memory latency at a time.  Here a workgroup takes a strip
 // of the tile -- whole pixel rows, so that the mask is written in whole lines --
@@ -41,7 +42,8 @@ struct StripLds {
     Staged w[kStripThreads / 64];
     uint32_t mask[(AA ? 4 : 1) * kStripRows * 8];  // sub-sample m at m * kStripRows * 8
     uint32_t nodes[kFrontier], leaves[kFrontier];
-    int n_nodes, n_leaves;
+    uint32_t upper[kObjectUpper];  // a level-2 frontier's nodes
+    int n_nodes, n_leaves, n_upper;
 };
 
 // Lights columns c0 .. c1 of a mask row.
@@ -73,7 +75,7 @@ __device__ __forceinline__ void strip(const DevIndex &ix, const DevReq &rq, int6
     const float ylo = xlo - (float)j0, yhi = xhi - (float)j0, last = (float)(rows - 1);
 
     for (int k = tid; k < NM * MW; k += kStripThreads) L.mask[k] = 0;
-    if (tid == 0) L.n_nodes = 0;
+    if (tid == 0) L.n_nodes = L.n_upper = 0;
     __syncthreads();
     auto meets = [&](const double4 &b) { return b.x <= qx1 && b.z >= qx0 && b.y <= qy1 && b.w >= qy0; };
     {
@@ -83,12 +85,11 @@ __device__ __forceinline__ void strip(const DevIndex &ix, const DevReq &rq, int6
             node = frontier[t * kFrontier + tid];
             hit = meets(ix.nodes[ix.meta[flevel] + node]);
         }
-        uint32_t *const to = flevel ? L.nodes : L.leaves;
-        const int pos = wave_alloc(&L.n_nodes, __ballot(hit), lane);
+        uint32_t *const to = flevel == 2 ? L.upper : flevel ? L.nodes : L.leaves;
+        const int pos = wave_alloc(flevel == 2 ? &L.n_upper : &L.n_nodes, __ballot(hit), lane);
         if (hit) to[pos] = node;
     }
     __syncthreads();
-    const int n_nodes = L.n_nodes;
 
     // exact FP64 squared distance from a sample (tile-local px) to object c
     auto dist2 = [&](const double2 &a, const double2 &d, double inv, double px, double py) -> double {
@@ -306,26 +307,38 @@ __device__ __forceinline__ void strip(const DevIndex &ix, const DevReq &rq, int6
             __builtin_amdgcn_wave_barrier();
         }
     };
+    // The children (of level `lvl`) that meet the strip of up to
+    // kStripThreads / kFan nodes at a time.
+    auto expand = [&](const uint32_t *nodes, int base, int n, int lvl, uint32_t *to, int *count) {
+        if (tid == 0) *count = 0;
+        __syncthreads();
+        const int k = base + tid / kFan;
+        bool hit = false;
+        int64_t child = 0;
+        if (k < n) {
+            child = (int64_t)nodes[k] * kFan + tid % kFan;
+            hit = child < ix.meta[kMaxLevels + lvl] && meets(ix.nodes[ix.meta[lvl] + child]);
+        }
+        const int pos = wave_alloc(count, __ballot(hit), lane);
+        if (hit) to[pos] = (uint32_t)child;
+        __syncthreads();
+    };
+    constexpr int kStep = kStripThreads / kFan;
     if (flevel == 0) {
-        take_leaves(n_nodes);
+        take_leaves(L.n_nodes);
     } else {
-        // the leaves below kStripThreads / kFan nodes at a time
-        const int64_t count = ix.meta[kMaxLevels], off = ix.meta[0];
-        for (int base = 0; base < n_nodes; base += kStripThreads / kFan) {
-            if (tid == 0) L.n_leaves = 0;
-            __syncthreads();
-            const int k = base + tid / kFan;
-            bool hit = false;
-            int64_t leaf = 0;
-            if (k < n_nodes) {
-                leaf = (int64_t)L.nodes[k] * kFan + tid % kFan;
-                hit = leaf < count && meets(ix.nodes[off + leaf]);
+        for (int up = 0;; up += kStep) {
+            if (flevel == 2) {
+                if (up >= L.n_upper) break;
+                expand(L.upper, up, L.n_upper, 1, L.nodes, &L.n_nodes);
             }
-            const int pos = wave_alloc(&L.n_leaves, __ballot(hit), lane);
-            if (hit) L.leaves[pos] = (uint32_t)leaf;
-            __syncthreads();
-            take_leaves(L.n_leaves);
-            __syncthreads();
+            const int n_nodes = L.n_nodes;
+            for (int base = 0; base < n_nodes; base += kStep) {
+                expand(L.nodes, base, n_nodes, 0, L.leaves, &L.n_leaves);
+                take_leaves(L.n_leaves);
+                __syncthreads();
+            }
+            if (flevel != 2) break;
         }
     }
     __syncthreads();
@@ -350,7 +363,7 @@ __device__ __forceinline__ void strip(const DevIndex &ix, const DevReq &rq, int6
 }
 
 // The object kernel's work items: the strips of the tiles whose frontier lies
-// one level above the leaves first, then of those with a frontier of leaves.
+// above the leaves first, then of those with a frontier of leaves.
 __device__ inline int64_t object_items(const DevBatch &B, int leaf_strips, int node_strips) {
     return (int64_t)B.hdr->node_tiles * node_strips + (int64_t)B.hdr->leaf_tiles * leaf_strips;
 }

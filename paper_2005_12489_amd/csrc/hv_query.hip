@@ -240,8 +240,39 @@ __device__ __forceinline__ Frontier frontier_walk(const DevIndex &ix, const DevR
     return Frontier{cur, ncur, lvl, cbits};
 }
 
-// objects: tiles whose frontier lies at level 0 or 1 go to the object kernel's
-// lists, not to the region kernel's.
+// A radius is looked at in the finest cells that give it at most kCellRho
+// cells and that the index has; below kCellMin they decide too little.  (The
+// window holds up to 15.  Half of that settles nearly as many pixels with half
+// the rows to read: 10,000 requests over 1e9 points 5.5 ms, 5.8 at 10, 6.5 at 15;
+// the 2e8 edges 3.0 ms at each.)
+constexpr double kCellRho = 8.0;
+constexpr double kCellMin = 1.5;
+constexpr float kCellMargin = 1e-3f;  // cells: far above the cells' own 1e-6 and FP32 rounding here
+
+// The level whose occupancy cells settle pixels of zoom z at radius r, as a
+// shift k >= 0 from z (cells are 2^-k px), or -1.
+__device__ inline int cell_shift(const DevIndex &ix, int z, double r) {
+    if (ix.cell_top < z) return -1;
+    const int k = min(ix.cell_top - z, ilogb(kCellRho / r));
+    return k >= 0 && ldexp(r, k) >= kCellMin ? k : -1;
+}
+
+// Whether a tile is taken object by object (hv_objects.h): its frontier lies at
+// level 0 or 1, or has few nodes at level 2 (65,536 to 262,144 objects in reach)
+// where the region kernel would read nearly every object anyway: segments at a
+// radius too small for its accepts, with no cells to settle the tile's pixels
+// first (cells: whether the query looks at them at all).  4,096 tiles of 10M
+// segments at r = 1/2: 0.40 -> 0.31 ms.  Points and larger radii are the other
+// way round (61 mixed requests 0.10 -> 0.19 ms): accepts light most pixels of
+// such a tile from its inner nodes.
+constexpr double kObjectsRadius = 1.0;
+__device__ inline bool by_objects(const DevIndex &ix, const DevReq &rq, int n, int level, bool cells) {
+    return level < 2 || (level == 2 && n <= kObjectUpper && ix.seg && rq.r < kObjectsRadius &&
+                         !(cells && cell_shift(ix, rq.z, rq.r) >= 0));
+}
+
+// objects: tiles by_objects() go to the object kernel's lists, not to the region
+// kernel's.
 template <int WPT>
 __global__ __launch_bounds__(256) void k_tile_frontier(DevBatch B, int rs, int cull, double grow, int objects) {
     static_assert(4 % WPT == 0, "a workgroup is four wavefronts");
@@ -267,7 +298,7 @@ __global__ __launch_bounds__(256) void k_tile_frontier(DevBatch B, int rs, int c
         reinterpret_cast<int4 *>(B.fmeta)[t] = make_int4(f.n, f.level, (int)(uint32_t)f.regions, (int)(uint32_t)(f.regions >> 32));
         B.done[t] = 0;
         if (objects && f.level == 0) B.list[n_req - 1 - atomicAdd(&B.hdr->leaf_tiles, 1)] = (uint32_t)t;
-        else if (objects && f.level == 1) B.elist[n_req - 1 - atomicAdd(&B.hdr->node_tiles, 1)] = (uint32_t)t;
+        else if (objects && by_objects(ix, rq, f.n, f.level, grow == 0.0)) B.elist[n_req - 1 - atomicAdd(&B.hdr->node_tiles, 1)] = (uint32_t)t;
         else B.list[atomicAdd(&B.hdr->counter, 1)] = (uint32_t)t;
     }
 }
@@ -706,23 +737,6 @@ __device__ inline bool range_lit(const uint32_t *mask, int ilo, int ihi, int jlo
 __device__ inline int region_cells(uint32_t rg) {
     const int ilo = rg & 63, ihi = (rg >> 6) & 63, jlo = (rg >> 12) & 63, jhi = (rg >> 18) & 63;
     return (jhi - jlo + 1) * ((ihi >> 3) - (ilo >> 3) + 1);
-}
-
-// A radius is looked at in the finest cells that give it at most kCellRho
-// cells and that the index has; below kCellMin they decide too little.  (The
-// window holds up to 15.  Half of that settles nearly as many pixels with half
-// the rows to read: 10,000 requests over 1e9 points 5.5 ms, 5.8 at 10, 6.5 at 15;
-// the 2e8 edges 3.0 ms at each.)
-constexpr double kCellRho = 8.0;
-constexpr double kCellMin = 1.5;
-constexpr float kCellMargin = 1e-3f;  // cells: far above the cells' own 1e-6 and FP32 rounding here
-
-// The level whose occupancy cells settle pixels of zoom z at radius r, as a
-// shift k >= 0 from z (cells are 2^-k px), or -1.
-__device__ inline int cell_shift(const DevIndex &ix, int z, double r) {
-    if (ix.cell_top < z) return -1;
-    const int k = min(ix.cell_top - z, ilogb(kCellRho / r));
-    return k >= 0 && ldexp(r, k) >= kCellMin ? k : -1;
 }
 
 // Settles the pixels of a region from the occupancy cells 2^-k px wide: lit
@@ -1977,7 +1991,7 @@ __global__ __launch_bounds__(kStripThreads) __attribute__((amdgpu_waves_per_eu(4
         if (part < 4) zero_part(A.out + (int64_t)t * kBytes, kBytes, part, 4);
         return;
     }
-    if (fm.y > 1) {
+    if (!by_objects(ix, rq, fm.x, fm.y, !AA)) {
         const RegionLds L = region_lds<kBothRegion, kBothOpl, AA>(reinterpret_cast<unsigned char *>(smem), cap, max_levels);
         if (ix.seg) region_query<kBothRegion, 1, kBothOpl, AA>(ix, rq, t, part, A.frontier, A.fmeta, A.out, cap, L);
         else region_query<kBothRegion, 0, kBothOpl, AA>(ix, rq, t, part, A.frontier, A.fmeta, A.out, cap, L);

@@ -1,6 +1,7 @@
-"""The object kernel -- tiles whose frontier lies at the leaves or one level
-above -- against the oracle: strip and word edges, wide and flat segments, the
-switch to a level-1 frontier, small and large batches."""
+"""The object kernel -- tiles whose frontier lies at the leaves or up to two
+levels above -- against the oracle: strip and word edges, wide and flat
+segments, the switches to a level-1 and a level-2 frontier, small and large
+batches."""
 import numpy as np
 import pytest
 
@@ -48,13 +49,13 @@ TILES = np.array([[Z, TX, TY], [Z, TX + 1, TY], [Z + 1, 2 * TX + 1, 2 * TY], [Z 
 
 
 @pytest.mark.parametrize("kind", [0, 1])
-@pytest.mark.parametrize("n", [1, 17, 250, 4096, 4200, 30_000])
+@pytest.mark.parametrize("n", [1, 17, 250, 4096, 4200, 30_000, 120_000])
 def test_masks(hv, torch, kind, n):
     obj = objects(kind, n, 7 * n + kind)
     ref = oracle.OracleIndex(obj, kind, merc01=True)
     log(f"objects kind={kind} n={n}")
     h = build(hv, torch, obj, kind | hv.HV_INPUT_MERC01)
-    for r in (0.3, 1.0, 2.5) + ((20.0, 64.0) if n <= 250 else ()):
+    for r in (0.3, 1.0, 2.5) + ((20.0, 64.0) if n <= 250 else ()) if n < 100_000 else (0.3, 0.9):
         tri = ref.render(TILES, r)["tri"]
         for L in (None, dict(region=32, waves_per_wg=1, objs_per_lane=2, cand_cap=128)):
             log(f"  r={r} launch={L}")
@@ -79,12 +80,12 @@ def test_batch_sizes(hv, torch, requests):
 
 
 @pytest.mark.parametrize("kind", [0, 1])
-@pytest.mark.parametrize("n", [17, 6000])
+@pytest.mark.parametrize("n", [17, 6000, 120_000])
 def test_anti_aliased(hv, torch, kind, n):
     obj = objects(kind, n, n + kind)
     ref = oracle.OracleIndex(obj, kind, merc01=True)
     h = build(hv, torch, obj, kind | hv.HV_INPUT_MERC01)
-    for r in (0.5, 2.0) + ((30.0,) if n < 100 else ()):
+    for r in (0.5, 2.0) + ((30.0,) if n < 100 else ()) if n < 100_000 else (0.5,):
         log(f"aa objects kind={kind} n={n} r={r}")
         got = render_aa(hv, torch, h, TILES, r, {"region": 32, "objs_per_lane": 2, "aa_split": -1})
         check_aa(got, ref.render_aa(TILES, r), f"objects kind={kind} n={n} r={r}")
