@@ -1499,7 +1499,7 @@ __host__ __device__ inline size_t fill_lds_bytes(int cap, int levels, int thread
 // four cells and any of them decides; at zoom `top` and beyond it lies within
 // one.  `mask` gets the settled pixels, the words at rows + 32 j those of its
 // row j that are outside.
-constexpr int kFillShift = 4;
+constexpr int kFillShift = 3;
 
 template <int RS>
 __device__ __forceinline__ void settle_fill(const DevIndex &ix, const DevReq &rq, int i0, int j0, uint32_t *mask,
@@ -1507,14 +1507,13 @@ __device__ __forceinline__ void settle_fill(const DevIndex &ix, const DevReq &rq
     constexpr int W = RS / 32;
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2), aligned(4)));
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    const int k = min(ix.cell_top - rq.z, kFillShift), level = rq.z + k;
-    const int64_t stride = cell_stride(level);
-    const uint32_t *in = ix.cells + cell_level_words(level) + cell_origin(level);
-    const uint32_t *near = in + cell_level_words(ix.cell_top + 1);
     const int gx = (rq.x << 8) + i0 + lane % RS;  // pixel, world
-    for (int row = wv * (64 / RS) + lane / RS; row < RS; row += nw * (64 / RS)) {
-        const int gy = (rq.y << 8) + j0 + row;
-        bool inside, outside;
+    const int64_t words = cell_level_words(ix.cell_top + 1);
+    // a look at the cells 2^-k px wide
+    auto look = [&](int k, int gy, bool &inside, bool &outside) {
+        const int level = rq.z + k;
+        const int64_t stride = cell_stride(level);
+        const uint32_t *in = ix.cells + cell_level_words(level) + cell_origin(level), *near = in + words;
         if (k > 0) {
             const int cx = (gx << k) + (1 << k >> 1) - 1, cy = (gy << k) + (1 << k >> 1) - 1;  // the upper left cell
             const int64_t at = (cx >> 5) * stride + cy;
@@ -1530,6 +1529,13 @@ __device__ __forceinline__ void settle_fill(const DevIndex &ix, const DevReq &rq
             inside = (in[at] >> (cx & 31)) & 1u;
             outside = !((near[at] >> (cx & 31)) & 1u);
         }
+    };
+    const int most = ix.cell_top - rq.z, k = min(most, kFillShift);
+    for (int row = wv * (64 / RS) + lane / RS; row < RS; row += nw * (64 / RS)) {
+        const int gy = (rq.y << 8) + j0 + row;
+        bool inside, outside;
+        look(k, gy, inside, outside);
+        if (k < most && !inside && !outside) look(most, gy, inside, outside);
         if (ix.cell_gaps) outside = false;
         const uint64_t lit = __ballot(inside), unlit = __ballot(outside);
         // the wave's 64 pixels are 64 / RS rows of W words
