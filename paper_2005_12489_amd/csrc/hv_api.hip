@@ -184,10 +184,11 @@ int run_batch(const hv::DevIndex *ixs, int n_ix, int max_levels, const hv::DevRe
               HostStage &st = t_stage) {
     if (hv::few_requests(shape, n_req, n_ix)) {
         unsigned char *dws = nullptr;
-        hipError_t e = hipMallocAsync((void **)&dws, hv::few_bytes(n_req), t_stream);
+        const size_t bytes = hv::few_bytes(shape, n_req);
+        hipError_t e = bytes ? hipMallocAsync((void **)&dws, bytes, t_stream) : hipSuccess;
         if (e != hipSuccess) return hip_status(e, who);
         e = hv::launch_few(ixs, n_ix, reqs, n_req, out, dws, max_levels, shape, t_stream, marks);
-        const hipError_t ef = hipFreeAsync(dws, t_stream);
+        const hipError_t ef = dws ? hipFreeAsync(dws, t_stream) : hipSuccess;
         if (e != hipSuccess) return hip_status(e, who);
         if (ef != hipSuccess) return hip_status(ef, who);
         return HV_OK;

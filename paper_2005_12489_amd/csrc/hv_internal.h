@@ -225,10 +225,11 @@ hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, 
 // Batches that travel in the kernels' arguments: this many requests over this
 // many indexes, in the default shape or filling.
 constexpr int kFewRequests = 64, kFewIndexes = 4;
+constexpr int kSelfRequests = 16;      // up to this many walk for their frontier in every workgroup
 bool few_requests(const LaunchShape &s, int64_t n_req, int n_ix);
-// Device bytes that launch_few needs at dws, and the launch itself (marks as for
-// launch_query).
-size_t few_bytes(int64_t n_req);
+// Device bytes that launch_few needs at dws (0: none), and the launch itself
+// (marks as for launch_query).
+size_t few_bytes(const LaunchShape &s, int64_t n_req);
 hipError_t launch_few(const DevIndex *ixs, int n_ix, const DevReq *reqs, int64_t n_req, uint8_t *out, unsigned char *dws,
                       int max_levels, const LaunchShape &s, hipStream_t st, hipEvent_t *marks);
 

@@ -33,6 +33,7 @@
 #include <algorithm>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 
 #include "hv_internal.h"
 
@@ -1941,12 +1942,15 @@ __global__ __launch_bounds__(256) void k_fill_region(DevBatch B, int cap, int ma
     }
 }
 
+constexpr int kSelfFillWaves = 2;  // filling's default shape
+
 // ------------------------------------------------------------ small batches
 // A batch of at most kFewRequests requests travels in the kernels' arguments:
 // no staging copy, and no lists or counters to clear -- every request has as
 // many workgroups as the kind of tile with the most parts, and those without a
 // part end at once.  (One tile of 10k points: 5 us of copy before 17 us of
-// kernels, and a third of the call's host time.)
+// kernels, and a third of the call's host time.)  Up to kSelfRequests requests
+// need no memory and no second launch either.
 struct FewBatch {
     uint8_t *out;
     uint32_t *frontier;  // per request: up to 256 frontier nodes
@@ -1983,49 +1987,80 @@ __device__ inline void zero_part(uint8_t *tile, int tile_bytes, int part, int pa
     for (int k = threadIdx.x; k < n; k += blockDim.x) m4[part * n + k] = make_uint4(0, 0, 0, 0);
 }
 
-template <int AA>
+// A tile's frontier as the query kernels read it: from memory, where
+// k_few_frontier left it, or, for so few requests that the second launch and the
+// memory cost more than every workgroup walking for itself (SELF), from LDS.
+struct FewFrontier {
+    const uint32_t *nodes;
+    const int32_t *meta;
+};
+
+struct SelfLds {
+    FrontierLds walk;
+    int4 meta;
+};
+
+template <bool SELF, int WPT, class Lds>
+__device__ __forceinline__ FewFrontier few_frontier(const FewBatch &A, const DevIndex &ix, const DevReq &rq, int t, Lds *self) {
+    if constexpr (SELF) {
+        const int tid = threadIdx.x;
+        const Frontier f = frontier_walk<WPT>(ix, rq, A.rs, A.cull, A.grow, tid, self->walk);
+        if (tid == 0) self->meta = make_int4(f.n, f.level, (int)(uint32_t)f.regions, (int)(uint32_t)(f.regions >> 32));
+        __syncthreads();
+        return FewFrontier{f.nodes, reinterpret_cast<const int32_t *>(&self->meta)};
+    } else {
+        return FewFrontier{A.frontier + t * kFrontier, A.fmeta + 4 * t};
+    }
+}
+
+template <int AA, bool SELF>
 __global__ __launch_bounds__(kStripThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_few_query(FewBatch, int cap, int max_levels) {
     extern __shared__ double4 smem[];
+    __shared__ typename std::conditional<SELF, SelfLds, int>::type self;  // (an int nothing uses takes no LDS)
     constexpr int RPT = (256 / kBothRegion) * (256 / kBothRegion);
+    constexpr int kBytes = AA ? HV_AA_BYTES : HV_MASK_BYTES;
     const FewBatch &A = few_batch();
     const int t = blockIdx.x / RPT, part = blockIdx.x % RPT;
-    const int4 fm = reinterpret_cast<const int4 *>(A.fmeta)[t];
     const DevReq rq = A.reqs[t];
     const DevIndex ix = A.ixs[rq.index];
-    if (fm.x == 0) {
-        constexpr int kBytes = AA ? HV_AA_BYTES : HV_MASK_BYTES;
-        if (part < 4) zero_part(A.out + (int64_t)t * kBytes, kBytes, part, 4);
+    const FewFrontier f = few_frontier<SELF, kBothWaves>(A, ix, rq, t, &self);
+    const int count = f.meta[0], level = f.meta[1];
+    uint8_t *const out = A.out + (int64_t)t * kBytes;
+    if (count == 0) {
+        if (part < 4) zero_part(out, kBytes, part, 4);
         return;
     }
-    if (!by_objects(ix, rq, fm.x, fm.y, !AA)) {
+    if (!by_objects(ix, rq, count, level, !AA)) {
         const RegionLds L = region_lds<kBothRegion, kBothOpl, AA>(reinterpret_cast<unsigned char *>(smem), cap, max_levels);
-        if (ix.seg) region_query<kBothRegion, 1, kBothOpl, AA>(ix, rq, t, part, A.frontier, A.fmeta, A.out, cap, L);
-        else region_query<kBothRegion, 0, kBothOpl, AA>(ix, rq, t, part, A.frontier, A.fmeta, A.out, cap, L);
+        if (ix.seg) region_query<kBothRegion, 1, kBothOpl, AA>(ix, rq, 0, part, f.nodes, f.meta, out, cap, L);
+        else region_query<kBothRegion, 0, kBothOpl, AA>(ix, rq, 0, part, f.nodes, f.meta, out, cap, L);
         return;
     }
-    const int strips = 2 * (fm.y ? kNodeStrips : kLeafStrips);
+    const int strips = 2 * (level ? kNodeStrips : kLeafStrips);
     if (part >= strips) return;
     const int rows = 256 / strips, j0 = part * rows;
     StripLds<AA> &L = *reinterpret_cast<StripLds<AA> *>(smem);
-    if (ix.seg) strip<1, AA>(ix, rq, t, fm.x, fm.y, j0, rows, A.frontier, A.out, L);
-    else strip<0, AA>(ix, rq, t, fm.x, fm.y, j0, rows, A.frontier, A.out, L);
+    if (ix.seg) strip<1, AA>(ix, rq, 0, count, level, j0, rows, f.nodes, out, L);
+    else strip<0, AA>(ix, rq, 0, count, level, j0, rows, f.nodes, out, L);
 }
 
-template <int RS>
-__global__ __launch_bounds__(256) void k_few_fill(FewBatch, int cap, int max_levels) {
+template <int RS, bool SELF>
+__global__ __launch_bounds__(SELF ? 64 * kSelfFillWaves : 256) void k_few_fill(FewBatch, int cap, int max_levels) {
     extern __shared__ double4 smem[];
+    __shared__ typename std::conditional<SELF, SelfLds, int>::type self;  // (an int nothing uses takes no LDS)
     constexpr int RPT = (256 / RS) * (256 / RS);
     const FewBatch &A = few_batch();
     const int t = blockIdx.x / RPT, part = blockIdx.x % RPT;
-    const int4 fm = reinterpret_cast<const int4 *>(A.fmeta)[t];
-    if (fm.x == 0) {
-        zero_part(A.out + (int64_t)t * HV_MASK_BYTES, HV_MASK_BYTES, part, RPT);
+    const DevReq rq = A.reqs[t];
+    const DevIndex ix = A.ixs[rq.index];
+    const FewFrontier f = few_frontier<SELF, kSelfFillWaves>(A, ix, rq, t, &self);
+    uint8_t *const out = A.out + (int64_t)t * HV_MASK_BYTES;
+    if (f.meta[0] == 0) {
+        zero_part(out, HV_MASK_BYTES, part, RPT);
         return;
     }
     const FillLds L = fill_lds<RS>(reinterpret_cast<unsigned char *>(smem), cap, max_levels);
-    const DevReq rq = A.reqs[t];
-    const DevIndex ix = A.ixs[rq.index];
-    fill_query<RS>(ix, rq, t, part, A.frontier, A.fmeta, A.out, cap, L);
+    fill_query<RS>(ix, rq, 0, part, f.nodes, f.meta, out, cap, L);
 }
 
 // Batches of up to this many requests take four wavefronts to a request's frontier.
@@ -2199,7 +2234,14 @@ bool few_requests(const LaunchShape &s, int64_t n_req, int n_ix) {
     return n_req <= kFewRequests && n_ix <= kFewIndexes && (s.fill || in_one_launch(s));
 }
 
-size_t few_bytes(int64_t n_req) { return (size_t)n_req * (sizeof(uint32_t) * kFrontier + sizeof(int32_t) * 4); }
+// Whether every workgroup walks for its tile's frontier itself.
+static bool self_frontier(const LaunchShape &s, int64_t n_req) {
+    return n_req <= kSelfRequests && s.cand_cap <= 512 && (!s.fill || (s.waves == kSelfFillWaves && s.region == 32));
+}
+
+size_t few_bytes(const LaunchShape &s, int64_t n_req) {
+    return self_frontier(s, n_req) ? 0 : (size_t)n_req * (sizeof(uint32_t) * kFrontier + sizeof(int32_t) * 4);
+}
 
 hipError_t launch_few(const DevIndex *ixs, int n_ix, const DevReq *reqs, int64_t n_req, uint8_t *out, unsigned char *dws,
                       int max_levels, const LaunchShape &s, hipStream_t st, hipEvent_t *marks) {
@@ -2214,14 +2256,16 @@ hipError_t launch_few(const DevIndex *ixs, int n_ix, const DevReq *reqs, int64_t
     memcpy(A.reqs, reqs, sizeof(DevReq) * (size_t)n_req);
     hipError_t e;
     if (marks && (e = hipEventRecord(marks[0], st)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_few_frontier, dim3((uint32_t)n_req), dim3(256), 0, st, A);
+    const bool self = self_frontier(s, n_req);
+    if (!self) hipLaunchKernelGGL(k_few_frontier, dim3((uint32_t)n_req), dim3(256), 0, st, A);
     if (marks && (e = hipEventRecord(marks[1], st)) != hipSuccess) return e;
     const size_t lds = query_lds_bytes(s, max_levels);
     const dim3 g((uint32_t)(n_req * (256 / s.region) * (256 / s.region))), b((uint32_t)(64 * s.waves));
-    if (s.fill && s.region == 64) hipLaunchKernelGGL(k_few_fill<64>, g, b, lds, st, A, s.cand_cap, max_levels);
-    else if (s.fill) hipLaunchKernelGGL(k_few_fill<32>, g, b, lds, st, A, s.cand_cap, max_levels);
-    else if (s.aa) hipLaunchKernelGGL(k_few_query<1>, g, b, lds, st, A, s.cand_cap, max_levels);
-    else hipLaunchKernelGGL(k_few_query<0>, g, b, lds, st, A, s.cand_cap, max_levels);
+    void (*const kernel)(FewBatch, int, int) =
+        s.fill ? (self ? k_few_fill<32, true> : s.region == 64 ? k_few_fill<64, false> : k_few_fill<32, false>)
+        : s.aa ? (self ? k_few_query<1, true> : k_few_query<1, false>)
+               : (self ? k_few_query<0, true> : k_few_query<0, false>);
+    hipLaunchKernelGGL(kernel, g, b, lds, st, A, s.cand_cap, max_levels);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (marks && (e = hipEventRecord(marks[2], st)) != hipSuccess) return e;
     return hipSuccess;
