@@ -72,6 +72,40 @@ __device__ inline void mark_row(const Line &l, int r, int g, int64_t stride, uin
     }
 }
 
+// A wave's lines, and pairs (lane | row - r0 << 6) of the rows they touch.
+constexpr int kUnits = 256;
+struct WaveLines {
+    double x0[64], y0[64], x1[64], y1[64], slope[64];
+    int r0[64], r1[64];
+    uint16_t units[kUnits];
+};
+
+// Marks the rows of the wave's lines (rows = 0: none), dealt over its lanes: a
+// lane per line waits for the longest of 64 (10M segments 0.38 ms).
+__device__ inline void mark_rows(const Line &l, int rows, int g, int64_t stride, uint32_t *base, WaveLines &w, int lane) {
+    w.x0[lane] = l.x0, w.y0[lane] = l.y0, w.x1[lane] = l.x1, w.y1[lane] = l.y1, w.slope[lane] = l.slope;
+    w.r0[lane] = l.r0, w.r1[lane] = l.r1;
+    int first = 0, total = 0;
+#pragma unroll
+    for (int b = 0; (1 << b) <= kLongCells; ++b) {
+        const uint64_t m = __ballot((rows >> b) & 1);
+        first += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)) << b;
+        total += __popcll(m) << b;
+    }
+    for (int u0 = 0; u0 < total; u0 += kUnits) {
+        __builtin_amdgcn_wave_barrier();
+        for (int k = max(u0 - first, 0); k < rows && first + k - u0 < kUnits; ++k)
+            w.units[first + k - u0] = (uint16_t)(lane | k << 6);
+        __builtin_amdgcn_wave_barrier();
+        for (int u = lane; u < min(total - u0, kUnits); u += 64) {
+            const int e = w.units[u], c = e & 63;
+            const Line q{w.x0[c], w.y0[c], w.x1[c], w.y1[c], w.slope[c], w.r0[c], w.r1[c]};
+            mark_row(q, q.r0 + (e >> 6), g, stride, base);
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
 // A workgroup takes kMarkChunk objects in the tree's (Hilbert) order, in which
 // the objects of one block of cells, a block's side being a power of two,
 // follow each other: it marks them in LDS block by block and writes out the
@@ -83,8 +117,9 @@ __global__ __launch_bounds__(256) void k_cells_mark(const double *__restrict__ o
     constexpr int H = W == 2 ? 0 : kHalo, HW = W == 2 ? 0 : 1;
     constexpr int kRows = kBlock + 2 * H, kCols = kBlock / 32 + 2 * HW;
     __shared__ uint32_t lds[kRows * kCols];
+    __shared__ WaveLines wave[W == 2 ? 1 : 4];
     __shared__ unsigned long long found[3];  // long segments, their cells, their first slot in the list
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int g = 256 << level;
     const int64_t stride = cell_stride(level);
     uint32_t *const base = cells + cell_level_words(level) + cell_origin(level);
@@ -113,6 +148,8 @@ __global__ __launch_bounds__(256) void k_cells_mark(const double *__restrict__ o
             const int64_t i = p + tid;
             const bool mine = i < end && block_of(i) == blk;
             unsigned long long slot = ~0ull;
+            Line line;
+            int rows = 0;
             if (mine) {
                 bool in = true;
 #pragma unroll
@@ -129,10 +166,12 @@ __global__ __launch_bounds__(256) void k_cells_mark(const double *__restrict__ o
                         slot = atomicAdd(&found[0], 1ull);
                         atomicAdd(&found[1], (unsigned long long)count);
                     } else {
-                        for (int r = l.r0; r <= l.r1; ++r) mark_row(l, r, g, kRows, at);
+                        line = l;
+                        rows = l.r1 - l.r0 + 1;
                     }
                 }
             }
+            if constexpr (W == 4) mark_rows(line, rows, g, kRows, at, wave[tid >> 6], lane);
             const int took = __syncthreads_count(mine);
             if (W == 4 && found[0]) {
                 if (tid == 0) {
