@@ -945,10 +945,71 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
     };
     const bool promising = push_frontier();
 
+    // A queued point's rows, one after another in a lane (points of one radius
+    // have about as many), or dealt over as many lanes as a short queue leaves
+    // idle.  The samples of a row within r are those within h of the point's
+    // column: FP32 knows h and the column to 4e-5 px for r up to 64, so columns
+    // 1e-4 px inside are lit, columns as far outside are not, and the FP64
+    // distance decides the few between.  (That margin is 4e-9 px^2 of squared
+    // distance at the least, a thousand times what FP64 rounds.)
+    auto drain_points = [&](int nq) {
+        int g = 0;
+        while (g < 3 && (nq << (g + 1)) <= nthr) ++g;
+        for (int q = tid >> g; q < nq; q += nthr >> g) {
+            const double2 a = L.ca[q];
+            const uint32_t rg = L.crng[q];
+            const int ilo = rg & 63, ihi = (rg >> 6) & 63, jhi = (rg >> 18) & 63;
+            const uint64_t want = ((2ull << (ihi - ilo)) - 1ull) << ilo;
+            for (int jj = (int)((rg >> 12) & 63) + (tid & ((1 << g) - 1)); jj <= jhi; jj += 1 << g) {
+#pragma unroll
+                for (int sy = 0; sy < (AA ? 2 : 1); ++sy) {
+                    const double wy = j0 + (double)jj + (AA ? (sy ? 0.75 : 0.25) : 0.5) - a.y;
+                    const double rn = r2 - wy * wy;
+                    if (rn < -1e-9) continue;
+                    const float h = __builtin_amdgcn_sqrtf(fmaxf((float)rn, 0.0f));
+#pragma unroll
+                    for (int sx = 0; sx < (AA ? 2 : 1); ++sx) {
+                        const int mm = AA ? 2 * sy + sx : 0;
+                        uint64_t todo = want;
+#pragma unroll
+                        for (int wd = 0; wd < W; ++wd)
+                            todo &= ~((uint64_t)mask[mm * MW + jj * W + wd] << (32 * wd));
+                        if (!todo) continue;
+                        // sample x of region column 0
+                        const double x0 = i0 + (AA ? (sx ? 0.75 : 0.25) : 0.5);
+                        const float f = (float)(a.x - x0);
+                        // columns [o0, o1] may be within r, [s0, s1] are
+                        const int o0 = max((int)ceilf(f - h - 1e-4f), ilo), o1 = min((int)floorf(f + h + 1e-4f), ihi);
+                        const int s0 = (int)ceilf(f - h + 1e-4f), s1 = (int)floorf(f + h - 1e-4f);
+                        if (o0 > o1) continue;
+                        uint64_t bits = (((2ull << (o1 - o0)) - 1ull) << o0) & todo;
+                        if (o0 < s0 || o1 > s1) {
+                            auto test = [&](int ii) {
+                                const double wx = x0 + (double)ii - a.x;
+                                if (!(wx * wx + wy * wy <= r2)) bits &= ~(1ull << ii);
+                            };
+                            // one column of an end at most (of both, where the
+                            // row's run is that narrow)
+                            if (o0 < s0) test(o0);
+                            if (o1 > s1) test(o1);
+                        }
+#pragma unroll
+                        for (int wd = 0; wd < W; ++wd)
+                            if ((uint32_t)(bits >> (32 * wd)))
+                                atomicOr(&mask[mm * MW + jj * W + wd], (uint32_t)(bits >> (32 * wd)));
+                    }
+                }
+            }
+        }
+    };
+
     // Tests every queued object against its pixels; returns true once the
     // whole region is lit.
     auto drain = [&]() -> bool {
         const int nq = ctl[1];
+        if constexpr (!SEG) {
+            drain_points(nq);
+        } else {
         const int per = (nq + nthr - 1) / nthr;
         const int q0 = min(nq, tid * per), q1 = min(nq, q0 + per);
         uint32_t cnt = 0;
@@ -1042,6 +1103,7 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
 #pragma unroll
             for (int mm = 0; mm < NM; ++mm)
                 if (bits[mm]) atomicOr(&mask[mm * MW + widx], bits[mm]);
+        }
         }
         __syncthreads();
         bool full = true;
