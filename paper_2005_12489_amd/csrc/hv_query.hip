@@ -42,6 +42,7 @@ namespace {
 
 constexpr uint32_t kBigFlag = 0x80000000u;  // staged object tested pixel-parallel
 constexpr int kSmallArea = 48;              // largest pixel range tested object-parallel
+constexpr int kUnitShift = 4;                // 16 columns of a row: a unit of a region's exact tests
 constexpr double kRangeEps = 1e-7;          // px, widens every pixel range
 constexpr double kAcceptMargin = 1e-3;      // px: accepts in FP32 use the radius r - kAcceptMargin
 constexpr int kCandBytes = 16 + 16 + 8 + 4; // staged object: a, d, 1/|d|^2, range
@@ -663,11 +664,11 @@ __host__ __device__ inline int query_stack_words(int levels, int threads, int pe
     return kFrontier + width * (levels > 1 ? levels - 1 : 0);
 }
 
-// stack | queued objects (SoA) | cell prefix sums | mask rows (four sets for
-// anti-aliased output, one per sub-sample) | control | scan scratch
+// stack | queued objects (SoA) | units of exact tests | mask rows (four sets
+// for anti-aliased output, one per sub-sample) | control
 __host__ __device__ inline size_t region_lds_bytes(int cap, int levels, int threads, int rs, int opl, int aa = 0) {
     return align16((size_t)query_stack_words(levels, threads, opl) * 4) + align16((size_t)cap * kCandBytes) +
-           align16((size_t)(cap + 1) * 4) + align16((size_t)rs * (rs / 32) * 4 * (aa ? 4 : 1)) + 16 + 64;
+           align16((size_t)cap * 4) + align16((size_t)rs * (rs / 32) * 4 * (aa ? 4 : 1)) + 16;
 }
 
 struct RegionLds {
@@ -675,34 +676,10 @@ struct RegionLds {
     double2 *ca, *cd;
     double *ci;
     uint32_t *crng;  // ilo | ihi << 6 | jlo << 12 | jhi << 18 (region pixels)
-    uint32_t *cpre;  // exclusive prefix sums of work cells per queued object
+    uint16_t *units; // the exact tests to make, 2 a queued object at a time
     uint32_t *mask;  // RS rows x RS/32 words (x4 for anti-aliased output: sub-sample m at m * RS * RS/32)
     int *ctl;        // [0] stack size, [1] queued objects, [2] settled from cells
-    uint32_t *scan;  // 16 words
 };
-
-// Exclusive scan over the workgroup (blockDim a multiple of 64, at most
-// 1024); `scan` holds 16 words of LDS.  Every thread must call it.
-__device__ inline uint32_t wg_excl_scan(uint32_t v, uint32_t *total, uint32_t *scan) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    uint32_t x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
-    }
-    if (lane == 63) scan[w] = x;
-    __syncthreads();
-    uint32_t off = 0, tot = 0;
-    for (int k = 0; k < nw; ++k) {
-        const uint32_t sk = scan[k];
-        if (k < w) off += sk;
-        tot += sk;
-    }
-    *total = tot;
-    __syncthreads();
-    return off + x - v;
-}
 
 // Region pixels whose centre lies within r, per axis, of the box
 // [x0, x1] x [y0, y1] (tile-local px), widened by kRangeEps; false if none.
@@ -733,11 +710,6 @@ __device__ inline bool range_lit(const uint32_t *mask, int ilo, int ihi, int jlo
             if ((mask[jj * W + w] & want) != want) return false;
         }
     return true;
-}
-
-__device__ inline int region_cells(uint32_t rg) {
-    const int ilo = rg & 63, ihi = (rg >> 6) & 63, jlo = (rg >> 12) & 63, jhi = (rg >> 18) & 63;
-    return (jhi - jlo + 1) * ((ihi >> 3) - (ilo >> 3) + 1);
 }
 
 // Settles the pixels of a region from the occupancy cells 2^-k px wide: lit
@@ -847,6 +819,7 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
     constexpr int W = RS / 32;   // mask words per region row
     constexpr int MW = RS * W;   // words of one mask
     constexpr int NM = AA ? 4 : 1;
+    using RowBits = std::conditional_t<W == 1, uint32_t, uint64_t>;
     const int tid = own_thread(), lane = tid & 63, nthr = blockDim.x;
     uint32_t *stk = L.stk;
     uint32_t *mask = L.mask;
@@ -1003,108 +976,130 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
         }
     };
 
+    // Queued segments: every wave takes each nw-th, one a lane, and lists the
+    // units of work they leave: (segment, row with an open pixel, 16 columns of
+    // its range).  Then a lane tests a unit's open pixels.  Most rows in reach
+    // are lit by then, from cells or accepts, and listing the open ones costs
+    // less than a lane for each.  Units of 4 or 8 columns spread a dense
+    // region's tests better over the lanes, but list more: mixed tiles of 2e8
+    // edges 2.70 and 2.61 ms, 16 columns 2.58 (2.73 with every row in reach and
+    // a binary search for its segment).
+    auto drain_segments = [&](int nq) {
+        // open pixels of [ilo, ihi] in row jj, as row bits
+        auto open = [&](int jj, int ilo, int ihi) -> RowBits {
+            RowBits lit = ~(RowBits)0;
+#pragma unroll
+            for (int mm = 0; mm < NM; ++mm) {
+                RowBits m = 0;
+#pragma unroll
+                for (int wd = 0; wd < W; ++wd) m |= (RowBits)mask[mm * MW + jj * W + wd] << (32 * wd);
+                lit &= m;
+            }
+            return ((((RowBits)2 << (ihi - ilo)) - 1) << ilo) & ~lit;
+        };
+        const int nw = nthr >> 6, wv = __builtin_amdgcn_readfirstlane(tid >> 6), window = 2 * cap / nw;
+        uint16_t *const units = L.units + wv * window;
+        for (int base = wv; base < nq; base += nthr) {
+            const int mine = base + lane * nw;
+            RowBits rows = 0;
+            int groups = 0;
+            if (mine < nq) {
+                const uint32_t rg = L.crng[mine];
+                const int ilo = rg & 63, ihi = (rg >> 6) & 63, jhi = (rg >> 18) & 63;
+                for (int jj = (rg >> 12) & 63; jj <= jhi; ++jj)
+                    if (open(jj, ilo, ihi)) rows |= (RowBits)1 << jj;
+                groups = ((ihi - ilo) >> kUnitShift) + 1;
+            }
+            const int count = (W == 1 ? __popc((uint32_t)rows) : __popcll(rows)) * groups;
+            int first = 0, total = 0;
+#pragma unroll
+            for (int b = 0; (RS * (RS >> kUnitShift)) >> b; ++b) {
+                const uint64_t m = __ballot((count >> b) & 1);
+                first += (int)lanes_below(m) << b;
+                total += __popcll(m) << b;
+            }
+            for (int w0 = 0; w0 < total; w0 += window) {
+                int at = first - w0;
+                for (RowBits left = rows; left && at < window; left &= left - 1) {
+                    const int jj = W == 1 ? __builtin_ctz((uint32_t)left) : __builtin_ctzll(left);
+                    for (int g = 0; g < groups; ++g, ++at)
+                        if (at >= 0 && at < window) units[at] = (uint16_t)(lane | jj << 6 | g << (W == 1 ? 11 : 12));
+                }
+                __builtin_amdgcn_wave_barrier();
+                for (int u = lane; u < min(total - w0, window); u += 64) {
+                    const uint32_t e = units[u];
+                    const int lo = base + (int)(e & 63) * nw, row = (e >> 6) & (RS - 1);
+                    const uint32_t rg = L.crng[lo];
+                    const int c0 = (int)(rg & 63) + ((int)(e >> (W == 1 ? 11 : 12)) << kUnitShift);
+                    const int c1 = min((int)((rg >> 6) & 63), c0 + (1 << kUnitShift) - 1);
+                    const double2 a = L.ca[lo];
+                    const double2 d = L.cd[lo];
+                    const double inv = L.ci[lo];
+                    // exact FP64 squared distance from a sample (tile-local px) to the segment
+                    auto dist2 = [&](double px, double py) -> double {
+                        const double wx = px - a.x, wy = py - a.y;
+                        double tt = (wx * d.x + wy * d.y) * inv;
+                        tt = fmin(fmax(tt, 0.0), 1.0);
+                        const double ex = wx - tt * d.x, ey = wy - tt * d.y;
+                        return ex * ex + ey * ey;
+                    };
+                    const double cy = j0 + (double)row + 0.5;
+                    RowBits todo = open(row, c0, c1);  // (bits are only ever set)
+                    RowBits bits[NM];
+#pragma unroll
+                    for (int mm = 0; mm < NM; ++mm) bits[mm] = 0;
+                    while (todo) {
+                        const int ii = W == 1 ? __builtin_ctz((uint32_t)todo) : __builtin_ctzll(todo);
+                        const RowBits bit = (RowBits)1 << ii;
+                        todo &= todo - 1;
+                        const double cx = i0 + (double)ii + 0.5;
+                        if (AA) {
+                            // From r >= 1 on, Algorithm 1's thresholds on the centre's
+                            // distance first: a sub-sample lies sqrt(2)/4 px from it,
+                            // so within rin of the object every sub-sample is within r,
+                            // beyond rout none is (both kept 1e-7 px inside the exact
+                            // bounds).  Otherwise (and for smaller r, where the band
+                            // between them holds nearly every pixel in reach)
+                            // sub-sample mm at (cx -+ 1/4, cy -+ 1/4) is tested itself
+                            // (bit 0 of mm picks +x, bit 1 picks +y).
+                            auto each = [&]() {
+#pragma unroll
+                                for (int mm = 0; mm < NM; ++mm)
+                                    if (dist2(cx + ((mm & 1) ? 0.25 : -0.25), cy + ((mm & 2) ? 0.25 : -0.25)) <= r2)
+                                        bits[mm] |= bit;
+                            };
+                            if (centre_first) {
+                                const double dc2 = dist2(cx, cy);
+                                if (dc2 <= rin2) {
+#pragma unroll
+                                    for (int mm = 0; mm < NM; ++mm) bits[mm] |= bit;
+                                } else if (dc2 <= rout2) {
+                                    each();
+                                }
+                            } else {
+                                each();
+                            }
+                        } else if (dist2(cx, cy) <= r2) {
+                            bits[0] |= bit;
+                        }
+                    }
+#pragma unroll
+                    for (int mm = 0; mm < NM; ++mm)
+#pragma unroll
+                        for (int wd = 0; wd < W; ++wd)
+                            if ((uint32_t)(bits[mm] >> (32 * wd)))
+                                atomicOr(&mask[mm * MW + row * W + wd], (uint32_t)(bits[mm] >> (32 * wd)));
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+    };
+
     // Tests every queued object against its pixels; returns true once the
     // whole region is lit.
     auto drain = [&]() -> bool {
-        const int nq = ctl[1];
-        if constexpr (!SEG) {
-            drain_points(nq);
-        } else {
-        const int per = (nq + nthr - 1) / nthr;
-        const int q0 = min(nq, tid * per), q1 = min(nq, q0 + per);
-        uint32_t cnt = 0;
-        for (int q = q0; q < q1; ++q) cnt += (uint32_t)region_cells(L.crng[q]);
-        uint32_t tot;
-        uint32_t off = wg_excl_scan(cnt, &tot, L.scan);
-        for (int q = q0; q < q1; ++q) {
-            L.cpre[q] = off;
-            off += (uint32_t)region_cells(L.crng[q]);
-        }
-        __syncthreads();
-        for (uint32_t cell = tid; cell < tot; cell += nthr) {
-            int lo = 0, hi = nq - 1;  // last object whose first cell is <= cell
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (L.cpre[mid] <= cell) lo = mid;
-                else hi = mid - 1;
-            }
-            const uint32_t rg = L.crng[lo];
-            const int ilo = rg & 63, ihi = (rg >> 6) & 63, jlo = (rg >> 12) & 63;
-            const int g0 = ilo >> 3, ng = (ihi >> 3) - g0 + 1;
-            const int local = (int)(cell - L.cpre[lo]);
-            // local / ng by reciprocal: exact here (local < 2^10, ng <= 9)
-            const int dq = (int)(((float)local + 0.5f) * __builtin_amdgcn_rcpf((float)ng));
-            const int row = jlo + dq, g = g0 + (local - dq * ng);
-            if (row >= RS || g < g0 || g >= g0 + ng) continue;  // never taken: the quotient is exact
-            const int c0 = max(ilo, 8 * g), c1 = min(ihi, 8 * g + 7);
-            const double2 a = L.ca[lo];
-            double2 d = make_double2(0.0, 0.0);
-            double inv = 0.0;
-            if (SEG) {
-                d = L.cd[lo];
-                inv = L.ci[lo];
-            }
-            // exact FP64 squared distance from a sample (tile-local px) to the object
-            auto dist2 = [&](double px, double py) -> double {
-                const double wx = px - a.x, wy = py - a.y;
-                if (SEG) {
-                    double tt = (wx * d.x + wy * d.y) * inv;
-                    tt = fmin(fmax(tt, 0.0), 1.0);
-                    const double ex = wx - tt * d.x, ey = wy - tt * d.y;
-                    return ex * ex + ey * ey;
-                }
-                return wx * wx + wy * wy;
-            };
-            const double cy = j0 + (double)row + 0.5;
-            // only the cell's pixels not done yet (bits are only ever set)
-            const int wbase = c0 & ~31, widx = row * W + (wbase >> 5);
-            uint32_t done = mask[widx];
-#pragma unroll
-            for (int mm = 1; mm < NM; ++mm) done &= mask[mm * MW + widx];
-            uint32_t todo = (((2u << (c1 - c0)) - 1u) << (c0 - wbase)) & ~done;
-            uint32_t bits[NM];
-#pragma unroll
-            for (int mm = 0; mm < NM; ++mm) bits[mm] = 0;
-            while (todo) {
-                const int ii = wbase + __builtin_ctz(todo);
-                const uint32_t bit = 1u << (ii & 31);
-                todo &= todo - 1u;
-                const double cx = i0 + (double)ii + 0.5;
-                if (AA) {
-                    // From r >= 1 on, Algorithm 1's thresholds on the centre's
-                    // distance first: a sub-sample lies sqrt(2)/4 px from it,
-                    // so within rin of the object every sub-sample is within r,
-                    // beyond rout none is (both kept 1e-7 px inside the exact
-                    // bounds).  Otherwise (and for smaller r, where the band
-                    // between them holds nearly every pixel in reach)
-                    // sub-sample mm at (cx -+ 1/4, cy -+ 1/4) is tested itself
-                    // (bit 0 of mm picks +x, bit 1 picks +y).
-                    auto each = [&]() {
-#pragma unroll
-                        for (int mm = 0; mm < NM; ++mm)
-                            if (dist2(cx + ((mm & 1) ? 0.25 : -0.25), cy + ((mm & 2) ? 0.25 : -0.25)) <= r2)
-                                bits[mm] |= bit;
-                    };
-                    if (centre_first) {
-                        const double dc2 = dist2(cx, cy);
-                        if (dc2 <= rin2) {
-#pragma unroll
-                            for (int mm = 0; mm < NM; ++mm) bits[mm] |= bit;
-                        } else if (dc2 <= rout2) {
-                            each();
-                        }
-                    } else {
-                        each();
-                    }
-                } else if (dist2(cx, cy) <= r2) {
-                    bits[0] |= bit;
-                }
-            }
-#pragma unroll
-            for (int mm = 0; mm < NM; ++mm)
-                if (bits[mm]) atomicOr(&mask[mm * MW + widx], bits[mm]);
-        }
-        }
+        if constexpr (SEG) drain_segments(ctl[1]);
+        else drain_points(ctl[1]);
         __syncthreads();
         bool full = true;
         for (int k = tid; k < NM * MW; k += nthr) full &= mask[k] == 0xffffffffu;
@@ -1439,10 +1434,9 @@ __device__ inline RegionLds region_lds(unsigned char *base, int cap, int max_lev
     L.cd = L.ca + cap;
     L.ci = reinterpret_cast<double *>(L.cd + cap);
     L.crng = reinterpret_cast<uint32_t *>(L.ci + cap);
-    L.cpre = reinterpret_cast<uint32_t *>(cb + align16((size_t)cap * kCandBytes));
-    L.mask = reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(L.cpre) + align16((size_t)(cap + 1) * 4));
+    L.units = reinterpret_cast<uint16_t *>(cb + align16((size_t)cap * kCandBytes));
+    L.mask = reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(L.units) + align16((size_t)cap * 4));
     L.ctl = reinterpret_cast<int *>(L.mask + RS * (RS / 32) * (AA ? 4 : 1));
-    L.scan = reinterpret_cast<uint32_t *>(L.ctl + 4);
     return L;
 }
 
