@@ -880,12 +880,31 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
     } else {
         for (int k = tid; k < NM * MW; k += nthr) mask[k] = 0;
     }
-    // a range is done once every pixel in it is set in every mask
-    auto range_done = [&](int ilo, int ihi, int jlo, int jhi) -> bool {
-        bool d = range_lit<W>(mask, ilo, ihi, jlo, jhi);
+    // pixels of row jj lit in every mask
+    auto lit_row = [&](int jj) -> RowBits {
+        RowBits lit = ~(RowBits)0;
 #pragma unroll
-        for (int mm = 1; mm < NM; ++mm) d = d && range_lit<W>(mask + mm * MW, ilo, ihi, jlo, jhi);
-        return d;
+        for (int mm = 0; mm < NM; ++mm) {
+            RowBits m = 0;
+#pragma unroll
+            for (int wd = 0; wd < W; ++wd) m |= (RowBits)mask[mm * MW + jj * W + wd] << (32 * wd);
+            lit &= m;
+        }
+        return lit;
+    };
+    // A range is done once every pixel in it is set in every mask.  Rows that
+    // have no open pixel (as of the last look at them: after the cells, and
+    // after each drain) need no reading, and most regions settled from cells
+    // have few others: without this mixed tiles of 2e8 edges took 2.57 ms
+    // instead of 2.09, of 1e9 points 4.18 instead of 3.71.
+    RowBits open_rows = ~(RowBits)0;
+    auto range_done = [&](int ilo, int ihi, int jlo, int jhi) -> bool {
+        const RowBits want = (((RowBits)2 << (ihi - ilo)) - 1) << ilo;
+        for (RowBits left = open_rows & ((((RowBits)2 << (jhi - jlo)) - 1) << jlo); left; left &= left - 1) {
+            const int jj = W == 1 ? __builtin_ctz((uint32_t)left) : __builtin_ctzll(left);
+            if (want & ~lit_row(jj)) return false;
+        }
+        return true;
     };
     if (tid == 0) {
         ctl[0] = 0;
@@ -893,6 +912,7 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
         ctl[2] = settled;
     }
     __syncthreads();
+    if (settled) open_rows = (RowBits)__ballot(lane < RS && ~lit_row(lane & (RS - 1)) != 0);
     // accepts keep a margin so that they never claim a sample whose distance
     // could round to just above r
     const double racc = r - 1e-7, racc2 = racc * racc;
@@ -987,15 +1007,7 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
     auto drain_segments = [&](int nq) {
         // open pixels of [ilo, ihi] in row jj, as row bits
         auto open = [&](int jj, int ilo, int ihi) -> RowBits {
-            RowBits lit = ~(RowBits)0;
-#pragma unroll
-            for (int mm = 0; mm < NM; ++mm) {
-                RowBits m = 0;
-#pragma unroll
-                for (int wd = 0; wd < W; ++wd) m |= (RowBits)mask[mm * MW + jj * W + wd] << (32 * wd);
-                lit &= m;
-            }
-            return ((((RowBits)2 << (ihi - ilo)) - 1) << ilo) & ~lit;
+            return ((((RowBits)2 << (ihi - ilo)) - 1) << ilo) & ~lit_row(jj);
         };
         const int nw = nthr >> 6, wv = __builtin_amdgcn_readfirstlane(tid >> 6), window = 2 * cap / nw;
         uint16_t *const units = L.units + wv * window;
@@ -1006,8 +1018,11 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
             if (mine < nq) {
                 const uint32_t rg = L.crng[mine];
                 const int ilo = rg & 63, ihi = (rg >> 6) & 63, jhi = (rg >> 18) & 63;
-                for (int jj = (rg >> 12) & 63; jj <= jhi; ++jj)
+                const int jlo = (rg >> 12) & 63;
+                for (RowBits left = open_rows & ((((RowBits)2 << (jhi - jlo)) - 1) << jlo); left; left &= left - 1) {
+                    const int jj = W == 1 ? __builtin_ctz((uint32_t)left) : __builtin_ctzll(left);
                     if (open(jj, ilo, ihi)) rows |= (RowBits)1 << jj;
+                }
                 groups = ((ihi - ilo) >> kUnitShift) + 1;
             }
             const int count = (W == 1 ? __popc((uint32_t)rows) : __popcll(rows)) * groups;
@@ -1101,12 +1116,11 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
         if constexpr (SEG) drain_segments(ctl[1]);
         else drain_points(ctl[1]);
         __syncthreads();
-        bool full = true;
-        for (int k = tid; k < NM * MW; k += nthr) full &= mask[k] == 0xffffffffu;
-        const bool all = __syncthreads_and(full);
+        open_rows = (RowBits)__ballot(lane < RS && ~lit_row(lane & (RS - 1)) != 0);
+        __syncthreads();
         if (tid == 0) ctl[1] = 0;
         __syncthreads();
-        return all;
+        return open_rows == 0;
     };
 
     // Two walks.  The first (accept pass) descends only until nodes are small
