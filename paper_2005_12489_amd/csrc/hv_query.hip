@@ -1399,9 +1399,9 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
         if (done) break;
         if (__syncthreads_or(accepted)) {
             // accepts may have lit the whole region
-            bool full = true;
-            for (int k = tid; k < NM * MW; k += nthr) full &= mask[k] == 0xffffffffu;
-            if (__syncthreads_and(full)) {
+            open_rows = (RowBits)__ballot(lane < RS && ~lit_row(lane & (RS - 1)) != 0);
+            __syncthreads();  // every wave has looked before a drain lights more
+            if (open_rows == 0) {
                 done = true;
                 break;
             }
