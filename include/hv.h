@@ -108,7 +108,9 @@ int hv_render_tiles(const hv_index *index, const hv_tile *tiles, int64_t n_tiles
                     const hv_style *style, uint8_t *out_masks);
 
 /* Release an index and its device memory (NULL-safe).  The caller must make
- * sure no render using it is still in flight. */
+ * sure no render using it is still in flight.  Blocks of up to 512 MB are
+ * kept for the next build, at most 1 GiB in the process; they are given back
+ * before an allocation of the library fails. */
 void hv_free(hv_index *index);
 
 /* Message describing the calling thread's most recent error ("" if none). */
@@ -321,8 +323,9 @@ hv_index *hv_polygon_index_build(const double *edges, int64_t n, const int64_t *
  * out_masks as for hv_render_tiles (8192 bytes per tile, same bit layout).
  * launch: region mode only (region 32 or 64; NULL = region 32 with two
  * waves per workgroup, objs_per_lane 2, cand_cap 256, at any batch size).
- * Each region's candidate polygons are those whose bounding box holds one
- * of its pixel centres not filled yet; their edges are tested in groups of up to 32
+ * Centres in cells of the index that lie wholly in a polygon, or have none
+ * near, are settled from those.  Each region's candidate polygons are those
+ * whose bounding box holds one of its pixel centres not settled or filled yet; their edges are tested in groups of up to 32
  * polygons, and only the edges of 8-edge runs whose stored bounding box can
  * cross one of the region's pixel-centre rows are read.
  * Errors as hv_render_tiles_ex, plus HV_EINVAL for an index that is not a

@@ -86,8 +86,8 @@ int validate_style(const hv_style *style) {
 // the heaviest regions set the time, and more waves on each region shorten
 // them; with many the GPU is full anyway and one wave per region (occupancy
 // bound by registers) does the least work per pixel.  4,096 tiles of 10M
-// segments, none dense: 0.39 ms with four waves, 0.47 with one; 10,000
-// requests over 1e9 points, half of them dense: 7.2 ms and 4.6.
+// segments, none dense: 0.28 ms with four waves, 0.31 with one; 10,000
+// requests over 1e9 points, half of them dense: 5.6 ms and 3.7.
 int default_waves(int64_t n, int64_t dense) {
     return n < 1024 || dense < 256 ? 4 : n < 4096 || dense < 1024 ? 2 : 1;
 }
@@ -104,7 +104,7 @@ int resolve_shape(const hv_launch *l, int max_levels, hv::LaunchShape *s, int64_
     s->waves = default_waves(n, dense);
     // (one wave: a queue of 96 takes a leaf step's 128 objects in two parts and
     // leaves LDS for 16 workgroups a CU instead of 14: 10,000 requests over 1e9
-    // points 4.6 ms instead of 4.9)
+    // points 3.7 ms instead of 3.9)
     s->cand_cap = s->waves == 1 ? 96 : 64 * s->waves * 2;
     s->grid = 0;
     s->region = 32;

@@ -2,30 +2,38 @@
 //
 // Display-driven computing makes each pixel a unit of work whose value comes
 // from index queries about nearby objects (Sec. 3).  A batch of requests --
-// each one tile of one index with its own radius -- runs as two kernels:
+// each one tile of one index with its own radius -- runs as two kernels, or as
+// one when it is small:
 //
-//  1. k_tile_frontier -- one wavefront per request walks the tree breadth-
-//     first with the tile's box grown by r and keeps the deepest level at
-//     which at most 256 nodes meet it.  A tile whose frontier is empty misses
-//     all data and takes no further work (Sec. 4.1: tiles outside the data's
-//     bounds make no task); it goes to a list of tiles whose masks the query
-//     kernel zero-fills.  The others are appended to a compacted work list.
-//  2. k_query -- a persistent grid (as many workgroups as the GPU holds at
-//     once) strides over the (tile, pixel block) items of that list, one
-//     wavefront per block (8x8, 16x16 or 32x32: 1, 4 or 16 pixels per lane),
-//     the way the paper's engine hands tiles to idle processes (Sec. 4.3).
-//     A block starts from its tile's frontier and walks down with the
-//     block's box grown by r: the OuterBox filter of Algorithm 1, shared by
-//     the block's pixels.  Objects that pass are staged in LDS in tile-local
-//     pixel coordinates with the range of block pixels their box grown by r
-//     covers.  Small ranges are tested object-parallel (one lane per object,
-//     only its own pixels: Algorithm 1's per-pixel box filter seen from the
-//     object's side); large ones pixel-parallel (every lane its own pixels).
+//  1. k_tile_frontier -- one wavefront per request (four in small batches) walks
+//     the tree breadth-first with the tile's box grown by r and keeps the
+//     deepest level at which at most 256 nodes meet it.  A tile whose frontier
+//     is empty misses all data and takes no further work (Sec. 4.1: tiles
+//     outside the data's bounds make no task); it goes to a list of tiles whose
+//     masks the query kernel zero-fills.  The others are listed by how they
+//     are rendered, by regions or by strips.
+//  2. the query kernel, in the way the tile needs:
+//     - k_query_region -- a workgroup per 32x32 or 64x64 pixel region.  It
+//       settles what pixels it can from the index's occupancy cells, then walks
+//       down from the tile's frontier with the region's box grown by r: the
+//       OuterBox filter of Algorithm 1, shared by the region's pixels.
+//     - k_query_objects (hv_objects.h) -- a workgroup per strip of a tile that
+//       few objects can reach; it takes them one by one.
+//     - k_query_both runs a batch's regions and strips in one launch.
+//     - k_query -- one wavefront per 8x8, 16x16 or 32x32 pixel block (1, 4 or
+//       16 pixels per lane), where the launch shape asks for blocks.  Objects
+//       that pass are staged in LDS in tile-local pixel coordinates with the
+//       range of block pixels their box grown by r covers.  Small ranges are
+//       tested object-parallel (one lane per object, only its own pixels:
+//       Algorithm 1's per-pixel box filter seen from the object's side); large
+//       ones pixel-parallel (every lane its own pixels).
 //     Every test is the exact FP64 distance against r, inclusive.  Once all
-//     pixels of the block are lit the wavefront stops, as Algorithm 1 returns
-//     as soon as one object lies within the radius.
+//     pixels of a region or block are lit its walk stops, as Algorithm 1
+//     returns as soon as one object lies within the radius.
+//  Calls of up to kFewRequests requests carry them in the kernel's arguments
+//  (k_few_query, k_few_fill), those of up to kSelfRequests in one launch.
 //
-// The tree walk is wavefront-uniform: the stack lives in LDS, each step pops
+// k_query's tree walk is wavefront-uniform: the stack lives in LDS, each step pops
 // up to four nodes of the same level and the 64 lanes test their 4 x 16
 // children at once; hits are pushed with one ballot.
 #include <hip/hip_runtime.h>
