@@ -87,7 +87,7 @@ int validate_style(const hv_style *style) {
 // them; with many the GPU is full anyway and one wave per region (occupancy
 // bound by registers) does the least work per pixel.  4,096 tiles of 10M
 // segments, none dense: 0.28 ms with four waves, 0.31 with one; 10,000
-// requests over 1e9 points, half of them dense: 5.6 ms and 3.7.
+// requests over 1e9 points, half of them dense: 5.6 ms and 3.5.
 int default_waves(int64_t n, int64_t dense) {
     return n < 1024 || dense < 256 ? 4 : n < 4096 || dense < 1024 ? 2 : 1;
 }

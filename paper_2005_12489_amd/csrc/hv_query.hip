@@ -250,12 +250,14 @@ __device__ __forceinline__ Frontier frontier_walk(const DevIndex &ix, const DevR
     return Frontier{cur, ncur, lvl, cbits};
 }
 
-// A radius is looked at in the finest cells that give it at most kCellRho
-// cells and that the index has; below kCellMin they decide too little.  (The
-// window holds up to 15.  Half of that settles nearly as many pixels with half
-// the rows to read: 10,000 requests over 1e9 points 5.5 ms, 5.8 at 10, 6.5 at 15;
-// the 2e8 edges 3.0 ms at each.)
-constexpr double kCellRho = 8.0;
+// A radius is looked at in the finest cells that give it at most this many
+// cells and that the index has; below kCellMin they decide too little.  The
+// window holds up to 15; fewer settle nearly as many pixels with fewer rows to
+// read.  What they leave costs more for segments than for points.  Query kernel
+// at 5, 8 and 15: 10,000 requests over 1e9 points 3.50, 3.66 and 4.55 ms; the 2e8
+// edges 2.17, 2.11 and 2.14; 61 requests over two sets 0.082 (0.070 at 8 for
+// segments and 5 for points), 0.070 and 0.074.
+constexpr double kCellRhoSegments = 8.0, kCellRhoPoints = 5.0;
 constexpr double kCellMin = 1.5;
 constexpr float kCellMargin = 1e-3f;  // cells: far above the cells' own 1e-6 and FP32 rounding here
 
@@ -263,7 +265,7 @@ constexpr float kCellMargin = 1e-3f;  // cells: far above the cells' own 1e-6 an
 // shift k >= 0 from z (cells are 2^-k px), or -1.
 __device__ inline int cell_shift(const DevIndex &ix, int z, double r) {
     if (ix.cell_top < z) return -1;
-    const int k = min(ix.cell_top - z, ilogb(kCellRho / r));
+    const int k = min(ix.cell_top - z, ilogb((ix.seg ? kCellRhoSegments : kCellRhoPoints) / r));
     return k >= 0 && ldexp(r, k) >= kCellMin ? k : -1;
 }
 
@@ -2290,8 +2292,8 @@ hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, 
     // Filling's regions, and in large batches the distance kernel's, differ in
     // cost by orders of magnitude (clusters next to empty sea, settled regions
     // next to walked ones), so each gets its own workgroup and the dispatcher
-    // balances them: 10,000 requests over 1e9 points take 6.1 ms instead of 6.8
-    // with a persistent grid.  Smaller batches (more waves to a region) and
+    // balances them: 10,000 requests over 1e9 points took 6.1 ms instead of 6.8
+    // with a persistent grid, while walks were longer (3.65 to 3.73 either way since).  Smaller batches (more waves to a region) and
     // anti-aliased ones keep that grid (10M segments 0.90 ms instead of 0.93).
     const bool spread = s.fill || (s.region && !s.aa && s.waves == 1);
     int64_t grid = s.grid > 0 ? s.grid : spread ? kSpreadGrid : persistent_grid(s, max_levels);
