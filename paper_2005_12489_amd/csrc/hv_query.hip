@@ -1358,10 +1358,13 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
 #pragma unroll
             for (int k = 0; k < OPL; ++k) {
                 // a queue smaller than a step's OPL * threads objects takes
-                // them threads at a time, draining in between
+                // them threads at a time, draining in between; every wave
+                // reads the count before any of them queues more
                 if (k > 0 && cap < nthr * OPL) {
                     __syncthreads();
-                    if (ctl[1] > cap - nthr && drain()) {
+                    const bool drain_now = ctl[1] > cap - nthr;
+                    __syncthreads();
+                    if (drain_now && drain()) {
                         done = true;
                         break;
                     }
