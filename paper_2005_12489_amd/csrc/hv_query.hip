@@ -50,7 +50,7 @@ namespace {
 
 constexpr uint32_t kBigFlag = 0x80000000u;  // staged object tested pixel-parallel
 constexpr int kSmallArea = 48;              // largest pixel range tested object-parallel
-constexpr int kUnitShift = 4;                // 16 columns of a row: a unit of a region's exact tests
+constexpr int kUnitShift = 3;                // 8 columns of a row: a unit of a region's exact tests
 constexpr double kRangeEps = 1e-7;          // px, widens every pixel range
 constexpr double kAcceptMargin = 1e-3;      // px: accepts in FP32 use the radius r - kAcceptMargin
 constexpr int kCandBytes = 16 + 16 + 8 + 4; // staged object: a, d, 1/|d|^2, range
@@ -674,11 +674,11 @@ __host__ __device__ inline int query_stack_words(int levels, int threads, int pe
     return kFrontier + width * (levels > 1 ? levels - 1 : 0);
 }
 
-// stack | queued objects (SoA) | units of exact tests | mask rows (four sets
-// for anti-aliased output, one per sub-sample) | control
+// stack | queued objects (SoA) | mask rows (four sets for anti-aliased output,
+// one per sub-sample) | control
 __host__ __device__ inline size_t region_lds_bytes(int cap, int levels, int threads, int rs, int opl, int aa = 0) {
     return align16((size_t)query_stack_words(levels, threads, opl) * 4) + align16((size_t)cap * kCandBytes) +
-           align16((size_t)cap * 4) + align16((size_t)rs * (rs / 32) * 4 * (aa ? 4 : 1)) + 16;
+           align16((size_t)rs * (rs / 32) * 4 * (aa ? 4 : 1)) + 16;
 }
 
 struct RegionLds {
@@ -686,7 +686,6 @@ struct RegionLds {
     double2 *ca, *cd;
     double *ci;
     uint32_t *crng;  // ilo | ihi << 6 | jlo << 12 | jhi << 18 (region pixels)
-    uint16_t *units; // the exact tests to make, 2 a queued object at a time
     uint32_t *mask;  // RS rows x RS/32 words (x4 for anti-aliased output: sub-sample m at m * RS * RS/32)
     int *ctl;        // [0] stack size, [1] queued objects, [2] settled from cells
 };
@@ -1006,35 +1005,45 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
         }
     };
 
-    // Queued segments: every wave takes each nw-th, one a lane, and lists the
-    // units of work they leave: (segment, row with an open pixel, 16 columns of
-    // its range).  Then a lane tests a unit's open pixels.  Most rows in reach
-    // are lit by then, from cells or accepts, and listing the open ones costs
-    // less than a lane for each.  Units of 4 or 8 columns spread a dense
-    // region's tests better over the lanes, but list more: mixed tiles of 2e8
-    // edges 2.70 and 2.61 ms, 16 columns 2.58 (2.73 with every row in reach and
-    // a binary search for its segment).
+    // Queued segments: the workgroup's lanes, dealt over its waves, take one each,
+    // or, of a short queue, each some rows of one, and count the units of work it
+    // leaves: (row with an open pixel, 8 columns of the segment's range).  Then a
+    // lane finds a unit of the wave's -- its segment among the lanes' prefix sums,
+    // its row among the segment's open ones -- and tests its open pixels.  Most
+    // rows in reach are lit by then, from cells or accepts, and counting the open
+    // ones costs less than a lane for each (mixed tiles of 2e8 edges 2.73 ms with
+    // every row in reach dealt out, 2.58 this way).  The units are found, not
+    // listed: where segments cover most of a region the list takes as long as
+    // the tests (1,024 tiles of 30 px segments at r = 32: 1.54 ms with a list of
+    // 16-column units, 0.75 found; 1.11 with 4 columns and 0.56 with 16, which
+    // leave too many lanes idle in sparse tiles: 256 of 50 such segments,
+    // anti-aliased at r = 5, 0.19 -> 0.26 ms).
     auto drain_segments = [&](int nq) {
         // open pixels of [ilo, ihi] in row jj, as row bits
         auto open = [&](int jj, int ilo, int ihi) -> RowBits {
             return ((((RowBits)2 << (ihi - ilo)) - 1) << ilo) & ~lit_row(jj);
         };
-        const int nw = nthr >> 6, wv = __builtin_amdgcn_readfirstlane(tid >> 6), window = 2 * cap / nw;
-        uint16_t *const units = L.units + wv * window;
-        for (int base = wv; base < nq; base += nthr) {
-            const int mine = base + lane * nw;
+        const int nw = nthr >> 6, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+        int sh = 0;  // 2^sh lanes to a segment, each its rows of every 2^sh
+        while (sh < (W == 1 ? 5 : 6) && (nq << (sh + 1)) <= nthr) ++sh;
+        const int slot = lane * nw + wv;
+        RowBits turn = (RowBits)1 << (slot & ((1 << sh) - 1));
+        for (int k = 1 << sh; k < RS; k <<= 1) turn |= turn << k;
+        for (int base = 0; base < nq; base += nthr) {
+            const int mine = (base + slot) >> sh;
             RowBits rows = 0;
-            int groups = 0;
+            int width = 0;
             if (mine < nq) {
                 const uint32_t rg = L.crng[mine];
                 const int ilo = rg & 63, ihi = (rg >> 6) & 63, jhi = (rg >> 18) & 63;
                 const int jlo = (rg >> 12) & 63;
-                for (RowBits left = open_rows & ((((RowBits)2 << (jhi - jlo)) - 1) << jlo); left; left &= left - 1) {
+                for (RowBits left = turn & open_rows & ((((RowBits)2 << (jhi - jlo)) - 1) << jlo); left; left &= left - 1) {
                     const int jj = W == 1 ? __builtin_ctz((uint32_t)left) : __builtin_ctzll(left);
                     if (open(jj, ilo, ihi)) rows |= (RowBits)1 << jj;
                 }
-                groups = ((ihi - ilo) >> kUnitShift) + 1;
+                width = ihi - ilo;
             }
+            const int groups = (width >> kUnitShift) + 1;
             const int count = (W == 1 ? __popc((uint32_t)rows) : __popcll(rows)) * groups;
             int first = 0, total = 0;
 #pragma unroll
@@ -1043,19 +1052,32 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
                 first += (int)lanes_below(m) << b;
                 total += __popcll(m) << b;
             }
-            for (int w0 = 0; w0 < total; w0 += window) {
-                int at = first - w0;
-                for (RowBits left = rows; left && at < window; left &= left - 1) {
-                    const int jj = W == 1 ? __builtin_ctz((uint32_t)left) : __builtin_ctzll(left);
-                    for (int g = 0; g < groups; ++g, ++at)
-                        if (at >= 0 && at < window) units[at] = (uint16_t)(lane | jj << 6 | g << (W == 1 ? 11 : 12));
+            for (int u0 = 0; u0 < total; u0 += 64) {
+                const int u = min(u0 + lane, total - 1);
+                int l = 0;  // the last lane whose first unit is at most u
+#pragma unroll
+                for (int h = 32; h > 0; h >>= 1)
+                    if (__shfl(first, l + h, 64) <= u) l += h;
+                const int k = u - __shfl(first, l, 64), ng = __shfl(groups, l, 64);
+                // k / ng by reciprocal: exact here (k < 2^10, ng <= 8)
+                int nth = (int)(((float)k + 0.5f) * __builtin_amdgcn_rcpf((float)ng)), row = 0;
+                const int g = k - nth * ng;
+                RowBits left = W == 1 ? (RowBits)__shfl((uint32_t)rows, l, 64)
+                                      : (RowBits)__shfl((unsigned long long)rows, l, 64);
+#pragma unroll
+                for (int h = RS / 2; h > 0; h >>= 1) {  // row: the nth set bit
+                    const RowBits low = left & (((RowBits)1 << h) - 1);
+                    const int c = W == 1 ? __popc((uint32_t)low) : __popcll(low);
+                    if (nth >= c) {
+                        nth -= c;
+                        row += h;
+                        left >>= h;
+                    }
                 }
-                __builtin_amdgcn_wave_barrier();
-                for (int u = lane; u < min(total - w0, window); u += 64) {
-                    const uint32_t e = units[u];
-                    const int lo = base + (int)(e & 63) * nw, row = (e >> 6) & (RS - 1);
+                if (u0 + lane < total) {
+                    const int lo = (base + l * nw + wv) >> sh;
                     const uint32_t rg = L.crng[lo];
-                    const int c0 = (int)(rg & 63) + ((int)(e >> (W == 1 ? 11 : 12)) << kUnitShift);
+                    const int c0 = (int)(rg & 63) + (g << kUnitShift);
                     const int c1 = min((int)((rg >> 6) & 63), c0 + (1 << kUnitShift) - 1);
                     const double2 a = L.ca[lo];
                     const double2 d = L.cd[lo];
@@ -1115,7 +1137,6 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
                             if ((uint32_t)(bits[mm] >> (32 * wd)))
                                 atomicOr(&mask[mm * MW + row * W + wd], (uint32_t)(bits[mm] >> (32 * wd)));
                 }
-                __builtin_amdgcn_wave_barrier();
             }
         }
     };
@@ -1461,8 +1482,7 @@ __device__ inline RegionLds region_lds(unsigned char *base, int cap, int max_lev
     L.cd = L.ca + cap;
     L.ci = reinterpret_cast<double *>(L.cd + cap);
     L.crng = reinterpret_cast<uint32_t *>(L.ci + cap);
-    L.units = reinterpret_cast<uint16_t *>(cb + align16((size_t)cap * kCandBytes));
-    L.mask = reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(L.units) + align16((size_t)cap * 4));
+    L.mask = reinterpret_cast<uint32_t *>(cb + align16((size_t)cap * kCandBytes));
     L.ctl = reinterpret_cast<int *>(L.mask + RS * (RS / 32) * (AA ? 4 : 1));
     return L;
 }
