@@ -1160,8 +1160,9 @@ __device__ __forceinline__ void region_query(const DevIndex &ix, const DevReq &r
     // unlikely to be that small.  In dense data it lights most pixels, so
     // that the second, full walk finds most ranges lit and reads few objects.
     // A frontier made of leaves, or of nodes whose leaves cannot be small,
-    // takes the full walk only.
-    bool accept_pass = racc > 0.0 && flevel > 0 && promising && !settled;
+    // takes the full walk only, and so do regions settled from cells, unless the
+    // index's long segments are not in them.
+    bool accept_pass = racc > 0.0 && flevel > 0 && promising && !(settled && !ix.cell_gaps);
     bool done = false;
     for (;;) {
         const int sp = ctl[0];

@@ -69,3 +69,34 @@ def test_settled(hv, torch, name):
             mism, amb, lit = parity(render(hv, torch, h, tiles, r, L), tri)
             assert mism == 0, f"r={r} {L}: {mism} mismatches of {lit} lit"
     hv.hv_free(h)
+
+
+def test_many_long_segments(hv, torch):
+    """More segments over many cells than the list of them holds: the cells have
+    none of them and settle little, and the accept pass lights the tiles as it
+    does for a set without cells (the same with one segment beyond the world)."""
+    rng = np.random.default_rng(6)
+    n = 3_000_000  # cells down to zoom 5, these 60 of them long
+    p = rng.uniform(0.25, 0.5, (n, 2))
+    a = rng.uniform(0, 2 * np.pi, n)
+    obj = np.concatenate([p, np.clip(p + 60 / 8192 * np.stack([np.cos(a), np.sin(a)], 1), 0, 1)], 1)
+    r = 8.0
+    tiles = np.stack([np.full(64, 5), 8 + np.arange(64) % 8, 8 + np.arange(64) // 8], 1)
+    L = dict(region=32, waves_per_wg=1, objs_per_lane=2, cand_cap=96, cull_nodes=64)
+    out = torch.empty((64, 8192), dtype=torch.uint8, device="cuda")
+    ref = oracle.OracleIndex(obj, 1, merc01=True)
+    ms = []
+    for name in ("long", "without cells"):
+        if name == "without cells":
+            obj[-1] = (1.1, 1.1, 1.2, 1.2)
+        h = build(hv, torch, obj, 1 | hv.HV_INPUT_MERC01)
+        log(f"many long segments: {name}")
+        if name == "long":
+            for rr in (0.5, 1.5, r):
+                mism, _, lit = parity(render(hv, torch, h, tiles[:4], rr, L), ref.render(tiles[:4], rr)["tri"])
+                assert mism == 0, f"r={rr}: {mism} mismatches of {lit} lit"
+        reqs = hv.requests(h, tiles, r)
+        ms.append(min(hv.hv_time_kernels(reqs, out, L, reps=3)[1] for _ in range(4)))
+        hv.hv_free(h)
+    log(f"long {ms[0]:.3f} ms, without cells {ms[1]:.3f} ms")
+    assert ms[0] < 1.35 * ms[1]
