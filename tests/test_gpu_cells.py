@@ -100,3 +100,26 @@ def test_many_long_segments(hv, torch):
         hv.hv_free(h)
     log(f"long {ms[0]:.3f} ms, without cells {ms[1]:.3f} ms")
     assert ms[0] < 1.35 * ms[1]
+
+
+def test_many_long_among_short_segments(hv, torch):
+    """As above, among short ones: the cells light regions with many of those,
+    which skip the accept pass, and settle the others little, which take it."""
+    rng = np.random.default_rng(7)
+    n, n_long = 2_600_000, 1_100_000  # cells down to zoom 5, these 64 px wide there
+    p = rng.uniform(0.25, 0.5, (n, 2))
+    p[n_long:, 0] = 0.25 + 0.125 * rng.uniform(0, 1, n - n_long) ** 4  # few in the east
+    a = rng.uniform(0, 2 * np.pi, n)
+    size = np.where(np.arange(n) < n_long, 64 / 8192, 1e-5)
+    obj = np.concatenate([p, np.clip(p + size[:, None] * np.stack([np.cos(a), np.sin(a)], 1), 0, 1)], 1)
+    ref = oracle.OracleIndex(obj, 1, merc01=True)
+    h = build(hv, torch, obj, 1 | hv.HV_INPUT_MERC01)
+    tiles = np.array([[5, 8, 8], [5, 9, 12], [5, 11, 9], [5, 13, 13], [6, 17, 20], [6, 30, 31]])
+    log("many long segments among short ones")
+    for r in (0.5, 1.5, 8.0):
+        tri = ref.render(tiles, r)["tri"]
+        for L in (dict(region=32, waves_per_wg=1, objs_per_lane=2, cand_cap=96, cull_nodes=16),
+                  dict(region=64, waves_per_wg=4, objs_per_lane=2, cand_cap=512, cull_nodes=16)):
+            mism, _, lit = parity(render(hv, torch, h, tiles, r, L), tri)
+            assert mism == 0, f"r={r} {L}: {mism} mismatches of {lit} lit"
+    hv.hv_free(h)
