@@ -97,6 +97,14 @@ int default_waves(int64_t n, int64_t dense) {
 // 65,536 up to which a tile goes to the object kernel.
 bool is_dense(int64_t n_objects, int32_t z) { return (double)n_objects >= std::ldexp(16384.0, 2 * z); }
 
+// Whether a launch shape fits a workgroup's 64 KiB.  A distance region's queue
+// counts 48 bytes an entry here (it takes 44), so that the shapes accepted stay
+// those that were when it took more.
+bool fits_lds(const hv::LaunchShape &s, int max_levels) {
+    const size_t spare = s.region && !s.fill ? ((size_t)s.cand_cap * 4 + 15) / 16 * 16 : 0;
+    return hv::query_lds_bytes(s, max_levels) + spare <= 65536;
+}
+
 int resolve_shape(const hv_launch *l, int max_levels, hv::LaunchShape *s, int64_t n, int64_t dense) {
     // default: one workgroup per 32x32 region with default_waves() waves and
     // two objects per lane at a leaf step; hv_launch selects any other shape
@@ -131,7 +139,7 @@ int resolve_shape(const hv_launch *l, int max_levels, hv::LaunchShape *s, int64_
         return fail(HV_EINVAL, "launch.waves_per_wg must be 1, 2 or 4");
     if (s->grid < 0 || s->grid > (1 << 20)) return fail(HV_EINVAL, "launch.grid_wgs must be in [0, 2^20]");
     if (l && (l->aa_split < -2 || l->aa_split > 62)) return fail(HV_EINVAL, "launch.aa_split must be in [-2, 62]");
-    if (hv::query_lds_bytes(*s, max_levels) > 65536)
+    if (!fits_lds(*s, max_levels))
         return fail(HV_EINVAL, "launch shape needs more than 64 KiB of LDS per workgroup");
     return HV_OK;
 }
@@ -698,7 +706,7 @@ int aa_shape(const hv_launch *launch, int max_levels, int64_t n, int64_t dense, 
         if (shape->cand_cap < 64 * shape->waves * shape->opl) shape->cand_cap = 64 * shape->waves * shape->opl;
     }
     shape->aa = 1;
-    if (hv::query_lds_bytes(*shape, max_levels) > 65536)
+    if (!fits_lds(*shape, max_levels))
         return fail(HV_EINVAL, "launch shape needs more than 64 KiB of LDS per workgroup");
     return HV_OK;
 }

@@ -74,3 +74,17 @@ def test_wide_segments(hv, torch):
     hv.hv_free(h)
     log(f"regions {ms[0]:.3f} ms, blocks {ms[1]:.3f} ms")
     assert ms[0] < 1.1 * ms[1]
+
+
+@pytest.mark.parametrize("rs,aa,cap", [(32, 0, 1340), (64, 0, 1332), (32, 1, 1332)])
+def test_largest_queue(hv, torch, rs, aa, cap):
+    """The largest queue within 64 KiB: 48 bytes an entry, 1 KiB of stack for an index
+    of one level, 16 bytes of control and the mask rows (four sets if anti-aliased)."""
+    obj = np.random.default_rng(3).uniform(0, 1, (12, 2))
+    h = build(hv, torch, obj, hv.HV_INPUT_MERC01)
+    L = dict(region=rs, waves_per_wg=4, objs_per_lane=4)
+    call = render_aa if aa else render
+    call(hv, torch, h, TILES, 2.0, dict(L, cand_cap=cap))
+    with pytest.raises(hv.HvError):
+        call(hv, torch, h, TILES, 2.0, dict(L, cand_cap=cap + 1))
+    hv.hv_free(h)
