@@ -448,13 +448,30 @@ __global__ __launch_bounds__(256) void k_gather_leaves(const double *__restrict_
     if (i < n && i % kLeaf == 0) leaf[i / kLeaf] = b;
 }
 
+// The median over 64 of n segments, spread over the sorted order, of the larger
+// side of their boxes; a wavefront.
+__device__ inline void median_extent(const double4 *__restrict__ obj, int64_t n, double *__restrict__ extent) {
+    const int lane = threadIdx.x & 63;
+    const double4 g = obj[n * lane / 64];
+    const float mine = (float)fmax(fabs(g.z - g.x), fabs(g.w - g.y));
+    int rank = 0;
+    for (int k = 0; k < 64; ++k) {
+        const float v = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(mine), k));
+        rank += v < mine || (v == mine && k < lane);
+    }
+    if (rank == 32) *extent = mine;
+}
+
 // A level's boxes and representatives from its children's.  Node i of level l
 // owns the sorted objects [i * 16^(l + 1), (i + 1) * 16^(l + 1)), so its
-// representative is its first child's.
+// representative is its first child's.  The launch of the root's level, one
+// workgroup, also takes the n objects' extent.
 __global__ __launch_bounds__(256) void k_level(const double4 *__restrict__ child, const double2 *__restrict__ child_rep,
                                                int64_t nchild, double4 *__restrict__ parent,
-                                               double2 *__restrict__ parent_rep) {
+                                               double2 *__restrict__ parent_rep, const double4 *__restrict__ obj,
+                                               int64_t n, double *__restrict__ extent) {
     static_assert(kFan == 16, "a node is 16 neighbouring lanes");
+    if (extent && blockIdx.x == 0 && threadIdx.x < 64) median_extent(obj, n, extent);
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const double4 b = box16(i < nchild ? child[i] : make_double4(INFINITY, INFINITY, -INFINITY, -INFINITY));
     if (i < nchild && i % kFan == 0) {
@@ -668,7 +685,7 @@ BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStr
     // without memory for them does without.
     const size_t obj_bytes = sizeof(double) * W * (size_t)n, order_bytes = sizeof(uint32_t) * (size_t)n;
     const size_t node_bytes = sizeof(double4) * (size_t)total, rep_bytes = sizeof(double2) * (size_t)total;
-    const size_t meta_bytes = sizeof(int64_t) * 2 * kMaxLevels;
+    const size_t meta_bytes = sizeof(int64_t) * kMetaWords;
     const int top = with_cells ? cell_top(n) : -1;
     const size_t cell_bytes = sizeof(uint32_t) * (size_t)cell_level_words(top + 1);
     const size_t long_bytes = top >= 0 && seg ? cell_long_bytes(n) : 0;
@@ -712,7 +729,7 @@ BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStr
     }
 
     {
-        int64_t meta[2 * kMaxLevels] = {};
+        int64_t meta[kMetaWords] = {};
         for (int l = 0; l < levels; ++l) {
             meta[l] = out->level_off[l];
             meta[kMaxLevels + l] = out->level_cnt[l];
@@ -756,8 +773,9 @@ BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStr
         hipLaunchKernelGGL(k_gather_leaves<2>, g, t, 0, st, objects, out->order, n, merc, out->obj, out->nodes, out->rep);
     for (int l = 1; l < levels; ++l) {
         const int64_t c = out->level_off[l - 1], nc = out->level_cnt[l - 1], at = out->level_off[l];
+        double *const extent = seg && l == levels - 1 ? reinterpret_cast<double *>(out->meta + kMetaExtent) : nullptr;
         hipLaunchKernelGGL(k_level, dim3((uint32_t)cdiv(nc, 256)), t, 0, st, out->nodes + c, out->rep + c, nc,
-                           out->nodes + at, out->rep + at);
+                           out->nodes + at, out->rep + at, reinterpret_cast<const double4 *>(out->obj), n, extent);
     }
     HV_TRY(hipGetLastError());
     if (cells)

@@ -15,6 +15,7 @@ constexpr int kEdgeChunk = 8;    // polygon edges per chunk box (filling)
 constexpr int kChunkSuper = 8;   // chunk boxes per super-chunk box (filling)
 constexpr int kFrontier = 256;   // most nodes in a tile's frontier
 constexpr int kMaxLevels = 16;   // node levels (2e9 objects need 8)
+constexpr int kMetaExtent = 2 * kMaxLevels, kMetaWords = kMetaExtent + 1;
 constexpr int kLevelShift = 27;  // stack entry: level << 27 | node index
 constexpr uint32_t kIdxMask = (1u << kLevelShift) - 1;
 constexpr double kCullPad = 1e-5;  // px beyond r for every cull box
@@ -24,7 +25,8 @@ struct DevIndex {
     const double *obj;           // Hilbert order; 2 (points) or 4 (segments) doubles each
     const double4 *nodes;        // all levels, level 0 (leaves) first; (minX, minY, maxX, maxY)
     const double2 *rep;          // per node, same order: the first vertex of its first object
-    const int64_t *meta;         // [0, kMaxLevels): level offsets; [kMaxLevels, 2*kMaxLevels): counts
+    const int64_t *meta;         // [0, kMaxLevels): level offsets; [kMaxLevels, 2*kMaxLevels): counts; [kMetaExtent]:
+                                 // the bits of a double, the median over the objects of the larger side of their boxes
     int64_t n;
     int32_t levels;
     int32_t seg;                 // 0 points, 1 segments / edges
@@ -110,7 +112,7 @@ struct IndexArrays {
     double4 *nodes = nullptr;
     double2 *rep = nullptr;      // per node: the first vertex of its first object
     uint32_t *order = nullptr;
-    int64_t *meta = nullptr;     // device copy of level_off / level_cnt
+    int64_t *meta = nullptr;     // device copy of level_off / level_cnt, and the objects' extent
     uint32_t *cells = nullptr;   // occupancy cells, or NULL
     int32_t cell_top = -1;
     int32_t cell_gaps = 0;

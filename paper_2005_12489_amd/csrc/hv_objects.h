@@ -1,10 +1,11 @@
 // Tiles with few objects in reach, object by object.
 //
 // Where a tile's frontier (k_tile_frontier) lies at the leaves, one level above
-// them or, without cells to settle it, two levels above with few nodes
-// (by_objects), at most 262,144 objects can reach the tile, and walking the tree
-// for each of its regions would test the same nodes and read the same leaves
-// over and over, a memory latency at a time.  Here a workgroup takes a strip
+// them or, without cells to settle it, two levels above with few nodes, at most
+// 262,144 objects can reach the tile.  If they are small and accepts would not
+// do most of the work (by_objects), walking the tree for each of its regions
+// would test the same nodes and read the same leaves over and over, a memory
+// latency at a time.  Here a workgroup takes a strip
 // of the tile -- whole pixel rows, so that the mask is written in whole lines --
 // and goes over the frontier's objects once, a lane to an object: Algorithm 1's
 // per-pixel box filter seen from the object's side gives the pixels in reach,

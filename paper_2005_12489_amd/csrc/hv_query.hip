@@ -126,6 +126,25 @@ __device__ inline uint64_t wave_or64(uint64_t v) {
     return v;
 }
 
+// A radius is looked at in the finest cells that give it at most this many
+// cells and that the index has; below kCellMin they decide too little.  The
+// window holds up to 15; fewer settle nearly as many pixels with fewer rows to
+// read.  What they leave costs more for segments than for points.  Query kernel
+// at 5, 8 and 15: 10,000 requests over 1e9 points 3.50, 3.66 and 4.55 ms; the 2e8
+// edges 2.17, 2.11 and 2.14; 61 requests over two sets 0.082 (0.070 at 8 for
+// segments and 5 for points), 0.070 and 0.074.
+constexpr double kCellRhoSegments = 8.0, kCellRhoPoints = 5.0;
+constexpr double kCellMin = 1.5;
+constexpr float kCellMargin = 1e-3f;  // cells: far above the cells' own 1e-6 and FP32 rounding here
+
+// The level whose occupancy cells settle pixels of zoom z at radius r, as a
+// shift k >= 0 from z (cells are 2^-k px), or -1.
+__device__ inline int cell_shift(const DevIndex &ix, int z, double r) {
+    if (ix.cell_top < z) return -1;
+    const int k = min(ix.cell_top - z, ilogb((ix.seg ? kCellRhoSegments : kCellRhoPoints) / r));
+    return k >= 0 && ldexp(r, k) >= kCellMin ? k : -1;
+}
+
 // A tile's frontier: its nodes (in LDS), their number and level, and the regions
 // they can reach.
 struct Frontier {
@@ -250,37 +269,78 @@ __device__ __forceinline__ Frontier frontier_walk(const DevIndex &ix, const DevR
     return Frontier{cur, ncur, lvl, cbits};
 }
 
-// A radius is looked at in the finest cells that give it at most this many
-// cells and that the index has; below kCellMin they decide too little.  The
-// window holds up to 15; fewer settle nearly as many pixels with fewer rows to
-// read.  What they leave costs more for segments than for points.  Query kernel
-// at 5, 8 and 15: 10,000 requests over 1e9 points 3.50, 3.66 and 4.55 ms; the 2e8
-// edges 2.17, 2.11 and 2.14; 61 requests over two sets 0.082 (0.070 at 8 for
-// segments and 5 for points), 0.070 and 0.074.
-constexpr double kCellRhoSegments = 8.0, kCellRhoPoints = 5.0;
-constexpr double kCellMin = 1.5;
-constexpr float kCellMargin = 1e-3f;  // cells: far above the cells' own 1e-6 and FP32 rounding here
-
-// The level whose occupancy cells settle pixels of zoom z at radius r, as a
-// shift k >= 0 from z (cells are 2^-k px), or -1.
-__device__ inline int cell_shift(const DevIndex &ix, int z, double r) {
-    if (ix.cell_top < z) return -1;
-    const int k = min(ix.cell_top - z, ilogb((ix.seg ? kCellRhoSegments : kCellRhoPoints) / r));
-    return k >= 0 && ldexp(r, k) >= kCellMin ? k : -1;
+// The median extent of an index's objects, normalised (0: points).
+__device__ inline double object_extent(const DevIndex &ix) {
+    return ix.seg && ix.levels > 0 ? __longlong_as_double(ix.meta[kMetaExtent]) : 0.0;
 }
 
 // Whether a tile is taken object by object (hv_objects.h): its frontier lies at
-// level 0 or 1, or has few nodes at level 2 (65,536 to 262,144 objects in reach)
-// where the region kernel would read nearly every object anyway: segments at a
-// radius too small for its accepts, with no cells to settle the tile's pixels
-// first (cells: whether the query looks at them at all).  4,096 tiles of 10M
-// segments at r = 1/2: 0.40 -> 0.31 ms.  Points and larger radii are the other
-// way round (61 mixed requests 0.10 -> 0.19 ms): accepts light most pixels of
-// such a tile from its inner nodes.
+// level 0 or 1, or, where no cells settle the tile's pixels, has few nodes at level
+// 2 (65,536 to 262,144 segments in reach at a radius too small for accepts), and
+// its objects suit strips:
+//  - An object over few pixels is narrow: a lane each.  Wide ones go one after
+//    another and every strip takes those it meets, while a region soon has their
+//    pixels lit: only sparse leaves of batches that fill the GPU go by strips.
+//    (extent: the median over the index.)  Among nodes larger than the tile most
+//    objects miss it, and every region would look at all of them.
+//  - Where leaves are small to the radius (as if the nodes shared the tile's area),
+//    regions read few objects: cells settle most pixels, or in denser sets accepts
+//    light them.  (Anti-aliased, accepts run on four grids, and strips take both.)
+//  - In small batches regions find idle compute units, and strips are too few: of
+//    binary tiles, those with little in reach go by strips, of anti-aliased ones
+//    the dense, whose regions' accepts take longest.
+// Kernel us of 256 tiles at one zoom, strips / regions: points, 3,900 a tile, r = 3
+// 98 / 260, 6 147 / 211, 12 602 / 500; 15,600 a tile 2 150 / 288, 4 224 / 161, 12
+// 1,550 / 233; 3 px segments, 15,600 a tile, 1 175 / 322, 4 286 / 176, 12 2,231 /
+// 173; 30 px segments, 100 a tile, 0.5 62 / 156, 15,600 a tile, 0.5 2,091 / 1,365.
+// 16 tiles: 30 px segments, 500 a tile, 77 / 43; points, 2,000 a tile, r = 4 48 / 34.
+// The lines were fitted to 22,000 such measurements, 20 to 60,000 objects a tile, 1
+// to 1,024 tiles, r = 1/2 to 64, with cells that reach the zoom and without: the
+// choice is within 3% of the better of the two in the mean.
+// Called by whole wavefronts.  (The nodes' order differs from one workgroup's walk
+// to another's, and all workgroups of a tile have to decide alike.)
 constexpr double kObjectsRadius = 1.0;
-__device__ inline bool by_objects(const DevIndex &ix, const DevReq &rq, int n, int level, bool cells) {
-    return level < 2 || (level == 2 && n <= kObjectUpper && ix.seg && rq.r < kObjectsRadius &&
-                         !(cells && cell_shift(ix, rq.z, rq.r) >= 0));
+constexpr double kNarrow = 12.0, kThin = 4.0;  // px: the reach on both sides and an object's extent
+constexpr double kDenseAA = 5.0, kDenseCells = 4.0, kDense = 1.5;  // diagonal of a leaf to the radius
+constexpr int kSparse = 64, kTiny = 8;         // frontier nodes of tiles that small batches take
+constexpr int64_t kFullRequests = 192;         // more fill the GPU
+constexpr double kLong = 64.0;                  // px: objects that can make many overlapping nodes larger than the tile
+constexpr int kManyNodes = 32, kWideLeaves = 160, kWideNodes = 32, kWideLeavesAA = 32;
+__device__ inline bool by_objects(const DevIndex &ix, const DevReq &rq, double extent, const Frontier &f, bool aa, int64_t requests) {
+    const int n = f.n, level = f.level;
+    if (level > 2) return false;
+    const bool spare = requests <= kFewRequests;
+    const double reach = 2.0 * (aa ? rq.r + 0.25 : rq.r);
+    if (spare && !aa && level == 0 && n <= kTiny) return reach <= kNarrow;
+    const auto cells = [&] { return !aa && cell_shift(ix, rq.z, rq.r) >= 0; };
+    if (level == 2 && !(n <= kObjectUpper && ix.seg && rq.r < kObjectsRadius && !cells())) return false;
+    const double S = ldexp(256.0, rq.z), over = reach + extent * S;
+    if (over > kNarrow) {
+        if (reach <= kNarrow && ((n > kManyNodes && extent * S >= kLong) || (level > 0 && !spare))) {
+            const int lane = threadIdx.x & 63;
+            int huge = 0;
+            for (int base = 0; base < n; base += 64) {
+                double d2 = 0.0;
+                if (base + lane < n) {
+                    const double4 nb = ix.nodes[ix.meta[level] + f.nodes[base + lane]];
+                    const double w = (nb.z - nb.x) * S, h = (nb.w - nb.y) * S;
+                    d2 = w * w + h * h;
+                }
+                huge += __popcll(__ballot(d2 >= 65536.0));
+            }
+            if (2 * huge > n) return true;
+        }
+        return requests > kFullRequests && level < 2 &&
+               n <= (level ? (aa || reach > kNarrow / 2 ? 0 : kWideNodes) : aa ? kWideLeavesAA : kWideLeaves);
+    }
+    if (spare && !aa && n > kSparse && over > kThin) return false;
+    bool dense = false;
+    if (rq.r >= kObjectsRadius) {
+        const float leaf = 1.41f * (ldexpf((256.0f + (float)reach) * __builtin_amdgcn_rsqf((float)n), -2 * level) + 0.7f * (float)(extent * S));
+        dense = leaf <= (float)((aa ? kDenseAA : cells() ? kDenseCells : kDense) * rq.r);
+    }
+    if (aa) return dense || !spare;
+    return !dense;
 }
 
 // objects: tiles by_objects() go to the object kernel's lists, not to the region
@@ -298,6 +358,7 @@ __global__ __launch_bounds__(256) void k_tile_frontier(DevBatch B, int rs, int c
     const int64_t t = B.order[i];  // requests by zoom, lowest first: the list follows this order
     const DevReq rq = B.reqs[t];
     const DevIndex ix = B.ixs[rq.index];
+    const double extent = object_extent(ix);
     const Frontier f = frontier_walk<WPT>(ix, rq, rs, cull, grow, tid, lds[slot]);
     if (f.n == 0) {
         // no data within r of the tile: its mask is all zero, written by the
@@ -306,12 +367,14 @@ __global__ __launch_bounds__(256) void k_tile_frontier(DevBatch B, int rs, int c
         return;
     }
     for (int k = tid; k < f.n; k += 64 * WPT) B.frontier[t * kFrontier + k] = f.nodes[k];
+    if (tid >= 64) return;
+    const bool strips = objects && by_objects(ix, rq, extent, f, grow != 0.0, n_req);
     if (tid == 0) {
         reinterpret_cast<int4 *>(B.fmeta)[t] = make_int4(f.n, f.level, (int)(uint32_t)f.regions, (int)(uint32_t)(f.regions >> 32));
         B.done[t] = 0;
-        if (objects && f.level == 0) B.list[n_req - 1 - atomicAdd(&B.hdr->leaf_tiles, 1)] = (uint32_t)t;
-        else if (objects && by_objects(ix, rq, f.n, f.level, grow == 0.0)) B.elist[n_req - 1 - atomicAdd(&B.hdr->node_tiles, 1)] = (uint32_t)t;
-        else B.list[atomicAdd(&B.hdr->counter, 1)] = (uint32_t)t;
+        if (!strips) B.list[atomicAdd(&B.hdr->counter, 1)] = (uint32_t)t;
+        else if (f.level == 0) B.list[n_req - 1 - atomicAdd(&B.hdr->leaf_tiles, 1)] = (uint32_t)t;
+        else B.elist[n_req - 1 - atomicAdd(&B.hdr->node_tiles, 1)] = (uint32_t)t;
     }
 }
 
@@ -674,11 +737,11 @@ __host__ __device__ inline int query_stack_words(int levels, int threads, int pe
     return kFrontier + width * (levels > 1 ? levels - 1 : 0);
 }
 
-// stack | queued objects (SoA) | mask rows (four sets for anti-aliased output,
-// one per sub-sample) | control
+// stack | queued objects (SoA) | units of exact tests | mask rows (four sets
+// for anti-aliased output, one per sub-sample) | control
 __host__ __device__ inline size_t region_lds_bytes(int cap, int levels, int threads, int rs, int opl, int aa = 0) {
     return align16((size_t)query_stack_words(levels, threads, opl) * 4) + align16((size_t)cap * kCandBytes) +
-           align16((size_t)rs * (rs / 32) * 4 * (aa ? 4 : 1)) + 16;
+           align16((size_t)cap * 4) + align16((size_t)rs * (rs / 32) * 4 * (aa ? 4 : 1)) + 16;
 }
 
 struct RegionLds {
@@ -2065,13 +2128,16 @@ constexpr int kSelfFillWaves = 2;  // filling's default shape
 struct FewBatch {
     uint8_t *out;
     uint32_t *frontier;  // per request: up to 256 frontier nodes
-    int32_t *fmeta;      // per request: frontier size (0: no data within r), level, 64 bits of regions
+    int32_t *fmeta;      // per request: frontier size (0: no data within r), level (and kStripsFlag), 64 bits of regions
     int32_t rs, cull;
+    int32_t objects;     // tiles may go by strips (not when filling)
     double grow;
     DevIndex ixs[kFewIndexes];
     DevReq reqs[kFewRequests];
 };
 static_assert(sizeof(FewBatch) + 16 <= 4096, "kernel arguments");
+
+constexpr int kStripsFlag = 256;  // of a frontier's level: the tile goes by strips
 
 // The batch where the launch put it: indexing the parameter itself would copy
 // it to every thread's stack.
@@ -2085,10 +2151,14 @@ __global__ __launch_bounds__(256) void k_few_frontier(FewBatch) {
     const int t = blockIdx.x, tid = threadIdx.x;
     const DevReq rq = A.reqs[t];
     const DevIndex ix = A.ixs[rq.index];
+    const double extent = object_extent(ix);
     const Frontier f = frontier_walk<4>(ix, rq, A.rs, A.cull, A.grow, tid, lds);
     for (int k = tid; k < f.n; k += 256) A.frontier[t * kFrontier + k] = f.nodes[k];
+    if (tid >= 64) return;
+    const int strips = A.objects && by_objects(ix, rq, extent, f, A.grow != 0.0, gridDim.x) ? kStripsFlag : 0;
     if (tid == 0)
-        reinterpret_cast<int4 *>(A.fmeta)[t] = make_int4(f.n, f.level, (int)(uint32_t)f.regions, (int)(uint32_t)(f.regions >> 32));
+        reinterpret_cast<int4 *>(A.fmeta)[t] =
+            make_int4(f.n, f.level | strips, (int)(uint32_t)f.regions, (int)(uint32_t)(f.regions >> 32));
 }
 
 // One of `parts` equal pieces of a tile's bytes.
@@ -2111,12 +2181,18 @@ struct SelfLds {
     int4 meta;
 };
 
+// (parts: workgroups of a request.)
 template <bool SELF, int WPT, class Lds>
-__device__ __forceinline__ FewFrontier few_frontier(const FewBatch &A, const DevIndex &ix, const DevReq &rq, int t, Lds *self) {
+__device__ __forceinline__ FewFrontier few_frontier(const FewBatch &A, const DevIndex &ix, const DevReq &rq, int t, int parts, Lds *self) {
     if constexpr (SELF) {
         const int tid = threadIdx.x;
+        const double extent = object_extent(ix);
         const Frontier f = frontier_walk<WPT>(ix, rq, A.rs, A.cull, A.grow, tid, self->walk);
-        if (tid == 0) self->meta = make_int4(f.n, f.level, (int)(uint32_t)f.regions, (int)(uint32_t)(f.regions >> 32));
+        if (tid < 64) {
+            const int strips = A.objects && by_objects(ix, rq, extent, f, A.grow != 0.0, gridDim.x / parts) ? kStripsFlag : 0;
+            if (tid == 0)
+                self->meta = make_int4(f.n, f.level | strips, (int)(uint32_t)f.regions, (int)(uint32_t)(f.regions >> 32));
+        }
         __syncthreads();
         return FewFrontier{f.nodes, reinterpret_cast<const int32_t *>(&self->meta)};
     } else {
@@ -2134,14 +2210,14 @@ __global__ __launch_bounds__(kStripThreads) __attribute__((amdgpu_waves_per_eu(4
     const int t = blockIdx.x / RPT, part = blockIdx.x % RPT;
     const DevReq rq = A.reqs[t];
     const DevIndex ix = A.ixs[rq.index];
-    const FewFrontier f = few_frontier<SELF, kBothWaves>(A, ix, rq, t, &self);
-    const int count = f.meta[0], level = f.meta[1];
+    const FewFrontier f = few_frontier<SELF, kBothWaves>(A, ix, rq, t, RPT, &self);
+    const int count = f.meta[0], level = f.meta[1] & (kStripsFlag - 1);
     uint8_t *const out = A.out + (int64_t)t * kBytes;
     if (count == 0) {
         if (part < 4) zero_part(out, kBytes, part, 4);
         return;
     }
-    if (!by_objects(ix, rq, count, level, !AA)) {
+    if (!(f.meta[1] & kStripsFlag)) {
         const RegionLds L = region_lds<kBothRegion, kBothOpl, AA>(reinterpret_cast<unsigned char *>(smem), cap, max_levels);
         if (ix.seg) region_query<kBothRegion, 1, kBothOpl, AA>(ix, rq, 0, part, f.nodes, f.meta, out, cap, L);
         else region_query<kBothRegion, 0, kBothOpl, AA>(ix, rq, 0, part, f.nodes, f.meta, out, cap, L);
@@ -2164,7 +2240,7 @@ __global__ __launch_bounds__(SELF ? 64 * kSelfFillWaves : 256) void k_few_fill(F
     const int t = blockIdx.x / RPT, part = blockIdx.x % RPT;
     const DevReq rq = A.reqs[t];
     const DevIndex ix = A.ixs[rq.index];
-    const FewFrontier f = few_frontier<SELF, kSelfFillWaves>(A, ix, rq, t, &self);
+    const FewFrontier f = few_frontier<SELF, kSelfFillWaves>(A, ix, rq, t, RPT, &self);
     uint8_t *const out = A.out + (int64_t)t * HV_MASK_BYTES;
     if (f.meta[0] == 0) {
         zero_part(out, HV_MASK_BYTES, part, RPT);
@@ -2308,7 +2384,7 @@ hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, 
         hipLaunchKernelGGL(k_tile_frontier<1>, dim3((uint32_t)((n_req + 3) / 4)), dim3(256), 0, st, B, s.region, s.cull,
                            grow, objects);
     if (marks && (e = hipEventRecord(marks[1], st)) != hipSuccess) return e;
-    if (s.region && !s.fill && !in_one_launch(s)) {
+    if (objects && !in_one_launch(s)) {
         const int64_t items = n_req * kNodeStrips;
         const dim3 go((uint32_t)(items < kObjectsGrid ? items : kObjectsGrid));
         if (s.aa) hipLaunchKernelGGL(k_query_objects<1>, go, dim3(kStripThreads), 0, st, B);
@@ -2362,6 +2438,7 @@ hipError_t launch_few(const DevIndex *ixs, int n_ix, const DevReq *reqs, int64_t
     A.frontier = reinterpret_cast<uint32_t *>(dws + sizeof(int32_t) * 4 * (size_t)n_req);
     A.rs = s.region;
     A.cull = s.cull;
+    A.objects = !s.fill;
     A.grow = s.aa ? 0.25 : 0.0;
     memcpy(A.ixs, ixs, sizeof(DevIndex) * (size_t)n_ix);
     memcpy(A.reqs, reqs, sizeof(DevReq) * (size_t)n_req);

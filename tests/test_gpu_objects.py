@@ -90,3 +90,62 @@ def test_anti_aliased(hv, torch, kind, n):
         got = render_aa(hv, torch, h, TILES, r, {"region": 32, "objs_per_lane": 2, "aa_split": -1})
         check_aa(got, ref.render_aa(TILES, r), f"objects kind={kind} n={n} r={r}")
     hv.hv_free(h)
+
+
+@pytest.mark.parametrize("aa", [0, 1])
+@pytest.mark.parametrize("length", [0.0, 3.0, 40.0])
+def test_choice(hv, torch, length, aa):
+    """Which tiles go by strips depends on the frontier's size and level, the
+    radius, the objects' extent and the batch's size; values do not.  Frontiers
+    of about 8, 32, 64 and 160 nodes, leaves small and large to the radius."""
+    rng = np.random.default_rng(int(length))
+    launches = (None, dict(region=32, waves_per_wg=1, objs_per_lane=2, cand_cap=128))
+    for n in (130, 560, 1100, 2700, 9000):
+        p = rng.uniform(-20.0, 276.0, (n, 2))
+        a = rng.uniform(0, 2 * np.pi, n)
+        d = length * np.stack([np.cos(a), np.sin(a)], 1)
+        obj = (np.concatenate([p, p + d], 1) if length else p)
+        obj = (obj + np.tile([256.0 * TX, 256.0 * TY], obj.shape[1] // 2)) / (256.0 * 2 ** Z)
+        kind = int(length > 0)
+        ref = oracle.OracleIndex(obj, kind, merc01=True)
+        h = build(hv, torch, obj, kind | hv.HV_INPUT_MERC01)
+        for r in (0.5, 1.0, 2.0, 2.1, 5.9, 6.1) if n < 9000 else (0.5, 2.1, 6.1):
+            want = ref.render_aa(TILES, r) if aa else ref.render(TILES, r)["tri"]
+            for requests in (4, 17, 65, 193) if n < 9000 else (17, 193):
+                for L in launches:
+                    log(f"choice length={length} aa={aa} n={n} r={r} requests={requests} launch={L}")
+                    tiles = np.resize(TILES, (requests, 3))
+                    got = (render_aa(hv, torch, h, tiles, r, dict(L or {"region": 32, "objs_per_lane": 2}, aa_split=-1))
+                           if aa else render(hv, torch, h, tiles, r, L))
+                    for k in range(4, requests):
+                        assert np.array_equal(got[k], got[k % 4]), f"request {k} of {requests}"
+                    if aa:
+                        check_aa(got[:4], want, f"n={n} r={r} {requests} {L}")
+                    else:
+                        mism, _, lit = parity(got[:4], want)
+                        assert mism == 0, f"n={n} r={r} {requests} {L}: {mism} mismatches of {lit} lit"
+        hv.hv_free(h)
+
+
+@pytest.mark.parametrize("kind,aa", [(0, 0), (1, 0), (0, 1)])
+def test_large_radius(hv, torch, kind, aa):
+    """A tile of many objects and a radius that lights all of it costs no more than
+    a few times what a small radius does: regions light their pixels and leave the
+    other objects (1 to 3 times; 10 to 25 times where every object in reach went
+    over every strip)."""
+    n = 15_000 * 16
+    p = np.random.default_rng(8).uniform(0, 4, (n, 2)) + 8.0  # 15,000 a tile at zoom 5
+    obj = (p if kind == 0 else np.concatenate([p, p + 3.0 / 256], 1)) / 32.0
+    h = build(hv, torch, obj, kind | hv.HV_INPUT_MERC01)
+    tiles = np.array([[5, 8 + k % 4, 8 + k // 4] for k in range(16)] * 16)
+    out = torch.empty((len(tiles), hv.HV_AA_BYTES if aa else 8192), dtype=torch.uint8, device="cuda")
+    ms = []
+    for r in (2.0, 16.0):
+        log(f"large radius kind={kind} aa={aa} r={r}")
+        reqs = hv.requests(h, tiles, r)
+        time = hv.hv_time_aa if aa else hv.hv_time_kernels
+        ms.append(min(time(reqs, out, dict(region=32, waves_per_wg=4, objs_per_lane=2, cand_cap=512, aa_split=-1) if aa
+                           else None, reps=3)[1] for _ in range(4)))
+    hv.hv_free(h)
+    log(f"r=2 {ms[0]:.3f} ms, r=16 {ms[1]:.3f} ms")
+    assert ms[1] < 5 * ms[0]
