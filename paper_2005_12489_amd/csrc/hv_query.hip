@@ -2250,6 +2250,11 @@ __global__ __launch_bounds__(SELF ? 64 * kSelfFillWaves : 256) void k_few_fill(F
     fill_query<RS>(ix, rq, 0, part, f.nodes, f.meta, out, cap, L);
 }
 
+// Beyond the default's four-wave shape, batches of more than this many requests
+// launch the object kernel: alone, one tile of 10k points 54 us a call with it, 45
+// without, 64 of them 51 and 48 (kernels 30 and 50 us).
+constexpr int64_t kOneLaunchRequests = 16;
+
 // Batches of up to this many requests take four wavefronts to a request's frontier.
 constexpr int64_t kWideFrontier = 512;
 
@@ -2377,7 +2382,8 @@ hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, 
     hipError_t e;
     if (marks && (e = hipEventRecord(marks[0], st)) != hipSuccess) return e;
     const double grow = s.aa ? 0.25 : 0.0;
-    const int objects = s.region && !s.fill;
+    // (the object kernel's own launch costs a few tiles more than strips save them)
+    const int objects = s.region && !s.fill && (in_one_launch(s) || n_req > kOneLaunchRequests);
     if (n_req <= kWideFrontier)
         hipLaunchKernelGGL(k_tile_frontier<4>, dim3((uint32_t)n_req), dim3(256), 0, st, B, s.region, s.cull, grow, objects);
     else

@@ -1,0 +1,52 @@
+"""What the library's host code launches, allocates and gives back, seen by a
+program that stands in for the HIP runtime (host/fake_hip.cpp)."""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+PKG = os.path.join(ROOT, "paper_2005_12489_amd")
+
+
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    lib = os.path.join(PKG, "libhv.so")
+    if not os.path.exists(lib):
+        import __graft_entry__
+        __graft_entry__.build()
+    out = str(tmp_path_factory.mktemp("host") / "fake_hip")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-rdynamic", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I" + os.path.join(ROOT, "include"), os.path.join(HERE, "host", "fake_hip.cpp"), lib,
+                    "-Wl,-rpath," + PKG, "-L/opt/rocm/lib", "-Wl,--allow-shlib-undefined", "-lpthread", "-o", out],
+                   check=True)
+    return out
+
+
+def talk(exe, *lines):
+    """The answers to commands: a list of words each."""
+    p = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, timeout=100)
+    assert p.returncode == 0, p.stderr
+    answers = [a.split() for a in p.stdout.splitlines()]
+    assert len(answers) == len(lines), p.stderr
+    return answers
+
+
+def kernels(answer):
+    """[(name, workgroups, threads)] of a call's launches, the call having succeeded."""
+    assert answer[0] == "0"
+    return [(f[0], int(f[1]), int(f[2])) for f in (w.rsplit(":", 3) for w in answer[1:])]
+
+
+def names(answer):
+    return [k[0].split("<")[0] for k in kernels(answer)]
+
+
+@pytest.mark.parametrize("call", ["batch", "aa"])
+def test_small_explicit_batches(exe, call):
+    """In another shape than the default's, a few requests take two launches: the
+    object kernel's costs more than its strips save."""
+    _, a, b = talk(exe, "build p 0 100000", f"{call} p 4 16 32 1 2 128 0", f"{call} p 4 17 32 1 2 128 0")
+    assert names(a) == ["k_tile_frontier", "k_query_region"]
+    assert names(b) == ["k_tile_frontier", "k_query_objects", "k_query_region"]
