@@ -225,7 +225,8 @@ hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, 
 
 
 // Batches that travel in the kernels' arguments: this many requests over this
-// many indexes, in the default shape or filling.
+// many indexes, in the default shape or filling (and no number of workgroups is
+// asked for: their launches have one per piece of a tile).
 constexpr int kFewRequests = 64, kFewIndexes = 4;
 constexpr int kSelfRequests = 32;      // up to this many walk for their frontier in every workgroup
 bool few_requests(const LaunchShape &s, int64_t n_req, int n_ix);

@@ -2424,7 +2424,7 @@ hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, 
 }
 
 bool few_requests(const LaunchShape &s, int64_t n_req, int n_ix) {
-    return n_req <= kFewRequests && n_ix <= kFewIndexes && (s.fill || in_one_launch(s));
+    return n_req <= kFewRequests && n_ix <= kFewIndexes && s.grid == 0 && (s.fill || in_one_launch(s));
 }
 
 // Whether every workgroup walks for its tile's frontier itself.

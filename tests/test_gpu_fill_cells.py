@@ -73,3 +73,27 @@ def test_settled(hv, torch, name):
         log(f"  lit={lit} ambiguous={amb} mismatches={mism}")
         assert mism == 0, f"{L}: {mism} mismatches"
     hv.hv_free(h)
+
+
+@pytest.mark.parametrize("region", [32, 64])
+@pytest.mark.parametrize("waves", [1, 4])
+def test_shapes_of_large_batches(hv, torch, region, waves):
+    """More tiles than a small call's, each its own workgroups and dealt over 7; and a
+    small call dealt over 7: as the oracle, and all alike."""
+    edges, first = polygons("clusters")
+    ref = oracle.OraclePolygons(edges, first, merc01=True)
+    h = hv.hv_polygon_index_build(torch.from_numpy(edges).cuda(), first, hv.HV_INPUT_MERC01)
+    few = np.array([(0, 0, 0), (2, 1, 1), (4, 6, 7), (9, 200, 210), (3, 0, 0)])
+    tri = ref.render(few)["tri"]
+    L = dict(region=region, waves_per_wg=waves, cand_cap=64 * waves)
+    for n, grid in ((5, 7), (66, 0), (66, 7), (130, 3)):
+        log(f"fill region={region} waves={waves} n={n} grid={grid}")
+        tiles = few[np.arange(n) % len(few)]
+        out = torch.full((n, 8192), 0xA5, dtype=torch.uint8, device="cuda")
+        hv.hv_render_fill(h, tiles, out, dict(L, grid_wgs=grid))
+        torch.cuda.synchronize()
+        bits = unpack_masks(out.cpu().numpy())
+        for k in range(n):
+            mism, _, lit = parity(bits[k], tri[k % len(few)])
+            assert mism == 0, f"tile {k} of {n}, grid {grid}: {mism} mismatches of {lit} lit"
+    hv.hv_free(h)

@@ -50,3 +50,13 @@ def test_small_explicit_batches(exe, call):
     _, a, b = talk(exe, "build p 0 100000", f"{call} p 4 16 32 1 2 128 0", f"{call} p 4 17 32 1 2 128 0")
     assert names(a) == ["k_tile_frontier", "k_query_region"]
     assert names(b) == ["k_tile_frontier", "k_query_objects", "k_query_region"]
+
+
+@pytest.mark.parametrize("call,index,shape", [("batch", "build p 0 100000", "32 4 2 512"), ("aa", "build p 1 100000", "32 4 2 512"),
+                                              ("fill", "polygons p 30000", "32 2 2 128"), ("fill", "polygons p 30000", "64 4 2 256")])
+def test_asked_for_workgroups(exe, call, index, shape):
+    """A persistent kernel of grid_wgs workgroups has that many, in small calls too."""
+    for n in (1, 40, 64, 65):
+        _, a, b = talk(exe, index, f"{call} p 4 {n} {shape} 7", f"{call} p 4 {n} {shape} 0")
+        assert kernels(a)[-1][1] == 7, f"{n} requests: {kernels(a)}"
+        assert kernels(b)[-1][1] >= 4 * n, f"{n} requests: {kernels(b)}"
