@@ -184,6 +184,17 @@ thread_local HostStage t_stage;
 // into child tiles and one-pass requests
 thread_local HostStage t_stage_b, t_stage_map;
 
+// A stream-ordered allocation on the calling thread's stream; where memory is
+// short, again without what is kept for coming builds.
+hipError_t stream_alloc(unsigned char **p, size_t bytes) {
+    hipError_t e = hipMallocAsync((void **)p, bytes, t_stream);
+    if (e == hipErrorOutOfMemory && hv::device_trim()) {
+        (void)hipGetLastError();
+        e = hipMallocAsync((void **)p, bytes, t_stream);
+    }
+    return e;
+}
+
 // Copies the staged workspace to a fresh stream-ordered device allocation
 // and launches the query; the allocation is released in stream order.  A batch
 // of few requests needs no copy.
@@ -193,7 +204,7 @@ int run_batch(const hv::DevIndex *ixs, int n_ix, int max_levels, const hv::DevRe
     if (hv::few_requests(shape, n_req, n_ix)) {
         unsigned char *dws = nullptr;
         const size_t bytes = hv::few_bytes(shape, n_req);
-        hipError_t e = bytes ? hipMallocAsync((void **)&dws, bytes, t_stream) : hipSuccess;
+        hipError_t e = bytes ? stream_alloc(&dws, bytes) : hipSuccess;
         if (e != hipSuccess) return hip_status(e, who);
         e = hv::launch_few(ixs, n_ix, reqs, n_req, out, dws, max_levels, shape, t_stream, marks);
         const hipError_t ef = dws ? hipFreeAsync(dws, t_stream) : hipSuccess;
@@ -206,7 +217,7 @@ int run_batch(const hv::DevIndex *ixs, int n_ix, int max_levels, const hv::DevRe
     if (e != hipSuccess) return hip_status(e, who);
     hv::stage_host(w, ixs, n_ix, reqs, n_req, out, st.p);
     unsigned char *dws = nullptr;
-    e = hipMallocAsync((void **)&dws, w.total, t_stream);
+    e = stream_alloc(&dws, w.total);
     if (e != hipSuccess) return hip_status(e, who);
     e = hipMemcpyAsync(dws, st.p, w.staged_bytes(), hipMemcpyHostToDevice, t_stream);
     if (e == hipSuccess) e = hipEventRecord(st.ev, t_stream);
@@ -765,8 +776,7 @@ int run_aa(const BatchPlan &p, int64_t n, uint8_t *out, const hv::LaunchShape &s
     hipError_t e = t_stage_map.acquire(map_bytes);
     if (e != hipSuccess) return hip_status(e, who);
     std::memcpy(t_stage_map.p, a.map.data(), map_bytes);
-    if ((e = hipMallocAsync((void **)&tmp, up(kid_bytes) + up(whole_bytes) + map_bytes, t_stream)) != hipSuccess)
-        return hip_status(e, who);
+    if ((e = stream_alloc(&tmp, up(kid_bytes) + up(whole_bytes) + map_bytes)) != hipSuccess) return hip_status(e, who);
     uint8_t *kids = tmp, *whole = tmp + up(kid_bytes);
     int32_t *map = reinterpret_cast<int32_t *>(tmp + up(kid_bytes) + up(whole_bytes));
     int rc = HV_OK;
@@ -1123,6 +1133,10 @@ hv_batcher *hv_batcher_create(int64_t max_requests, int32_t max_indexes, int32_t
         if (e == hipSuccess) {
             std::memset(s.host, 0, b->w.staged_bytes());
             e = hipMalloc((void **)&s.dev, b->w.total);
+            if (e == hipErrorOutOfMemory && hv::device_trim()) {
+                (void)hipGetLastError();
+                e = hipMalloc((void **)&s.dev, b->w.total);
+            }
         }
         if (e == hipSuccess) e = hipEventCreateWithFlags(&s.done, hipEventDisableTiming);
         for (int k = 0; k < n_shapes && e == hipSuccess; ++k) {

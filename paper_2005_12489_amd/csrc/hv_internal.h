@@ -98,11 +98,13 @@ struct BuildResult {
 // Device memory for indexes and their builds.  hipFree takes about 29 ms per
 // GB on MI355X, so blocks given back are kept, up to kPoolBytes in all, for
 // the next request that they fit; beyond that the oldest are freed, and all of
-// them before an allocation fails.  device_release waits for the device, as
-// hipFree does.  Safe from several threads; a block stays on its device.
+// them before an allocation of the library fails (device_trim, which returns
+// whether there were any).  device_release waits for the device, as hipFree does.
+// Safe from several threads; a block stays on its device.
 constexpr size_t kPoolBytes = size_t(1) << 30;
 hipError_t device_acquire(void **p, size_t bytes, size_t *held);
 void device_release(void *p, size_t held);
+bool device_trim();
 
 // Device arrays owned by one index (freed by free_index_arrays).
 struct IndexArrays {

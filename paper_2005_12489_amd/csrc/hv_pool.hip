@@ -23,7 +23,18 @@ void drop(size_t k) {
     g_free.erase(g_free.begin() + (std::ptrdiff_t)k);
 }
 
+bool trim() {  // (g_mu held)
+    const bool any = !g_free.empty();
+    while (!g_free.empty()) drop(g_free.size() - 1);
+    return any;
+}
+
 }  // namespace
+
+bool device_trim() {
+    std::lock_guard<std::mutex> g(g_mu);
+    return trim();
+}
 
 hipError_t device_acquire(void **p, size_t bytes, size_t *held) {
     *p = nullptr;
@@ -47,9 +58,8 @@ hipError_t device_acquire(void **p, size_t bytes, size_t *held) {
     }
     const size_t want = bytes ? bytes : 1;
     e = hipMalloc(p, want);
-    if (e != hipSuccess && !g_free.empty()) {
+    if (e != hipSuccess && trim()) {
         (void)hipGetLastError();
-        while (!g_free.empty()) drop(g_free.size() - 1);
         e = hipMalloc(p, want);
     }
     if (e == hipSuccess) *held = want;

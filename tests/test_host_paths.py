@@ -60,3 +60,14 @@ def test_asked_for_workgroups(exe, call, index, shape):
         _, a, b = talk(exe, index, f"{call} p 4 {n} {shape} 7", f"{call} p 4 {n} {shape} 0")
         assert kernels(a)[-1][1] == 7, f"{n} requests: {kernels(a)}"
         assert kernels(b)[-1][1] >= 4 * n, f"{n} requests: {kernels(b)}"
+
+
+@pytest.mark.parametrize("call", ["batch p 4 3000", "batch p 4 50", "aa p 4 2000", "aa p 0 100 32 1 2 128 0", "batcher b 20000"])
+def test_kept_memory_makes_way(exe, call):
+    """Memory kept for the next build is given back before an allocation of a call
+    that renders, or of a batcher, fails."""
+    lines = ["build p 0 2000000", "build q 1 6000000", "free q", "memory"]
+    held = int(talk(exe, *lines)[-1][1])
+    answers = talk(exe, *lines, f"limit {held + 1000}", call, "limit 1", call)
+    assert answers[5][0] == "0"
+    assert answers[7][0] != "0"
