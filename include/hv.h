@@ -108,10 +108,15 @@ int hv_render_tiles(const hv_index *index, const hv_tile *tiles, int64_t n_tiles
                     const hv_style *style, uint8_t *out_masks);
 
 /* Release an index and its device memory (NULL-safe).  The caller must make
- * sure no render using it is still in flight.  Blocks of up to 512 MB are
+ * sure no render using it is still in flight.  Blocks of up to 512 MiB are
  * kept for the next build, at most 1 GiB in the process; they are given back
- * before an allocation of the library fails. */
+ * by hv_trim and before an allocation of the library fails. */
 void hv_free(hv_index *index);
+
+/* Give back the device memory kept by hv_free and by builds, to other
+ * allocators of the device (those of the calling process cannot have it
+ * otherwise).  Safe while other threads build, render and free. */
+void hv_trim(void);
 
 /* Message describing the calling thread's most recent error ("" if none). */
 const char *hv_last_error(void);

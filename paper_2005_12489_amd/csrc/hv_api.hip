@@ -426,6 +426,8 @@ void hv_free(hv_index *index) {
     delete index;
 }
 
+void hv_trim(void) { (void)hv::device_trim(); }
+
 hv_index *hv_polygon_index_build(const double *edges, int64_t n, const int64_t *first, int64_t npoly, int flags) {
     if ((flags & ~HV_INPUT_MERC01) != 0) {
         fail(HV_EINVAL, "flags must be 0 or HV_INPUT_MERC01");

@@ -41,7 +41,7 @@ HV_MAX_ZOOM = 22
 HV_NOALLOC_MAX_REQUESTS = 4096
 HV_NOALLOC_MAX_INDEXES = 16
 
-SYMBOLS = ("hv_index_build", "hv_render_tiles", "hv_render_tiles_ex", "hv_free", "hv_last_error",
+SYMBOLS = ("hv_index_build", "hv_render_tiles", "hv_render_tiles_ex", "hv_free", "hv_trim", "hv_last_error",
            "hv_set_stream", "hv_index_info", "hv_index_read", "hv_render_batch", "hv_batcher_create",
            "hv_batcher_run", "hv_batcher_latency", "hv_batcher_free", "hv_autotune", "hv_tuned_launch",
            "hv_time_kernels", "hv_time_aa", "hv_time_fill", "hv_render_batch_aa", "hv_polygon_index_build", "hv_render_fill",
@@ -94,6 +94,8 @@ lib.hv_render_tiles_ex.argtypes = [_P, _P, ctypes.c_int64, ctypes.POINTER(hv_sty
                                    ctypes.POINTER(hv_launch)]
 lib.hv_free.restype = None
 lib.hv_free.argtypes = [_P]
+lib.hv_trim.restype = None
+lib.hv_trim.argtypes = []
 lib.hv_last_error.restype = ctypes.c_char_p
 lib.hv_last_error.argtypes = []
 lib.hv_set_stream.restype = ctypes.c_int
@@ -224,6 +226,11 @@ def hv_render_tiles_ex(index: int, tiles, style, out_masks, launch: hv_launch | 
 
 def hv_free(index: int | None) -> None:
     lib.hv_free(index)
+
+
+def hv_trim() -> None:
+    """Gives the device memory kept for the next builds back, e.g. to torch's allocator."""
+    lib.hv_trim()
 
 
 def hv_index_info(index: int) -> dict:

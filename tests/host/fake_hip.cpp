@@ -150,6 +150,7 @@ int main() {
         };
         hv_launch l;
         if (cmd == "limit") in >> limit_bytes;
+        else if (cmd == "trim") hv_trim();
         else if (cmd == "memory") extra << " " << live_bytes << " " << most_bytes;
         else if (cmd == "build") {  // build NAME KIND N
             int kind;

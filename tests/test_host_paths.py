@@ -71,3 +71,20 @@ def test_kept_memory_makes_way(exe, call):
     answers = talk(exe, *lines, f"limit {held + 1000}", call, "limit 1", call)
     assert answers[5][0] == "0"
     assert answers[7][0] != "0"
+
+
+def test_trim(exe):
+    """hv_trim gives back what hv_free kept, and nothing of what is in use."""
+    a = talk(exe, "build p 0 200000", "trim", "memory", "build q 1 3000000", "polygons r 300000", "free q", "free r",
+             "memory", "trim", "memory", "batch p 4 100", "free p", "trim", "memory")
+    assert int(a[7][1]) > int(a[2][1])
+    assert a[9][1] == a[2][1]
+    assert a[10][0] == "0" and a[13][1] == "0"
+
+
+def test_pool_threads(exe):
+    """Threads that build and free at once: every block is given out once, and all
+    of them, at most 1 GiB kept, can be given back."""
+    a = talk(exe, "threads 8", "memory", "trim", "memory")
+    assert a[0] == ["0"]
+    assert 0 < int(a[1][1]) <= 1 << 30 and a[3][1] == "0"
