@@ -186,7 +186,7 @@ typedef struct {
     int32_t key_bits;       /* Hilbert order used for sorting (bits per axis) */
     int32_t pad;
     double root[4];         /* data bounding box: min X, min Y, max X, max Y (normalised) */
-    int64_t device_bytes;   /* device memory held by the index */
+    int64_t device_bytes;   /* device memory held by the index (blocks reused from hv_free in full) */
     double build_ms;        /* wall time of hv_index_build */
 } hv_info;
 

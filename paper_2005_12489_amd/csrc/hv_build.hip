@@ -627,10 +627,7 @@ BuildResult build_polygons(const double *edges, int64_t n, const int64_t *first,
     if (cells) {
         tree->cell_top = found.outside ? -1 : top;
         tree->cell_gaps = found.gaps;
-        tree->device_bytes += (int64_t)cell_bytes;
     }
-    tree->device_bytes += (int64_t)(sizeof(double) * 4 * (size_t)n + sizeof(int64_t) * (size_t)(npoly + 1) +
-                                    sizeof(float4) * (size_t)(nchunk + nsuper));
     return r;
 }
 
@@ -720,7 +717,6 @@ BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStr
         out->cells = reinterpret_cast<uint32_t *>(block + o_cells);
         out->cell_top = top;
     }
-    out->device_bytes = (int64_t)(obj_bytes + order_bytes + node_bytes + rep_bytes + (cells ? cell_bytes : 0));
     Scratch small;
     unsigned char *work = reinterpret_cast<unsigned char *>(out->obj);
     if (sort.bytes > obj_bytes) {

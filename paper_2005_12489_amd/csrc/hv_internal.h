@@ -109,7 +109,7 @@ bool device_trim();
 // Device arrays owned by one index (freed by free_index_arrays).
 struct IndexArrays {
     void *block = nullptr;       // holds them all
-    size_t block_bytes = 0;
+    size_t block_bytes = 0;      // (up to twice what they take, where a kept block was reused)
     double *obj = nullptr;
     double4 *nodes = nullptr;
     double2 *rep = nullptr;      // per node: the first vertex of its first object
@@ -125,7 +125,6 @@ struct IndexArrays {
     int64_t level_off[kMaxLevels] = {};
     int64_t level_cnt[kMaxLevels] = {};
     int64_t nodes_total = 0;
-    int64_t device_bytes = 0;
 };
 
 // Device arrays of a polygon index beyond its box tree (freed by

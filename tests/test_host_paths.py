@@ -88,3 +88,11 @@ def test_pool_threads(exe):
     a = talk(exe, "threads 8", "memory", "trim", "memory")
     assert a[0] == ["0"]
     assert 0 < int(a[1][1]) <= 1 << 30 and a[3][1] == "0"
+
+
+@pytest.mark.parametrize("first,then", [("build a 1 4000000", "build b 1 2500000"), ("polygons a 600000", "polygons b 390000")])
+def test_device_bytes(exe, first, then):
+    """hv_info's device_bytes are what indexes hold, also in reused blocks."""
+    a = talk(exe, "build p 0 300000", first, "trim", "memory", "free a", then, "trim", "memory")
+    assert int(a[0][1]) + int(a[1][1]) == int(a[3][1])
+    assert int(a[0][1]) + int(a[5][1]) == int(a[7][1])
