@@ -649,7 +649,7 @@ int hv_index_info(const hv_index *index, hv_info *info) {
     info->key_bits = index->a.key_bits;
     info->pad = 0;
     for (int k = 0; k < 4; ++k) info->root[k] = index->root[k];
-    info->device_bytes = (int64_t)(index->a.block_bytes + index->p.block_bytes);
+    info->device_bytes = (int64_t)(index->a.block_bytes + index->a.cell_bytes + index->p.block_bytes);
     info->build_ms = index->build_ms;
     return HV_OK;
 }

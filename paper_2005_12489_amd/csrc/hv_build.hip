@@ -514,6 +514,12 @@ struct Scratch {
     }
 };
 
+// A block of their own for the cells, which are given back if they turn out to
+// be of no use.  (They are an aid only: without memory for them, none.)
+void acquire_cells(IndexArrays *a, size_t bytes) {
+    if (device_acquire(reinterpret_cast<void **>(&a->cells), bytes, &a->cell_bytes) != hipSuccess) (void)hipGetLastError();
+}
+
 BuildResult hip_fail(hipError_t e) {
     (void)hipGetLastError();
     if (e == hipErrorOutOfMemory) return {HV_ENOMEM, "out of device memory"};
@@ -588,16 +594,9 @@ BuildResult build_polygons(const double *edges, int64_t n, const int64_t *first,
         const uint32_t p = order[(size_t)k];
         sorted_first[(size_t)k + 1] = sorted_first[(size_t)k] + (first[p + 1] - first[p]);
     }
-    // (the cells are an aid only: without memory for them, none)
     const int top = cell_top(n);
-    const size_t bare = index.bytes, cell_bytes = 2 * sizeof(uint32_t) * (size_t)cell_level_words(top + 1);
-    const size_t o_cells = index.take(cell_bytes);
-    bool cells = top >= 0;
-    if (cells && device_acquire(&poly->block, index.bytes, &poly->block_bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        cells = false;
-    }
-    if (!cells && (e = device_acquire(&poly->block, bare, &poly->block_bytes)) != hipSuccess) return bail(e);
+    if ((e = device_acquire(&poly->block, index.bytes, &poly->block_bytes)) != hipSuccess) return bail(e);
+    if (top >= 0) acquire_cells(tree, 2 * sizeof(uint32_t) * (size_t)cell_level_words(top + 1));
     unsigned char *const block = static_cast<unsigned char *>(poly->block);
     poly->edges = reinterpret_cast<double *>(block + o_edges);
     poly->first = reinterpret_cast<int64_t *>(block + o_first);
@@ -617,21 +616,30 @@ BuildResult build_polygons(const double *edges, int64_t n, const int64_t *first,
     }
     if ((e = hipGetLastError()) != hipSuccess) return bail(e);
     CellFlags found = {};
-    if (cells) {
-        tree->cells = reinterpret_cast<uint32_t *>(block + o_cells);
+    if (tree->cells) {
         if ((e = build_poly_cells(poly->edges, poly->first, tree->obj, npoly, top, tree->cells, flg, st)) != hipSuccess)
             return bail(e);
         if ((e = hipMemcpyAsync(&found, flg, sizeof found, hipMemcpyDeviceToHost, st)) != hipSuccess) return bail(e);
     }
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return bail(e);
-    if (cells) {
-        tree->cell_top = found.outside ? -1 : top;
+    if (found.outside) {
+        free_cells(tree);
+    } else if (tree->cells) {
+        tree->cell_top = top;
         tree->cell_gaps = found.gaps;
     }
     return r;
 }
 
+void free_cells(IndexArrays *a) {
+    if (a->cells) device_release(a->cells, a->cell_bytes);
+    a->cells = nullptr;
+    a->cell_bytes = 0;
+    a->cell_top = -1;
+}
+
 void free_index_arrays(IndexArrays *a) {
+    free_cells(a);
     if (a->block) device_release(a->block, a->block_bytes);
     *a = IndexArrays{};
 }
@@ -677,20 +685,16 @@ BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStr
     const int64_t ncount = 256 * nb;
     const int64_t npart = cdiv(ncount, kRTile);
 
-    // All arrays of the index in one block (a free costs 29 ms per GB here,
-    // whatever the number of blocks); the cells are an aid only, and an index
-    // without memory for them does without.
+    // All arrays of the index but the cells in one block.
     const size_t obj_bytes = sizeof(double) * W * (size_t)n, order_bytes = sizeof(uint32_t) * (size_t)n;
     const size_t node_bytes = sizeof(double4) * (size_t)total, rep_bytes = sizeof(double2) * (size_t)total;
     const size_t meta_bytes = sizeof(int64_t) * kMetaWords;
     const int top = with_cells ? cell_top(n) : -1;
-    const size_t cell_bytes = sizeof(uint32_t) * (size_t)cell_level_words(top + 1);
     const size_t long_bytes = top >= 0 && seg ? cell_long_bytes(n) : 0;
     Carve index;
     const size_t o_obj = index.take(obj_bytes), o_order = index.take(order_bytes), o_nodes = index.take(node_bytes);
     const size_t o_rep = index.take(rep_bytes), o_meta = index.take(meta_bytes);
-    const size_t o_flags = index.take(sizeof(CellFlags)), bare = index.bytes;
-    const size_t o_cells = index.take(cell_bytes);
+    const size_t o_flags = index.take(sizeof(CellFlags));
     // The sort works in the objects' own array, which is only written after
     // it; sets too small for that (the arrays are aligned) get scratch of their own,
     // as does the list of segments over many cells.
@@ -699,13 +703,12 @@ BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStr
     const size_t o_v1 = sort.take(order_bytes), o_counts = sort.take(sizeof(uint32_t) * (size_t)ncount);
     const size_t o_part = sort.take(sizeof(uint32_t) * (size_t)npart);
     Scratch scratch;
-    if (top >= 0 && (scratch.alloc(long_bytes) != hipSuccess ||
-                     device_acquire(&out->block, index.bytes, &out->block_bytes) != hipSuccess)) {
-        (void)hipGetLastError();
-        out->block = nullptr;
+    HV_TRY(device_acquire(&out->block, index.bytes, &out->block_bytes));
+    if (top >= 0) {
+        if (scratch.alloc(long_bytes) == hipSuccess) acquire_cells(out, sizeof(uint32_t) * (size_t)cell_level_words(top + 1));
+        else (void)hipGetLastError();
     }
-    const bool cells = top >= 0 && out->block;
-    if (!out->block) HV_TRY(device_acquire(&out->block, bare, &out->block_bytes));
+    const bool cells = out->cells != nullptr;
     unsigned char *const block = static_cast<unsigned char *>(out->block);
     out->obj = reinterpret_cast<double *>(block + o_obj);
     out->order = reinterpret_cast<uint32_t *>(block + o_order);
@@ -713,10 +716,7 @@ BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStr
     out->rep = reinterpret_cast<double2 *>(block + o_rep);
     out->meta = reinterpret_cast<int64_t *>(block + o_meta);
     CellFlags *const flags = reinterpret_cast<CellFlags *>(block + o_flags);
-    if (cells) {
-        out->cells = reinterpret_cast<uint32_t *>(block + o_cells);
-        out->cell_top = top;
-    }
+    if (cells) out->cell_top = top;
     Scratch small;
     unsigned char *work = reinterpret_cast<unsigned char *>(out->obj);
     if (sort.bytes > obj_bytes) {
@@ -780,7 +780,7 @@ BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStr
     HV_TRY(hipMemcpyAsync(&found, flags, sizeof found, hipMemcpyDeviceToHost, st));
     HV_TRY(hipStreamSynchronize(st));
     out->cell_gaps = found.gaps;
-    if (found.outside) out->cell_top = -1;
+    if (found.outside) free_cells(out);
     if (found.bad) {
         free_index_arrays(out);
         return {HV_EINVAL, "objects hold a non-finite coordinate, |lon| > 180 or |lat| > 90"};

@@ -108,14 +108,15 @@ bool device_trim();
 
 // Device arrays owned by one index (freed by free_index_arrays).
 struct IndexArrays {
-    void *block = nullptr;       // holds them all
+    void *block = nullptr;       // holds them all but the cells
     size_t block_bytes = 0;      // (up to twice what they take, where a kept block was reused)
     double *obj = nullptr;
     double4 *nodes = nullptr;
     double2 *rep = nullptr;      // per node: the first vertex of its first object
     uint32_t *order = nullptr;
     int64_t *meta = nullptr;     // device copy of level_off / level_cnt, and the objects' extent
-    uint32_t *cells = nullptr;   // occupancy cells, or NULL
+    uint32_t *cells = nullptr;   // occupancy cells (a block), or NULL
+    size_t cell_bytes = 0;
     int32_t cell_top = -1;
     int32_t cell_gaps = 0;
     int64_t n = 0;
@@ -155,6 +156,7 @@ void free_poly_arrays(PolyArrays *p);
 BuildResult build_index(const double *objects, int kind_flags, int64_t n, hipStream_t stream,
                         IndexArrays *out, bool with_cells);
 void free_index_arrays(IndexArrays *a);
+void free_cells(IndexArrays *a);
 
 struct LaunchShape {
     int block;        // 8 or 16

@@ -123,3 +123,33 @@ def test_many_long_among_short_segments(hv, torch):
             mism, _, lit = parity(render(hv, torch, h, tiles, r, L), tri)
             assert mism == 0, f"r={r} {L}: {mism} mismatches of {lit} lit"
     hv.hv_free(h)
+
+
+@pytest.mark.parametrize("kind", [0, 1, 2])
+def test_unused_cells_are_given_back(hv, torch, kind):
+    """An index with an object beyond the world cannot use its cells, and does not keep
+    their memory: the finest level has 4^k cells, as many as 32 for each of 2^18 objects
+    allow, so 2^22 (bits)."""
+    n = 1 << 18
+    rng = np.random.default_rng(kind)
+    p = rng.uniform(0.2, 0.8, (n, 2))
+    d = 1e-4 * rng.normal(size=(n, 2))
+    obj = p if kind == 0 else np.concatenate([p, p + d], 1)
+    held = []
+    for outside in (False, True):
+        if outside:
+            obj[:3] += 1.0
+        log(f"unused cells kind={kind} outside={outside}")
+        hv.hv_trim()  # (no reused block)
+        if kind == 2:
+            ring = obj.reshape(-1, 4, 4).copy()  # rings of four edges
+            ring[:, :, 2:] = np.roll(ring[:, :, :2], -1, axis=1)
+            first = np.arange(0, n + 1, 4, dtype=np.int64)
+            t = torch.from_numpy(ring.reshape(-1, 4)).cuda()
+            h = hv.hv_polygon_index_build(t, first, hv.HV_INPUT_MERC01)
+        else:
+            h = build(hv, torch, obj, kind | hv.HV_INPUT_MERC01)
+        held.append(hv.hv_index_info(h)["device_bytes"])
+        hv.hv_free(h)
+    log(f"held {held}")
+    assert held[0] - held[1] >= (1 << 22) // 8

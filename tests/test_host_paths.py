@@ -96,3 +96,20 @@ def test_device_bytes(exe, first, then):
     a = talk(exe, "build p 0 300000", first, "trim", "memory", "free a", then, "trim", "memory")
     assert int(a[0][1]) + int(a[1][1]) == int(a[3][1])
     assert int(a[0][1]) + int(a[5][1]) == int(a[7][1])
+
+
+@pytest.mark.parametrize("build", ["build p 0 2000000", "build p 1 2000000", "polygons p 600000"])
+def test_without_memory_for_cells(exe, build):
+    """The occupancy cells are an aid: an index is built without them where their
+    block does not fit, and holds what it would otherwise less that block."""
+    with_cells, memory = talk(exe, build, "memory")
+    most, whole = int(memory[2]), int(with_cells[1])
+    held = {whole}
+    for limit in range(most - 1, whole // 2, -max(1, most // 97)):
+        a = talk(exe, f"limit {limit}", build, "trim", "memory")
+        if a[1][0] != "0":
+            assert a[3][1] == "0"  # and nothing is left of a failed build
+            break
+        held.add(int(a[1][1]))
+        assert a[1][1] == a[3][1]
+    assert len(held) == 2, held
