@@ -947,23 +947,30 @@ int hv_autotune(const hv_request *sample, int64_t n, uint8_t *scratch_masks, hv_
     if ((rc = validate_out(scratch_masks))) return rc;
     // Candidate shapes, all in region mode: side, waves, objects per lane,
     // queue, and the cull depth in the last field (0 = 256 frontier nodes).
-    // The default's three shapes come first (queues at their minimum, 64 x
-    // waves x objects per lane: larger queues cost occupancy); grid 2^20
-    // gives each region its own workgroup, which helps batches whose regions
-    // differ widely in cost; a queue of 64 or 96 x waves (a leaf step's
-    // objects taken 64 x waves at a time) frees LDS for more workgroups per
-    // CU.
+    // The default's three shapes come first (two and four waves with queues at
+    // 64 x waves x objects per lane: larger ones cost occupancy).  A queue of 64
+    // or 96 for one wave (a leaf step's objects taken in two parts) frees LDS for
+    // more workgroups per CU.  With one wave, grid 0 gives each region its own
+    // workgroup, which helps batches whose regions differ widely in cost;
+    // kPersistent is the grid that two and four waves have.
     // One wavefront per pixel block (region 0) is
     // not a candidate: it never won, and without the accept pass a single
     // run of it on a few dense low-zoom tiles can take seconds.
-    static const hv_launch cands[] = {
-        {0, 128, 1, 0, 32, 2, 0}, {0, 256, 2, 0, 32, 2, 0}, {0, 512, 4, 0, 32, 2, 0}, {0, 128, 1, 0, 32, 2, 128},
-        {0, 128, 1, 0, 32, 2, 32}, {0, 512, 4, 0, 32, 2, 32}, {0, 128, 1, 1 << 20, 32, 2, 0},
-        {0, 96, 1, 1 << 20, 32, 2, 0}, {0, 64, 1, 1 << 20, 32, 2, 0}, {0, 96, 1, 0, 32, 2, 0}, {0, 64, 1, 0, 32, 2, 0},
+    constexpr int kPersistent = -1;
+    hv_launch cands[] = {
+        {0, 96, 1, 0, 32, 2, 0}, {0, 256, 2, 0, 32, 2, 0}, {0, 512, 4, 0, 32, 2, 0}, {0, 128, 1, 0, 32, 2, 0},
+        {0, 128, 1, 0, 32, 2, 128}, {0, 128, 1, 0, 32, 2, 32}, {0, 512, 4, 0, 32, 2, 32}, {0, 64, 1, 0, 32, 2, 0},
+        {0, 128, 1, kPersistent, 32, 2, 0}, {0, 96, 1, kPersistent, 32, 2, 0}, {0, 64, 1, kPersistent, 32, 2, 0},
         {0, 64, 1, 0, 32, 1}, {0, 256, 1, 0, 32, 4},
         {0, 128, 2, 0, 32, 1}, {0, 256, 4, 0, 32, 1}, {0, 128, 1, 0, 64, 2}, {0, 256, 2, 0, 64, 2},
         {0, 256, 4, 0, 64, 1}, {0, 512, 4, 0, 64, 2},
     };
+    for (hv_launch &c : cands) {
+        if (c.grid_wgs != kPersistent) continue;
+        c.grid_wgs = 0;
+        hv::LaunchShape shape;
+        if (!resolve_shape(&c, p.max_levels, &shape, n, n)) c.grid_wgs = hv::persistent_grid(shape, p.max_levels);
+    }
     // events around the two kernels only: staging and the workspace
     // allocation are the same for every shape and only add noise
     hipEvent_t m[3] = {nullptr, nullptr, nullptr};

@@ -113,3 +113,21 @@ def test_without_memory_for_cells(exe, build):
         held.add(int(a[1][1]))
         assert a[1][1] == a[3][1]
     assert len(held) == 2, held
+
+
+def test_autotune_candidates(exe):
+    """Every shape is timed once (a first run and three on the whole sample), but for
+    those that differ in the cull depth, which the launch does not show; one wave with
+    a workgroup to a region and persistent; and of equals the default is taken."""
+    _, a = talk(exe, "build p 0 3000000", "tune p 6 4096")
+    assert a[:2] == ["0", "32:1:2:96:0"]
+    count = {}
+    for w in a[2:]:
+        if "region" in w or "both" in w:
+            count[w] = count.get(w, 0) + 1
+    whole = {w: c for w, c in count.items() if int(w.rsplit(":", 3)[1]) > 128 * 64}  # (not the parts of the sample)
+    assert sorted(set(whole.values())) == [4, 8, 12], whole
+    assert list(whole.values()).count(12) == 1 and list(whole.values()).count(8) == 1, whole
+    one_wave = [w.rsplit(":", 3) for w in whole if w.rsplit(":", 3)[2] == "64" and "<32,2," in w]
+    lds = sorted({f[3] for f in one_wave})
+    assert len(lds) == 3 and len(one_wave) == 6, one_wave  # queues of 64, 96, 128, two grids each
