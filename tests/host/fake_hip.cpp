@@ -175,20 +175,23 @@ int main() {
             in >> name;
             hv_free(ix[name]);
         } else if (cmd == "batch" || cmd == "aa" || cmd == "tune" || cmd == "run" || cmd == "fill") {
-            // CMD NAME Z N [shape]: N requests at zoom Z (run NAME BATCHER Z N)
+            // CMD NAME Z N [shape]: N requests at zoom Z (run NAME BATCHER Z N K: K of
+            // them there, the others at zoom 22)
             std::string b;
             int z;
-            int64_t n;
+            int64_t n, there;
             in >> name;
             if (cmd == "run") in >> b;
             in >> z >> n;
-            hv_launch *const L = shape(&l);
+            there = n;
+            if (cmd == "run") in >> there;
+            hv_launch *const L = cmd == "run" ? nullptr : shape(&l);
             std::vector<hv_request> rq((size_t)n);
             std::vector<hv_tile> tiles((size_t)n);
             for (int64_t k = 0; k < n; ++k) {
                 memset(&tiles[k], 0, sizeof tiles[k]);
                 tiles[k].z = z;
-                rq[k] = hv_request{ix[name], z, 0, 0, 0, 2.0};
+                rq[k] = hv_request{ix[name], k < there ? z : 22, 0, 0, 0, 2.0};
             }
             if (cmd == "batch") rc = hv_render_batch(rq.data(), n, out, L);
             else if (cmd == "aa") rc = hv_render_batch_aa(rq.data(), n, out, L);

@@ -131,3 +131,21 @@ def test_autotune_candidates(exe):
     one_wave = [w.rsplit(":", 3) for w in whole if w.rsplit(":", 3)[2] == "64" and "<32,2," in w]
     lds = sorted({f[3] for f in one_wave})
     assert len(lds) == 3 and len(one_wave) == 6, one_wave  # queues of 64, 96, 128, two grids each
+
+
+@pytest.mark.parametrize("n,dense,waves", [(1, 1, 4), (1023, 1023, 4), (1024, 255, 4), (1024, 256, 2), (4095, 4095, 2),
+                                           (4096, 1023, 2), (4096, 1024, 1), (9000, 0, 4), (9000, 255, 4), (9000, 256, 2),
+                                           (9000, 9000, 1)])
+def test_waves_by_size_and_density(exe, n, dense, waves):
+    """The default's waves per region follow the batch's size and how many of its
+    requests lie in dense data, in a batcher's graphs as in a call; a batcher too
+    small for a class of sizes takes the next."""
+    # 16,384 objects a tile and more count as dense: 300,000 at zoom 2
+    _, b, small, a, c, d = talk(exe, "build p 0 300000", "batcher b 10000", "batcher s 3000",
+                                f"run p b 2 {n} {dense}", f"run p s 2 {min(n, 3000)} {min(dense, 3000)}",
+                                f"batch p {2 if dense else 22} {n}")
+    assert b == ["0"] and small == ["0"]
+    assert kernels(a)[-1][2] == 64 * waves, kernels(a)
+    assert kernels(c)[-1][2] == 64 * max(waves, 2), kernels(c)
+    if dense in (0, n) and n > 64:
+        assert kernels(d)[-1][2] == 64 * waves, kernels(d)
