@@ -484,13 +484,15 @@ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Bits per axis of the Hilbert grid: enough for ~16 cells per object on
 // average, a multiple of 4 so that the key is a whole number of digits.
-int key_bits_for(int64_t n) {
+constexpr int key_bits_for(int64_t n) {
     int lg = 0;
     while ((int64_t(1) << lg) < n && lg < 62) ++lg;
     int kb = (lg + 1) / 2 + 4;
     kb = (kb + 3) / 4 * 4;
-    return std::min(32, std::max(8, kb));
+    return std::max(8, kb);
 }
+
+static_assert(2 * key_bits_for(HV_MAX_OBJECTS) <= 40, "keys are sorted as 8 and 32 bits");
 
 // Offsets of the arrays of one block.
 struct Carve {

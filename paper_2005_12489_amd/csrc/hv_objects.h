@@ -150,8 +150,9 @@ __device__ __forceinline__ void strip(const DevIndex &ix, const DevReq &rq, int6
     // FP64 test's, but few samples need one: an object grown by a radius is
     // convex, so a row of samples meets it in one run.  Outside the run for
     // r + kSlack no sample is within r, inside that for r - kSlack all are, FP32
-    // rounding included (it moves a run's end by less than a tenth of the
-    // slack), and the few between the two are tested.
+    // rounding included (at radii up to 64 px and columns up to 320 it moves a run's end by
+    // less than 6e-5 px), and the few between the two are tested.
+    static_assert(HV_MAX_RADIUS <= 64.0 && kSlack >= 1e-4, "the slack covers FP32's rounding of a run's ends");
     auto test_run = [&](int c, int ilo, int ihi, int j) {
         const double2 a = W.a[c];
         double2 d = make_double2(0.0, 0.0);

@@ -713,10 +713,12 @@ namespace {
 // the region's box grown by r, all lanes testing children together, and
 // queues every object that meets the box in LDS with the range of region
 // pixels within r of the object's box (the per-pixel box filter of
-// Algorithm 1 seen from the object's side).  The queue is then dealt out as
-// work cells -- (object, pixel row, group of 8 columns) -- evenly over all
-// lanes, whatever the objects' sizes: each cell tests at most 8 pixels
-// with the exact FP64 distance and sets the lit ones with one LDS OR.
+// Algorithm 1 seen from the object's side).  When the queue is full or the tree
+// done, it is drained: a point's rows by a lane, which lights their runs and
+// tests the pixels near the runs' ends (drain_points); of segments the units (row
+// in reach with an open pixel, group of 8 columns) are dealt evenly over the
+// lanes, each testing at most 8 pixels with the exact FP64 distance and setting
+// the lit ones with one LDS OR (drain_segments).
 
 // Most children an inner traversal step of a region tests (16 popped nodes).
 constexpr int kInnerWidth = 256;
