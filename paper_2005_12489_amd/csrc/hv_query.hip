@@ -739,11 +739,11 @@ __host__ __device__ inline int query_stack_words(int levels, int threads, int pe
     return kFrontier + width * (levels > 1 ? levels - 1 : 0);
 }
 
-// stack | queued objects (SoA) | units of exact tests | mask rows (four sets
-// for anti-aliased output, one per sub-sample) | control
+// stack | queued objects (SoA) | mask rows (four sets for anti-aliased output,
+// one per sub-sample) | control
 __host__ __device__ inline size_t region_lds_bytes(int cap, int levels, int threads, int rs, int opl, int aa = 0) {
     return align16((size_t)query_stack_words(levels, threads, opl) * 4) + align16((size_t)cap * kCandBytes) +
-           align16((size_t)cap * 4) + align16((size_t)rs * (rs / 32) * 4 * (aa ? 4 : 1)) + 16;
+           align16((size_t)rs * (rs / 32) * 4 * (aa ? 4 : 1)) + 16;
 }
 
 struct RegionLds {
