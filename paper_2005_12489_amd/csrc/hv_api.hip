@@ -223,7 +223,7 @@ int run_batch(const hv::DevIndex *ixs, int n_ix, int max_levels, const hv::DevRe
     if (e == hipSuccess) e = hipEventRecord(st.ev, t_stream);
     if (e == hipSuccess) {
         st.pending = true;
-        e = hv::launch_query(w, dws, max_levels, shape, t_stream, marks);
+        e = hv::launch_query(w, dws, max_levels, shape, t_stream, marks, hv::strips_pay(ixs, reqs, n_req));
     }
     const hipError_t ef = hipFreeAsync(dws, t_stream);
     if (e != hipSuccess) return hip_status(e, who);
@@ -1337,7 +1337,8 @@ int hv_render_batch_noalloc(const hv_request *reqs, int64_t n, uint8_t *out_mask
     // overwrites a workspace that an earlier call on the same stream still uses.
     hipError_t e = hipMemcpyAsync(ws, g_noalloc_host, w.staged_bytes(), hipMemcpyHostToDevice, t_stream);
     if (e == hipSuccess) e = hipStreamSynchronize(t_stream);
-    if (e == hipSuccess) e = hv::launch_query(w, ws, max_levels, shape, t_stream);
+    if (e == hipSuccess)
+        e = hv::launch_query(w, ws, max_levels, shape, t_stream, nullptr, hv::strips_pay(table, g_noalloc_reqs, n));
     if (e != hipSuccess) return hip_status(e, "hv_render_batch_noalloc");
     t_err.clear();
     return HV_OK;

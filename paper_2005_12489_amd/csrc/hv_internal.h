@@ -224,8 +224,10 @@ DevBatch device_batch(const Workspace &w, unsigned char *dws);
 // (three events, or NULL) it records marks[0] before the frontier kernel,
 // marks[1] between the two and marks[2] after the query kernel.
 hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, const LaunchShape &s,
-                        hipStream_t stream, hipEvent_t *marks = nullptr);
-
+                        hipStream_t stream, hipEvent_t *marks = nullptr, bool strips = true);
+// Whether launch_query's strips are worth their launch to a batch (true where the
+// requests are not known yet).
+bool strips_pay(const DevIndex *ixs, const DevReq *reqs, int64_t n_req);
 
 // Batches that travel in the kernels' arguments: this many requests over this
 // many indexes, in the default shape or filling (and no number of workgroups is

@@ -2252,10 +2252,12 @@ __global__ __launch_bounds__(SELF ? 64 * kSelfFillWaves : 256) void k_few_fill(F
     fill_query<RS>(ix, rq, 0, part, f.nodes, f.meta, out, cap, L);
 }
 
-// Beyond the default's four-wave shape, batches of more than this many requests
-// launch the object kernel: alone, one tile of 10k points 54 us a call with it, 45
-// without, 64 of them 51 and 48 (kernels 30 and 50 us).
+// Beyond the default's four-wave shape strips take a launch of their own, which
+// a few requests need only where tiles are rich.  Single tiles in explicit shapes:
+// of 40 objects in the mean 54 us a call with it, 45 without; of 2,400 61 to 64
+// with and 65 to 72 without (the fullest 120 and 220 to 350).
 constexpr int64_t kOneLaunchRequests = 16;
+constexpr double kRichTile = 1024.0;  // objects a tile, were they spread evenly
 
 // Batches of up to this many requests take four wavefronts to a request's frontier.
 constexpr int64_t kWideFrontier = 512;
@@ -2377,15 +2379,14 @@ int persistent_grid(const LaunchShape &s, int max_levels) {
 }
 
 hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, const LaunchShape &s,
-                        hipStream_t st, hipEvent_t *marks) {
+                        hipStream_t st, hipEvent_t *marks, bool strips) {
     const int64_t n_req = w.n_req;  // requests the grids cover; the header holds how many are live
     if (n_req == 0) return hipSuccess;
     const DevBatch B = device_batch(w, dws);
     hipError_t e;
     if (marks && (e = hipEventRecord(marks[0], st)) != hipSuccess) return e;
     const double grow = s.aa ? 0.25 : 0.0;
-    // (the object kernel's own launch costs a few tiles more than strips save them)
-    const int objects = s.region && !s.fill && (in_one_launch(s) || n_req > kOneLaunchRequests);
+    const int objects = s.region && !s.fill && (in_one_launch(s) || strips);
     if (n_req <= kWideFrontier)
         hipLaunchKernelGGL(k_tile_frontier<4>, dim3((uint32_t)n_req), dim3(256), 0, st, B, s.region, s.cull, grow, objects);
     else
@@ -2423,6 +2424,13 @@ hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, 
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (marks && (e = hipEventRecord(marks[2], st)) != hipSuccess) return e;
     return hipSuccess;
+}
+
+bool strips_pay(const DevIndex *ixs, const DevReq *reqs, int64_t n_req) {
+    if (n_req > kOneLaunchRequests) return true;
+    for (int64_t k = 0; k < n_req; ++k)
+        if ((double)ixs[reqs[k].index].n >= ldexp(kRichTile, 2 * reqs[k].z)) return true;
+    return false;
 }
 
 bool few_requests(const LaunchShape &s, int64_t n_req, int n_ix) {
