@@ -283,9 +283,13 @@ __device__ inline double object_extent(const DevIndex &ix) {
 //    pixels lit: only sparse leaves of batches that fill the GPU go by strips.
 //    (extent: the median over the index.)  Among nodes larger than the tile most
 //    objects miss it, and every region would look at all of them.
-//  - Where leaves are small to the radius (as if the nodes shared the tile's area),
-//    regions read few objects: cells settle most pixels, or in denser sets accepts
-//    light them.  (Anti-aliased, accepts run on four grids, and strips take both.)
+//  - Where objects cover the tile many times over, the cells settle most pixels, and
+//    where leaves are small to the radius (as if the nodes shared the tile's area),
+//    accepts light them: regions then read few objects.  (Anti-aliased, accepts run
+//    on four grids, and strips take both.)  The first line is drawn where regions
+//    win twofold in batches of such tiles, for in mixed batches they come as a few
+//    slow ones: 1,024 requests of clustered points 157 us with regions from half
+//    that cover on, 137 like this.
 //  - In small batches regions find idle compute units, and strips are too few: of
 //    binary tiles, those with little in reach go by strips, of anti-aliased ones
 //    the dense, whose regions' accepts take longest.
@@ -296,15 +300,15 @@ __device__ inline double object_extent(const DevIndex &ix) {
 // 16 tiles: 30 px segments, 500 a tile, 77 / 43; points, 2,000 a tile, r = 4 48 / 34.
 // The lines were fitted to 22,000 such measurements, 20 to 60,000 objects a tile, 1
 // to 1,024 tiles, r = 1/2 to 64, with cells that reach the zoom and without: the
-// choice is within 3% of the better of the two in the mean.
+// choice is within 4% of the better of the two in the mean.
 // Called by whole wavefronts.  (The nodes' order differs from one workgroup's walk
 // to another's, and all workgroups of a tile have to decide alike.)
 constexpr double kObjectsRadius = 1.0;
 constexpr double kNarrow = 12.0, kThin = 4.0;  // px: the reach on both sides and an object's extent
-constexpr double kDenseAA = 5.0, kDenseCells = 4.0, kDense = 1.5;  // diagonal of a leaf to the radius
+constexpr float kDenseAA = 5.0f, kDense = 1.5f;  // diagonal of a leaf to the radius
+constexpr float kCovered = 24.0f;               // area within r of an object to the tile's, objects added up
 constexpr int kSparse = 64, kTiny = 8;         // frontier nodes of tiles that small batches take
 constexpr int64_t kFullRequests = 192;         // more fill the GPU
-constexpr double kLong = 64.0;                  // px: objects that can make many overlapping nodes larger than the tile
 constexpr int kManyNodes = 32, kWideLeaves = 160, kWideNodes = 32, kWideLeavesAA = 32;
 __device__ inline bool by_objects(const DevIndex &ix, const DevReq &rq, double extent, const Frontier &f, bool aa, int64_t requests) {
     const int n = f.n, level = f.level;
@@ -315,36 +319,43 @@ __device__ inline bool by_objects(const DevIndex &ix, const DevReq &rq, double e
     const auto cells = [&] { return !aa && cell_shift(ix, rq.z, rq.r) >= 0; };
     if (level == 2 && !(n <= kObjectUpper && ix.seg && rq.r < kObjectsRadius && !cells())) return false;
     const double S = ldexp(256.0, rq.z), over = reach + extent * S;
-    if (over > kNarrow) {
-        if (reach <= kNarrow && ((n > kManyNodes && extent * S >= kLong) || (level > 0 && !spare))) {
-            const int lane = threadIdx.x & 63;
-            int huge = 0;
-            for (int base = 0; base < n; base += 64) {
-                double d2 = 0.0;
-                if (base + lane < n) {
-                    const double4 nb = ix.nodes[ix.meta[level] + f.nodes[base + lane]];
-                    const double w = (nb.z - nb.x) * S, h = (nb.w - nb.y) * S;
-                    d2 = w * w + h * h;
-                }
-                huge += __popcll(__ballot(d2 >= 65536.0));
+    // whether most nodes are larger than the tile
+    const auto huge = [&] {
+        const int lane = threadIdx.x & 63;
+        int count = 0;
+        for (int base = 0; base < n; base += 64) {
+            double d2 = 0.0;
+            if (base + lane < n) {
+                const double4 nb = ix.nodes[ix.meta[level] + f.nodes[base + lane]];
+                const double w = (nb.z - nb.x) * S, h = (nb.w - nb.y) * S;
+                d2 = w * w + h * h;
             }
-            if (2 * huge > n) return true;
+            count += __popcll(__ballot(d2 >= 65536.0));
         }
+        return 2 * count > n;
+    };
+    if (over > kNarrow) {
+        if (reach <= kNarrow && (n > kManyNodes || level > 0) && huge()) return true;
         return requests > kFullRequests && level < 2 &&
                n <= (level ? (aa || reach > kNarrow / 2 ? 0 : kWideNodes) : aa ? kWideLeavesAA : kWideLeaves);
     }
-    if (spare && !aa && n > kSparse && over > kThin) return false;
+    if (spare && !aa && level < 2 && n > kSparse && over > kThin) return level > 0 && huge();
     bool dense = false;
-    if (rq.r >= kObjectsRadius) {
-        const float leaf = 1.41f * (ldexpf((256.0f + (float)reach) * __builtin_amdgcn_rsqf((float)n), -2 * level) + 0.7f * (float)(extent * S));
-        dense = leaf <= (float)((aa ? kDenseAA : cells() ? kDenseCells : kDense) * rq.r);
+    const float tile = 256.0f + (float)reach, r = (float)rq.r;
+    if (rq.r >= kObjectsRadius && cells()) {
+        dense = ldexpf(16.0f * (float)n, 4 * level) * r * (3.14f * r + 2.0f * (float)(extent * S)) >= kCovered * tile * tile;
+    } else if (rq.r >= kObjectsRadius) {
+        const float leaf = 1.41f * (ldexpf(tile * __builtin_amdgcn_rsqf((float)n), -2 * level) + 0.7f * (float)(extent * S));
+        dense = leaf <= (aa ? kDenseAA : kDense) * r;
     }
     if (aa) return dense || !spare;
     return !dense;
 }
 
 // objects: tiles by_objects() go to the object kernel's lists, not to the region
-// kernel's.
+// kernel's.  2: it is a launch of its own, and strips do not fill the regions'
+// waits: no batch of more than one request is a small one (64 anti-aliased tiles
+// of clustered points, one wave to a region, 151 us a call instead of 271).
 template <int WPT>
 __global__ __launch_bounds__(256) void k_tile_frontier(DevBatch B, int rs, int cull, double grow, int objects) {
     static_assert(4 % WPT == 0, "a workgroup is four wavefronts");
@@ -368,7 +379,8 @@ __global__ __launch_bounds__(256) void k_tile_frontier(DevBatch B, int rs, int c
     }
     for (int k = tid; k < f.n; k += 64 * WPT) B.frontier[t * kFrontier + k] = f.nodes[k];
     if (tid >= 64) return;
-    const bool strips = objects && by_objects(ix, rq, extent, f, grow != 0.0, n_req);
+    const int64_t batch = objects > 1 && n_req > 1 && n_req <= kFewRequests ? kFewRequests + 1 : n_req;
+    const bool strips = objects && by_objects(ix, rq, extent, f, grow != 0.0, batch);
     if (tid == 0) {
         reinterpret_cast<int4 *>(B.fmeta)[t] = make_int4(f.n, f.level, (int)(uint32_t)f.regions, (int)(uint32_t)(f.regions >> 32));
         B.done[t] = 0;
@@ -2253,11 +2265,12 @@ __global__ __launch_bounds__(SELF ? 64 * kSelfFillWaves : 256) void k_few_fill(F
 }
 
 // Beyond the default's four-wave shape strips take a launch of their own, which
-// a few requests need only where tiles are rich.  Single tiles in explicit shapes:
-// of 40 objects in the mean 54 us a call with it, 45 without; of 2,400 61 to 64
-// with and 65 to 72 without (the fullest 120 and 220 to 350).
+// a few requests need only where a tile can hold much.  Single tiles in explicit
+// shapes: of an index of 10k points 54 us a call with it, 45 without; of 10M
+// segments at zoom 6 61 to 64 with and 65 to 72 without (the fullest 120 and 220 to
+// 350); 8 tiles of clustered 1M points, anti-aliased, 124 and 165 to 210.
 constexpr int64_t kOneLaunchRequests = 16;
-constexpr double kRichTile = 1024.0;  // objects a tile, were they spread evenly
+constexpr int64_t kRichIndex = 65536;
 
 // Batches of up to this many requests take four wavefronts to a request's frontier.
 constexpr int64_t kWideFrontier = 512;
@@ -2386,7 +2399,7 @@ hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, 
     hipError_t e;
     if (marks && (e = hipEventRecord(marks[0], st)) != hipSuccess) return e;
     const double grow = s.aa ? 0.25 : 0.0;
-    const int objects = s.region && !s.fill && (in_one_launch(s) || strips);
+    const int objects = !s.region || s.fill ? 0 : in_one_launch(s) ? 1 : strips ? 2 : 0;
     if (n_req <= kWideFrontier)
         hipLaunchKernelGGL(k_tile_frontier<4>, dim3((uint32_t)n_req), dim3(256), 0, st, B, s.region, s.cull, grow, objects);
     else
@@ -2429,7 +2442,7 @@ hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, 
 bool strips_pay(const DevIndex *ixs, const DevReq *reqs, int64_t n_req) {
     if (n_req > kOneLaunchRequests) return true;
     for (int64_t k = 0; k < n_req; ++k)
-        if ((double)ixs[reqs[k].index].n >= ldexp(kRichTile, 2 * reqs[k].z)) return true;
+        if (ixs[reqs[k].index].n >= kRichIndex) return true;
     return false;
 }
 
