@@ -2272,8 +2272,10 @@ __global__ __launch_bounds__(SELF ? 64 * kSelfFillWaves : 256) void k_few_fill(F
 constexpr int64_t kOneLaunchRequests = 16;
 constexpr int64_t kRichIndex = 65536;
 
-// Batches of up to this many requests take four wavefronts to a request's frontier.
-constexpr int64_t kWideFrontier = 512;
+// Batches of up to this many requests take four wavefronts to a request's frontier:
+// four / one take 23 / 32 us for 512 requests, 29 / 37 for 1,024, 66 / 52 for 2,048
+// and 149 / 73 for 4,096 (2e8 clustered points; segments alike).
+constexpr int64_t kWideFrontier = 1024;
 
 using RegionKernel = void (*)(DevBatch, int, int);
 
@@ -2421,8 +2423,9 @@ hipError_t launch_query(const Workspace &w, unsigned char *dws, int max_levels, 
     // Filling's regions, and in large batches the distance kernel's, differ in
     // cost by orders of magnitude (clusters next to empty sea, settled regions
     // next to walked ones), so each gets its own workgroup and the dispatcher
-    // balances them: 10,000 requests over 1e9 points took 6.1 ms instead of 6.8
-    // with a persistent grid, while walks were longer (3.65 to 3.73 either way since).  Smaller batches (more waves to a region) and
+    // balances them: 10,000 requests over 2e8 points take 3.51 ms instead of 3.66
+    // with a persistent grid, over 2e8 edges 5.52 instead of 5.62; 4,096 requests
+    // 2% less to 4% more.  Smaller batches (more waves to a region) and
     // anti-aliased ones keep that grid (10M segments 0.90 ms instead of 0.93).
     const bool spread = s.fill || (s.region && !s.aa && s.waves == 1);
     int64_t grid = s.grid > 0 ? s.grid : spread ? kSpreadGrid : persistent_grid(s, max_levels);

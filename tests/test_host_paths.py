@@ -150,3 +150,10 @@ def test_waves_by_size_and_density(exe, n, dense, waves):
     assert kernels(c)[-1][2] == 64 * max(waves, 2), kernels(c)
     if dense in (0, n) and n > 64:
         assert kernels(d)[-1][2] == 64 * waves, kernels(d)
+
+
+def test_frontier_waves(exe):
+    """Four wavefronts to a request's frontier in batches of up to 1,024."""
+    _, a, b = talk(exe, "build p 0 100000", "batch p 4 1024", "batch p 4 1025")
+    assert kernels(a)[0] == ("k_tile_frontier<4>", 1024, 256)
+    assert kernels(b)[0] == ("k_tile_frontier<1>", 257, 256)
