@@ -419,6 +419,9 @@ def fill_bench(args, hv, torch):
     frontier_ms, fill_ms = hv.hv_time_fill(h, t4, out, launch, reps=max(args.steps, 3))
     roofline = roofline_record(WORKLOADS["c4fill"]["name"], launch, frontier_ms, fill_ms,
                                kernel=fill_kernel_name(launch))
+    if roofline:
+        roofline["alg_bytes_note"] = ("edges that a ray from the candidate polygons' rows crosses; no lower bound: "
+                                      "pixels settled from cells or filled by another polygon need none of them")
     per_tile = None
     if not args.no_per_tile:
         pe = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(n)]
